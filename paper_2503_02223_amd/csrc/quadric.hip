@@ -230,14 +230,34 @@ __global__ __launch_bounds__(64) void fit_quadric_kernel(int n_obj, int n_views,
     status[k] = st;
 }
 
-// Boxes of the objects in rendered id maps: one workgroup per view reduces the
-// per-object min/max pixel coordinates in LDS, then writes its K boxes.
-__global__ __launch_bounds__(256) void id_boxes_kernel(const int32_t* __restrict__ id_map, int W, int H, int K,
-                                                       double* __restrict__ boxes, int32_t* __restrict__ box_obj,
-                                                       int32_t* __restrict__ box_view) {
-    __shared__ int s_box[DQO_MAX_K][4];
-    const int v = blockIdx.x;
-    for (int k = threadIdx.x; k < K; k += blockDim.x) {
+// Boxes of the objects in rendered id maps, in three passes over the output
+// array itself (the first 16 bytes of a box's four doubles hold its integer
+// bounds until the last pass widens them): clear, reduce, finish.  The
+// reduction is spread over workgroups of kBoxRows image rows.  Each keeps the
+// objects' bounds in LDS and reads an object's bounds before it updates them:
+// they only ever widen, so a stale value can cost an atomic but not lose one,
+// and almost every pixel lies inside the bounds that its neighbours have left.
+// Bound by the read of the id map (4 B per pixel): one workgroup per view with
+// four LDS atomics per pixel took 725 us at 640x480, these three launches
+// 12 us.
+constexpr int kBoxThreads = 256;
+constexpr int kBoxRows = 8;
+
+__global__ __launch_bounds__(kBoxThreads) void id_boxes_clear_kernel(int n, int W, int H, int* __restrict__ boxes) {
+    const int b = blockIdx.x * kBoxThreads + threadIdx.x;
+    if (b >= n) return;
+    int* o = boxes + 8 * (int64_t)b;
+    o[0] = W;
+    o[1] = H;
+    o[2] = -1;
+    o[3] = -1;
+}
+
+__global__ __launch_bounds__(kBoxThreads) void id_boxes_kernel(const int32_t* __restrict__ id_map, int W, int H, int K,
+                                                               int* __restrict__ boxes) {
+    __shared__ __align__(16) int s_box[DQO_MAX_K][4];
+    const int v = blockIdx.y, y0 = blockIdx.x * kBoxRows, y1 = min(H, y0 + kBoxRows);
+    for (int k = threadIdx.x; k < K; k += kBoxThreads) {
         s_box[k][0] = W;
         s_box[k][1] = H;
         s_box[k][2] = -1;
@@ -245,31 +265,60 @@ __global__ __launch_bounds__(256) void id_boxes_kernel(const int32_t* __restrict
     }
     __syncthreads();
     const int32_t* im = id_map + (int64_t)v * W * H;
-    for (int64_t i = threadIdx.x; i < (int64_t)W * H; i += blockDim.x) {
-        const int k = im[i];
-        if (k < 0 || k >= K) continue;
-        const int u = (int)(i % W), y = (int)(i / W);
-        atomicMin(&s_box[k][0], u);
-        atomicMin(&s_box[k][1], y);
-        atomicMax(&s_box[k][2], u);
-        atomicMax(&s_box[k][3], y);
+    for (int x0 = 0; x0 < W; x0 += kBoxThreads) {
+        const int u = x0 + (int)threadIdx.x;
+        int id[kBoxRows];  // a column of the strip: its loads are in flight together
+#pragma unroll
+        for (int r = 0; r < kBoxRows; ++r) id[r] = (u < W && y0 + r < y1) ? im[(int64_t)(y0 + r) * W + u] : -1;
+#pragma unroll
+        for (int r = 0; r < kBoxRows; ++r) {
+            const int k = id[r], y = y0 + r;
+            if (k < 0 || k >= K) continue;
+            const int4 c = *reinterpret_cast<const int4*>(s_box[k]);
+            if (u < c.x) atomicMin(&s_box[k][0], u);
+            if (y < c.y) atomicMin(&s_box[k][1], y);
+            if (u > c.z) atomicMax(&s_box[k][2], u);
+            if (y > c.w) atomicMax(&s_box[k][3], y);
+        }
     }
     __syncthreads();
-    for (int k = threadIdx.x; k < K; k += blockDim.x) {
-        const int64_t b = (int64_t)v * K + k;
-        const bool seen = s_box[k][2] >= 0;
-        boxes[4 * b + 0] = seen ? (double)s_box[k][0] : 0.0;
-        boxes[4 * b + 1] = seen ? (double)s_box[k][1] : 0.0;
-        boxes[4 * b + 2] = seen ? (double)(s_box[k][2] + 1) : 0.0;
-        boxes[4 * b + 3] = seen ? (double)(s_box[k][3] + 1) : 0.0;
-        box_obj[b] = seen ? k : -1;
-        box_view[b] = v;
+    for (int k = threadIdx.x; k < K; k += kBoxThreads) {
+        if (s_box[k][2] < 0) continue;
+        int* o = boxes + 8 * ((int64_t)v * K + k);
+        atomicMin(&o[0], s_box[k][0]);
+        atomicMin(&o[1], s_box[k][1]);
+        atomicMax(&o[2], s_box[k][2]);
+        atomicMax(&o[3], s_box[k][3]);
     }
+}
+
+__global__ __launch_bounds__(kBoxThreads) void id_boxes_finish_kernel(int n, int K, int* __restrict__ boxes,
+                                                                      int32_t* __restrict__ box_obj,
+                                                                      int32_t* __restrict__ box_view) {
+    const int b = blockIdx.x * kBoxThreads + threadIdx.x;
+    if (b >= n) return;
+    int* o = boxes + 8 * (int64_t)b;
+    const bool seen = o[2] >= 0;
+    const int e[4] = {o[0], o[1], o[2] + 1, o[3] + 1};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {  // the doubles as words: one element type for the whole array
+        const double d = seen ? (double)e[c] : 0.0;
+        o[2 * c] = __double2loint(d);
+        o[2 * c + 1] = __double2hiint(d);
+    }
+    box_obj[b] = seen ? b % K : -1;
+    box_view[b] = b / K;
 }
 
 hipError_t launch_id_boxes(const int32_t* id_map, int n_views, int W, int H, int K, double* boxes, int32_t* box_obj,
                            int32_t* box_view, hipStream_t st) {
-    hipLaunchKernelGGL(id_boxes_kernel, dim3(n_views), dim3(256), 0, st, id_map, W, H, K, boxes, box_obj, box_view);
+    const int n = n_views * K;
+    const dim3 per_box((unsigned)((n + kBoxThreads - 1) / kBoxThreads));
+    hipLaunchKernelGGL(id_boxes_clear_kernel, per_box, dim3(kBoxThreads), 0, st, n, W, H, (int*)boxes);
+    hipLaunchKernelGGL(id_boxes_kernel, dim3((unsigned)((H + kBoxRows - 1) / kBoxRows), (unsigned)n_views),
+                       dim3(kBoxThreads), 0, st, id_map, W, H, K, (int*)boxes);
+    hipLaunchKernelGGL(id_boxes_finish_kernel, per_box, dim3(kBoxThreads), 0, st, n, K, (int*)boxes, box_obj,
+                       box_view);
     return hipGetLastError();
 }
 
