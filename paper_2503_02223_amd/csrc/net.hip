@@ -298,23 +298,47 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(int S, int64_t E, int
     }
 }
 
-// Smallest valid depth of each crop (one workgroup per crop).
-__global__ __launch_bounds__(256) void dmin_kernel(int HW, const float* __restrict__ rgbdm, float* __restrict__ dmin) {
+// Per-crop reductions (smallest depth, mean log-error, PSNR): one workgroup of
+// kCropThreads per crop, kCropUnroll pixels per thread in flight, wavefront
+// shuffles and one LDS step.  They are bound by the latency of one CU's reads
+// (128 KB per 128x128 crop): 256 threads with one pixel in flight and a
+// barrier tree took 10 to 30 us.
+constexpr int kCropThreads = 1024;
+constexpr int kCropUnroll = 4;
+
+// The workgroup's combination of one value per thread, in thread 0 (a fixed order).
+template <typename A, typename F>
+__device__ __forceinline__ A crop_reduce(A v, A (&s)[kCropThreads / kWave], F f) {
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) v = f(v, (A)__shfl_xor(v, d));
+    if ((threadIdx.x & (kWave - 1)) == 0) s[threadIdx.x >> 6] = v;
+    __syncthreads();
+    A r = s[0];
+    for (int w = 1; w < kCropThreads / kWave; ++w) r = f(r, s[w]);
+    return r;
+}
+
+// Smallest valid depth of each crop.
+__global__ __launch_bounds__(kCropThreads) void dmin_kernel(int HW, const float* __restrict__ rgbdm,
+                                                            float* __restrict__ dmin) {
+    __shared__ float s[kCropThreads / kWave];
     const int b = blockIdx.x;
     const float* base = rgbdm + (size_t)b * 5 * HW;
     float m = INFINITY;
-    for (int i = threadIdx.x; i < HW; i += 256) {
-        const float d = base[3 * HW + i];
-        if (base[4 * HW + i] > 0.5f && d > 0.0f) m = fminf(m, d);
+    for (int i0 = threadIdx.x; i0 < HW; i0 += kCropUnroll * kCropThreads) {
+        float d[kCropUnroll], k[kCropUnroll];
+#pragma unroll
+        for (int u = 0; u < kCropUnroll; ++u) {
+            const int i = min(i0 + u * kCropThreads, HW - 1);  // a pixel twice does not change the least
+            d[u] = base[3 * HW + i];
+            k[u] = base[4 * HW + i];
+        }
+#pragma unroll
+        for (int u = 0; u < kCropUnroll; ++u)
+            if (k[u] > 0.5f && d[u] > 0.0f) m = fminf(m, d[u]);
     }
-    __shared__ float s[256];
-    s[threadIdx.x] = m;
-    __syncthreads();
-    for (int k = 128; k > 0; k >>= 1) {
-        if (threadIdx.x < k) s[threadIdx.x] = fminf(s[threadIdx.x], s[threadIdx.x + k]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) dmin[b] = s[0];
+    m = crop_reduce(m, s, [](float a, float c) { return fminf(a, c); });
+    if (threadIdx.x == 0) dmin[b] = m;
 }
 
 // NHWC16 BF16 input: r, g, b, 4 (d - d_min) / d_min (valid pixels), valid, zeros.
@@ -466,65 +490,78 @@ __global__ __launch_bounds__(256) void loss_final_kernel(int nblk, const double*
 }
 
 // Mean predicted log-error over each crop's valid pixels and the decision.
-__global__ __launch_bounds__(256) void fallback_kernel(int HW, const float* __restrict__ rgbdm,
-                                                       const float* __restrict__ out, float thr,
-                                                       int32_t* __restrict__ use_pred, float* __restrict__ mean_out) {
-    const int b = blockIdx.x;
+__global__ __launch_bounds__(kCropThreads) void fallback_kernel(int HW, const float* __restrict__ rgbdm,
+                                                                const float* __restrict__ out, float thr,
+                                                                int32_t* __restrict__ use_pred,
+                                                                float* __restrict__ mean_out) {
+    __shared__ float ss[kCropThreads / kWave];
+    __shared__ int sc[kCropThreads / kWave];
+    const int64_t b = blockIdx.x;
+    const float* c5 = rgbdm + b * 5 * HW;
+    const float* o = out + (b * 6 + 5) * HW;
     float s = 0.0f;
     int c = 0;
-    for (int i = threadIdx.x; i < HW; i += 256)
-        if (valid_px(rgbdm, HW, (int64_t)b * 5 * HW + i)) {
-            s += out[((int64_t)b * 6 + 5) * HW + i];
-            ++c;
+    for (int i0 = threadIdx.x; i0 < HW; i0 += kCropUnroll * kCropThreads) {
+        float d[kCropUnroll], k[kCropUnroll], e[kCropUnroll];
+#pragma unroll
+        for (int u = 0; u < kCropUnroll; ++u) {
+            const int i = min(i0 + u * kCropThreads, HW - 1);
+            d[u] = c5[3 * (int64_t)HW + i];
+            k[u] = c5[4 * (int64_t)HW + i];
+            e[u] = o[i];
         }
-    __shared__ float ss[256];
-    __shared__ int sc[256];
-    ss[threadIdx.x] = s;
-    sc[threadIdx.x] = c;
-    __syncthreads();
-    for (int k = 128; k > 0; k >>= 1) {
-        if (threadIdx.x < k) {
-            ss[threadIdx.x] += ss[threadIdx.x + k];
-            sc[threadIdx.x] += sc[threadIdx.x + k];
-        }
-        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kCropUnroll; ++u)
+            if (i0 + u * kCropThreads < HW && k[u] > 0.5f && d[u] > 0.0f) {
+                s += e[u];
+                ++c;
+            }
     }
+    s = crop_reduce(s, ss, [](float a, float x) { return a + x; });
+    c = crop_reduce(c, sc, [](int a, int x) { return a + x; });
     if (threadIdx.x == 0) {
-        const float mean = sc[0] > 0 ? ss[0] / (float)sc[0] : INFINITY;
+        const float mean = c > 0 ? s / (float)c : INFINITY;
         use_pred[b] = mean <= thr ? 1 : 0;
         if (mean_out) mean_out[b] = mean;
     }
 }
 
-__global__ __launch_bounds__(256) void psnr_kernel(int HW, const float* __restrict__ color,
-                                                   const float* __restrict__ rgbdm, double* __restrict__ psnr) {
-    const int v = blockIdx.x;
+__global__ __launch_bounds__(kCropThreads) void psnr_kernel(int HW, const float* __restrict__ color,
+                                                            const float* __restrict__ rgbdm, double* __restrict__ psnr) {
+    __shared__ double ss[kCropThreads / kWave];
+    __shared__ int sc[kCropThreads / kWave];
+    const int64_t v = blockIdx.x, N = HW;
+    const float* c5 = rgbdm + v * 5 * N;
+    const float* col = color + v * 3 * N;
     double s = 0.0;
     int c = 0;
-    for (int i = threadIdx.x; i < HW; i += 256) {
-        const int64_t base = (int64_t)v * 5 * HW + i;
-        if (valid_px(rgbdm, HW, base)) {
+    for (int i0 = threadIdx.x; i0 < HW; i0 += kCropUnroll * kCropThreads) {
+        float d[kCropUnroll], k[kCropUnroll], a[kCropUnroll][3], t[kCropUnroll][3];
 #pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                const double e = (double)color[((int64_t)v * 3 + k) * HW + i] - (double)rgbdm[base + k * HW];
-                s += e * e;
+        for (int u = 0; u < kCropUnroll; ++u) {
+            const int64_t i = min(i0 + u * kCropThreads, HW - 1);
+            d[u] = c5[3 * N + i];
+            k[u] = c5[4 * N + i];
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                a[u][q] = col[q * N + i];
+                t[u][q] = c5[q * N + i];
             }
-            ++c;
         }
+#pragma unroll
+        for (int u = 0; u < kCropUnroll; ++u)
+            if (i0 + u * kCropThreads < HW && k[u] > 0.5f && d[u] > 0.0f) {
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    const double e = (double)a[u][q] - (double)t[u][q];
+                    s += e * e;
+                }
+                ++c;
+            }
     }
-    __shared__ double ss[256];
-    __shared__ int sc[256];
-    ss[threadIdx.x] = s;
-    sc[threadIdx.x] = c;
-    __syncthreads();
-    for (int k = 128; k > 0; k >>= 1) {
-        if (threadIdx.x < k) {
-            ss[threadIdx.x] += ss[threadIdx.x + k];
-            sc[threadIdx.x] += sc[threadIdx.x + k];
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) psnr[v] = sc[0] > 0 ? 10.0 * log10(3.0 * sc[0] / ss[0]) : 0.0;
+    s = crop_reduce(s, ss, [](double x, double y) { return x + y; });
+    c = crop_reduce(c, sc, [](int x, int y) { return x + y; });
+    if (threadIdx.x == 0) psnr[v] = c > 0 ? 10.0 * log10(3.0 * c / s) : 0.0;
 }
 
 // ------------------------------------------------------------------ launchers
@@ -564,7 +601,7 @@ hipError_t launch_forward(const dqo_net_layout& L, const Work& w, int B, int H, 
     const int HW = H * W;
     const int64_t P = (int64_t)B * HW;
     const unsigned pb = (unsigned)((P + 255) / 256);
-    hipLaunchKernelGGL(dmin_kernel, dim3(B), dim3(256), 0, st, HW, rgbdm, w.dmin);
+    hipLaunchKernelGGL(dmin_kernel, dim3(B), dim3(kCropThreads), 0, st, HW, rgbdm, w.dmin);
     hipLaunchKernelGGL(input_kernel, dim3(pb), dim3(256), 0, st, P, HW, rgbdm, w.dmin, w.x0);
     conv<16, 32, kEpiRelu>(B, H, W, w.x0, wf + L.wk_offset[0], theta + L.b_offset[0], nullptr, w.a1, nullptr, 0, st);
     conv<32, 64, kEpiRelu>(B, H, W, w.a1, wf + L.wk_offset[1], theta + L.b_offset[1], nullptr, w.a2, nullptr, 0, st);
@@ -603,12 +640,12 @@ hipError_t launch_backward(const dqo_net_layout& L, const Work& w, int B, int H,
 
 hipError_t launch_fallback(int B, int H, int W, const float* rgbdm, const float* out, float thr, int32_t* use_pred,
                            float* mean_out, hipStream_t st) {
-    hipLaunchKernelGGL(fallback_kernel, dim3(B), dim3(256), 0, st, H * W, rgbdm, out, thr, use_pred, mean_out);
+    hipLaunchKernelGGL(fallback_kernel, dim3(B), dim3(kCropThreads), 0, st, H * W, rgbdm, out, thr, use_pred, mean_out);
     return hipGetLastError();
 }
 
 hipError_t launch_psnr(int V, int H, int W, const float* color, const float* rgbdm, double* psnr, hipStream_t st) {
-    hipLaunchKernelGGL(psnr_kernel, dim3(V), dim3(256), 0, st, H * W, color, rgbdm, psnr);
+    hipLaunchKernelGGL(psnr_kernel, dim3(V), dim3(kCropThreads), 0, st, H * W, color, rgbdm, psnr);
     return hipGetLastError();
 }
 
