@@ -115,7 +115,9 @@ typedef struct dqo_camera {
  * segments: NULL, in which case every view sees all n Gaussians, or
  *   [n_views][2] = (first, count): view v sees Gaussians [first, first + count)
  *   only.  Segments let one launch render independent Gaussian sets (object
- *   crops, per-object jobs) each in its own view; they may overlap.
+ *   crops, per-object jobs) each in its own view; they may overlap.  Only the
+ *   items inside their view's segment (the listed items) are projected and
+ *   sorted; the others have no tiles.
  * windows: NULL (whole images) or [n_views][4] = (x0, y0, x1, y1): view v
  *   renders only pixels x0 <= u < x1, y0 <= v < y1 (within the image; empty
  *   when x1 <= x0 or y1 <= y0).  Pixels outside the window are written as if
@@ -147,12 +149,14 @@ typedef struct dqo_frame_desc {
 enum dqo_buf {
     DQO_BUF_SPLATS = 0,  /* [V*n] records of 16 values: mx,my,A,B,C,opacity,z,id,r,g,b,0, first pair slot,
                             tile rectangle x0 | y0 << 16, rectangle width, 0 (integers as FP32 bit patterns,
-                            FP64 values) */
+                            FP64 values); written for the listed items */
     DQO_BUF_RECTS,       /* [V*n] int16x4 tile rectangle x0,y0,x1,y1 (inclusive), empty = x1<x0 */
     DQO_BUF_COUNTS,      /* [V*n] uint32 tiles covered */
-    DQO_BUF_OFFSETS,     /* [V*n] uint32 first slot of the item's pairs in emission order */
-    DQO_BUF_DEPTH_KEYS,  /* [V*n] uint32 sorted depth keys (float bits of z; culled = 0xffffffff) */
-    DQO_BUF_DEPTH_ORDER, /* [V*n] uint32 item index (view*n + g) in depth order (GLOBAL depth order only) */
+    DQO_BUF_OFFSETS,     /* [V*n] uint32 first slot of the item's pairs in emission order (listed items) */
+    DQO_BUF_DEPTH_KEYS,  /* [V*n] uint32 sorted depth keys (float bits of z; culled = 0xffffffff), one per
+                            listed item */
+    DQO_BUF_DEPTH_ORDER, /* [V*n] uint32 item index (view*n + g) in depth order (GLOBAL depth order only),
+                            one per listed item */
     DQO_BUF_PAIR_KEYS,   /* [cap] uint32 sorted global tile id (view*tiles + tile) */
     DQO_BUF_PAIR_VALS,   /* [cap] uint32 item index, in (tile, depth, index) order; after a render
                             forward, bit 31 is set on the pairs whose Gaussian cannot contribute at

@@ -30,7 +30,7 @@ int key_bits(int64_t tiles_total) {
 
 struct Geo {
     dqo_layout L;
-    int64_t items;
+    int64_t items, listed;
     int depth_blocks, scan_blocks, pair_blocks, pair_passes, pair_first_buf;
     int64_t lb_words;
     // scratch sub-offsets (relative to DQO_BUF_SCRATCH)
@@ -94,12 +94,26 @@ Geo geometry(const dqo_ctx* ctx, const dqo_frame_desc* d, const dqo_camera* cams
     g.pair_first_buf = g.pair_passes & 1;
     g.items = (int64_t)d->n * d->n_views;
     const int64_t M = g.items, cap = d->pair_capacity;
+    // Only the items inside their view's segment are projected, sorted and
+    // emitted.  The buffers hold any segments of these n and views, since the
+    // descriptor's arrays may change between calls on one state.
+    g.listed = M;
+    if (d->segments) {
+        g.listed = 0;
+        for (int v = 0; v < d->n_views; ++v) g.listed += d->segments[2 * v + 1];
+    }
     const int order = ctx->cfg.depth_order;
     g.tile_sort = order == DQO_DEPTH_ORDER_TILE;  // AUTO: GLOBAL
     g.tile_sort_lds = ctx->cfg.tile_sort_lds > 0 ? ctx->cfg.tile_sort_lds : 4096;
     const int64_t ts = d->dtype == DQO_F64 ? 8 : 4;
-    g.depth_blocks = (int)((M + kDepthNt * depth_ipt(M) - 1) / (kDepthNt * depth_ipt(M)));
-    g.scan_blocks = (int)((M + kScanTile - 1) / kScanTile);
+    auto depth_blocks = [](int64_t m) { return (int)((m + kDepthNt * depth_ipt(m) - 1) / (kDepthNt * depth_ipt(m))); };
+    g.depth_blocks = depth_blocks(g.listed);
+    g.scan_blocks = (int)((g.listed + kScanTile - 1) / kScanTile);
+    // the most blocks any listing of at most M items takes: blocks get longer
+    // at 2^18 and 2^19 items, so fewer items can need more of them
+    const int depth_blocks_max = std::max(depth_blocks(M), std::max(depth_blocks(std::min<int64_t>(M, (1 << 18) - 1)),
+                                                                    depth_blocks(std::min<int64_t>(M, (1 << 19) - 1))));
+    const int scan_blocks_max = (int)((M + kScanTile - 1) / kScanTile);
     g.pair_blocks = (int)((cap + kPairTileMin - 1) / kPairTileMin);
     int64_t sz[DQO_BUF_COUNT];
     sz[DQO_BUF_SPLATS] = M * kSplatWords * ts;
@@ -124,7 +138,7 @@ Geo geometry(const dqo_ctx* ctx, const dqo_frame_desc* d, const dqo_camera* cams
     g.off_sums = so; so = align256(so + M * kGradWords * ts);
     g.off_pose = so; so = align256(so + (int64_t)d->n_views * ((d->n + 255) / 256) * 6 * 8);
     g.off_written = so; so = align256(so + cap);
-    g.off_sbase = so; so = align256(so + (int64_t)g.scan_blocks * 4);
+    g.off_sbase = so; so = align256(so + (int64_t)scan_blocks_max * 4);
     // segment boundaries (64-pixel tiles, frames the backward segments):
     // sum over tiles of ceil(range / L) - 1 <= cap / L
     g.ckpt_cap = (tw * th == kWave && tiles_total <= kSegTilesMax) ? cap / kSegLen + 1 : 0;
@@ -134,8 +148,8 @@ Geo geometry(const dqo_ctx* ctx, const dqo_frame_desc* d, const dqo_camera* cams
     g.off_tlast = so; so = align256(so + tiles_total * 4);
     g.off_ckpt = so; so = align256(so + g.ckpt_cap * 6 * kWave * ts);
     // look-back words: every block's, then every group's (grouped look-back)
-    g.off_lbd = so; so = align256(so + (int64_t)kMaxDepthPasses * lb_blocks(g.depth_blocks) * kRadixBins * 8);
-    g.off_lbs = so; so = align256(so + (int64_t)lb_blocks(g.scan_blocks) * (kRadixBins + 1) * 8);
+    g.off_lbd = so; so = align256(so + (int64_t)kMaxDepthPasses * lb_blocks(depth_blocks_max) * kRadixBins * 8);
+    g.off_lbs = so; so = align256(so + (int64_t)lb_blocks(scan_blocks_max) * (kRadixBins + 1) * 8);
     g.off_lbp = so; so = align256(so + (int64_t)kMaxPairPasses * lb_blocks(g.pair_blocks) * kRadixBins * 8);
     g.lb_words = (so - g.off_lbd) / 8;
     sz[DQO_BUF_SCRATCH] = so;
@@ -185,6 +199,7 @@ StatePtrs state_ptrs(const Geo& g, void* state) {
     s.lb_scan = (uint64_t*)(sc + g.off_lbs);
     s.lb_pair = (uint64_t*)(sc + g.off_lbp);
     s.items = g.items;
+    s.listed = g.listed;
     s.capacity = g.L.bytes[DQO_BUF_PAIR_KEYS] / 4;
     s.depth_blocks = g.depth_blocks;
     s.scan_blocks = g.scan_blocks;
@@ -199,7 +214,7 @@ StatePtrs state_ptrs(const Geo& g, void* state) {
     s.fused_emit = DQO_FUSED_EMIT && g.pair_passes >= 1 && g.scan_blocks <= scan_emit_resident(true);
     // One histogram copy per 64 producer workgroups (up to kHistCopies): enough
     // to spread the atomics, few enough for the radix passes to sum cheaply.
-    const int64_t proj_blocks = (g.items + 256 * kProjItems - 1) / (256 * kProjItems);
+    const int64_t proj_blocks = (g.listed + 256 * kProjItems - 1) / (256 * kProjItems);
     s.hist_copies_depth = (int)std::max<int64_t>(1, std::min<int64_t>(kHistCopies, proj_blocks / 64));
     s.hist_copies_pair = (int)std::max<int64_t>(1, std::min<int64_t>(kHistCopies, g.scan_blocks / 64));
     return s;
@@ -241,6 +256,7 @@ Frame<T> make_frame(const dqo_ctx* ctx, const dqo_frame_desc* d, const dqo_camer
         dc.tile_x1 = x1 > x0 ? (x1 - 1) / tw : -1;
         dc.tile_y1 = y1 > y0 ? (y1 - 1) / th : -1;
         dc.job = d->jobs ? d->jobs[v] : -1;
+        f.views.list_off[v + 1] = f.views.list_off[v] + (uint32_t)(dc.seg_hi - dc.seg_lo);
     }
     f.views.n_views = d->n_views;
     f.views.W = cams[0].width;

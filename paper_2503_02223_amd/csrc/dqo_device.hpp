@@ -148,7 +148,19 @@ struct Views {
     int tile_w, tile_h;
     int tiles_x, tiles_y;
     int tiles_per_view;
+    // Listed items: the (view, Gaussian) items inside their view's segment, in
+    // item order (all items unless the frame has segments).  Entries
+    // [list_off[v], list_off[v + 1]) are view v's Gaussians seg_lo, seg_lo + 1, ...
+    uint32_t list_off[DQO_MAX_VIEWS + 1];
 };
+
+// The view of listed item j (a few uniform compares; one view: none).
+template <typename T>
+__device__ __forceinline__ int listed_view(const Views<T>& V, uint32_t j) {
+    int v = 0;
+    for (int k = 1; k < V.n_views; ++k) v += j >= V.list_off[k] ? 1 : 0;
+    return v;
+}
 
 template <typename T>
 struct Consts {
@@ -382,15 +394,16 @@ struct StatePtrs {
     uint64_t* lb_scan;    // [blocks][257]: 256 digits of the fused first pair pass, then the pair count
     uint64_t* lb_pair;    // [kMaxPairPasses][blocks][256]
     int64_t items;        // V * n
+    int64_t listed;       // items inside their view's segment (== items without segments): sorted and emitted
     int64_t capacity;
-    int depth_blocks;     // radix blocks over items
+    int depth_blocks;     // radix blocks over the listed items
     int scan_blocks;
     int pair_blocks;      // radix blocks over capacity
     int pair_passes;
     int pair_first_buf;   // buffer emission writes into so the sort ends in buffer 0
-    // Per-tile depth order: items are not sorted by depth; pairs are emitted
-    // in item order (order = identity) and each tile's pairs sorted after the
-    // tile sort.
+    // Per-tile depth order: items are not sorted by depth (their keys stay at
+    // their item index); pairs are emitted in item order and each tile's
+    // pairs sorted after the tile sort.
     bool tile_sort;
     bool fused_emit;      // the emission performs the first pair pass (resident scan grid)
     int tile_sort_lds;    // longest tile range sorted in LDS (longer ones: global-memory passes)
@@ -447,9 +460,12 @@ hipError_t launch_clear_ctrl(Ctrl* ctrl, uint64_t* lb, int64_t lb_words, hipStre
 hipError_t launch_clear_status(Ctrl* ctrl, hipStream_t st);
 hipError_t launch_zero_words(uint32_t* p, int64_t n, hipStream_t st);
 
-// The order in which items emit their pairs (and own consecutive pair
-// slots): the depth order, or item order (nullptr) under per-tile depth order.
-inline const uint32_t* item_order(const StatePtrs& s) { return s.tile_sort ? nullptr : s.depth_vals[0]; }
+// The order in which the listed items emit their pairs (and own consecutive
+// pair slots): the depth order, or under per-tile depth order the item order
+// (nullptr where every item is listed, else the list as projected).
+inline const uint32_t* item_order(const StatePtrs& s) {
+    return s.tile_sort && s.listed == s.items ? nullptr : s.depth_vals[0];
+}
 
 // Workgroups of Kernel (at Threads per group, no dynamic LDS) that the
 // current device holds at once, computed once per kernel; 0 if unknown.

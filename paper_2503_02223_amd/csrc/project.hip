@@ -117,7 +117,8 @@ __device__ __forceinline__ void project_item(const DevCam<T>& c, const Consts<T>
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void project_kernel(Views<T> V, Consts<T> cs, int64_t n, int64_t M,
+__global__ __launch_bounds__(256) void project_kernel(Views<T> V, Consts<T> cs, int64_t n, uint32_t listed,
+                                                      int key_by_item,
                                                       const T* __restrict__ params, const int32_t* __restrict__ ids,
                                                       T* __restrict__ splats, short4* __restrict__ rects,
                                                       uint32_t* __restrict__ counts, uint32_t* __restrict__ dkeys,
@@ -147,22 +148,22 @@ __global__ __launch_bounds__(256) void project_kernel(Views<T> V, Consts<T> cs, 
     // flush histogram counts to the shared copies.
     uint32_t kmin_inv = 0u, kmax = 0u;  // visible depth keys: max of ~key, max of key
     for (int it = 0; it < kProjItems; ++it) {
-        const int64_t i = ((int64_t)blockIdx.x * kProjItems + it) * 256 + tid;
-        if (i < M) {
-            const int v = (int)(i / n);
-            const int64_t g = i - (int64_t)v * n;
-            const bool in_seg = g >= V.cam[v].seg_lo && g < V.cam[v].seg_hi;
+        const uint32_t j = (blockIdx.x * (uint32_t)kProjItems + it) * 256u + tid;
+        if (j < listed) {
+            const int v = listed_view(V, j);
+            const int64_t g = V.cam[v].seg_lo + (int64_t)(j - V.list_off[v]);
+            const int64_t i = (int64_t)v * n + g;
             T p[kParams];
             bool finite = true;
 #pragma unroll
             for (int r = 0; r < kParams; ++r) {
-                p[r] = in_seg ? params[(int64_t)r * n + g] : T(0);
+                p[r] = params[(int64_t)r * n + g];
                 finite = finite && isfinite(p[r]);
             }
             if (!finite) atomicOr(&ctrl->status, (uint32_t)DQO_STATUS_NONFINITE);
             Proj<T> pr;
             pr.visible = false;
-            if (finite && in_seg) project_item(V.cam[v], cs, p, pr);
+            if (finite) project_item(V.cam[v], cs, p, pr);
             uint32_t cnt = 0;
             short4 rc = make_short4(0, 0, -1, -1);
             T w[kSplatWords];
@@ -211,8 +212,8 @@ __global__ __launch_bounds__(256) void project_kernel(Views<T> V, Consts<T> cs, 
             rects[i] = rc;
             counts[i] = cnt;
             const uint32_t key = pr.visible ? __float_as_uint((float)pr.z) : 0xffffffffu;
-            dkeys[i] = key;
-            dvals[i] = (uint32_t)i;
+            dkeys[key_by_item ? i : (int64_t)j] = key;
+            dvals[j] = (uint32_t)i;
             // the depth passes count their later digits themselves (relative to the smallest key)
             atomicAdd(&s_hist[key & 255u], 1u);
             if (pr.visible) {
@@ -221,6 +222,16 @@ __global__ __launch_bounds__(256) void project_kernel(Views<T> V, Consts<T> cs, 
             }
         }
     }
+    // Items outside their view's segment cover no tile.
+    if (listed != (uint32_t)(V.n_views * n))
+        for (int v = 0; v < V.n_views; ++v) {
+            const int64_t lo = V.cam[v].seg_lo, cnt = V.cam[v].seg_hi - lo;
+            for (int64_t k = (int64_t)blockIdx.x * 256 + tid; k < n - cnt; k += (int64_t)gridDim.x * 256) {
+                const int64_t i = (int64_t)v * n + (k < lo ? k : k + cnt);
+                counts[i] = 0u;
+                rects[i] = make_short4(0, 0, -1, -1);
+            }
+        }
 #pragma unroll
     for (int d = 1; d < kWave; d <<= 1) {
         kmin_inv = max(kmin_inv, (uint32_t)__shfl_xor(kmin_inv, d));
@@ -251,8 +262,8 @@ __global__ __launch_bounds__(256) void project_kernel(Views<T> V, Consts<T> cs, 
 // emission then reads its block's offset and waits on nothing (eight
 // keyframes, 9.6M items: 206 -> 211 training steps/s).
 __global__ __launch_bounds__(kScanThreads) void scan_block_sums_kernel(const uint32_t* __restrict__ order,
-                                                                      const uint32_t* __restrict__ counts, uint32_t M,
-                                                                      uint32_t* __restrict__ sums) {
+                                                                      const uint32_t* __restrict__ counts, uint32_t listed,
+                                                                      uint32_t M, uint32_t* __restrict__ sums) {
     __shared__ uint32_t s_tmp[kScanThreads / kWave];
     const int tid = threadIdx.x;
     const uint32_t base = blockIdx.x * (uint32_t)kScanTile;
@@ -260,7 +271,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_block_sums_kernel(const uin
 #pragma unroll
     for (int k = 0; k < kScanIpt; ++k) {
         const uint32_t q = base + tid * kScanIpt + k;
-        if (q < M) v += counts[order ? min(order[q], M - 1) : q];
+        if (q < listed) v += counts[order ? min(order[q], M - 1) : q];
     }
     const uint32_t excl = block_exclusive_scan<kScanThreads>(v, s_tmp);
     if (tid == kScanThreads - 1) sums[blockIdx.x] = excl + v;
@@ -304,8 +315,8 @@ __global__ __launch_bounds__(kScanThreads) void scan_block_base_kernel(uint32_t*
 template <typename T, bool FUSED>
 __global__ __launch_bounds__(kScanThreads) void scan_emit_kernel(
     const uint32_t* __restrict__ order, const uint32_t* __restrict__ counts, const short4* __restrict__ rects,
-    uint32_t* __restrict__ offsets, T* __restrict__ splats, uint32_t* __restrict__ pkeys, uint32_t* __restrict__ pvals, uint32_t M,
-    uint32_t cap, int64_t n, int tiles_x, int tiles_per_view, int pair_passes, int copies, uint64_t* lb, Ctrl* ctrl,
+    uint32_t* __restrict__ offsets, T* __restrict__ splats, uint32_t* __restrict__ pkeys, uint32_t* __restrict__ pvals, uint32_t listed,
+    uint32_t M, uint32_t cap, int64_t n, int tiles_x, int tiles_per_view, int pair_passes, int copies, uint64_t* lb, Ctrl* ctrl,
     const uint32_t* __restrict__ block_base) {
     __shared__ uint32_t s_incl[kScanTile];
     __shared__ uint32_t s_rec[kScanTile];
@@ -331,14 +342,14 @@ __global__ __launch_bounds__(kScanThreads) void scan_emit_kernel(
     __shared__ uint32_t s_gb[FUSED ? kRadixBins : 1];
     const int tid = threadIdx.x;
     // The block's records at its workgroup index (the order in force unless a
-    // ticket is drawn), loaded before anything waits; order is a permutation
-    // of [0, M) (the depth order), or the identity.
+    // ticket is drawn), loaded before anything waits; order lists the items
+    // (in depth order), or is the identity.
     uint32_t c[kScanIpt], rec[kScanIpt], sum = 0;
     auto load_recs = [&](uint32_t b) {
 #pragma unroll
         for (int k = 0; k < kScanIpt; ++k) {
             const uint32_t q = b * (uint32_t)kScanTile + tid * kScanIpt + k;
-            rec[k] = q < M ? (order ? min(order[q], M - 1) : q) : 0xffffffffu;
+            rec[k] = q < listed ? (order ? min(order[q], M - 1) : q) : 0xffffffffu;
         }
     };
     load_recs(blockIdx.x);
@@ -365,7 +376,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_emit_kernel(
     __syncthreads();
     const uint32_t bid = s_bid;
     const uint32_t base = bid * (uint32_t)kScanTile;
-    if (base >= M) return;
+    if (base >= listed) return;
     if (bid != blockIdx.x) load_recs(bid);
     // The block's records with their counts and tile rectangles, gathered
     // with every load in flight at once and kept in LDS for the emission.
@@ -449,7 +460,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_emit_kernel(
                                       : lookback_grouped(ch, ch + (size_t)gridDim.x * kCh, kCh, (int)bid, agg, epoch,
                                                          &ctrl->status);
             s_base = excl;
-            if (base + kScanTile >= M) {
+            if (base + kScanTile >= listed) {
                 const uint32_t total = excl + agg;
                 ctrl->num_pairs = total;
                 if (total > cap) atomicOr(&ctrl->status, (uint32_t)DQO_STATUS_OVERFLOW);
@@ -477,7 +488,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_emit_kernel(
 #pragma unroll
     for (int k = 0; k < kScanIpt; ++k) {
         const uint32_t q = tid * kScanIpt + k;
-        if (base + q < M) {
+        if (base + q < listed) {
             const uint32_t first = gbase + s_incl[q] - c[k];
             offsets[s_rec[q]] = first;
             // also in the splat record, beside the rectangle (unused when the item has no pairs)
@@ -587,12 +598,14 @@ hipError_t launch_project_bin(const Frame<T>& f, const T* params, const int32_t*
     const StatePtrs& s = f.s;
     hipLaunchKernelGGL(prep_kernel, dim3((unsigned)std::max(1, std::max(s.hist_copies_depth, s.hist_copies_pair))),
                        dim3(256), 0, st, s.ctrl, s.hist_copies_depth, s.hist_copies_pair);
-    const int64_t M = s.items;
+    const int64_t M = s.items, N = s.listed;
     const int64_t range_words = 2 * (int64_t)f.views.tiles_per_view * f.views.n_views;
     if (M == 0) return launch_zero_words(s.ranges, range_words, st);
-    hipLaunchKernelGGL(project_kernel<T>, dim3((unsigned)((M + 256 * kProjItems - 1) / (256 * kProjItems))), dim3(256),
+    // (a frame whose segments are all empty still clears its ranges and counts)
+    hipLaunchKernelGGL(project_kernel<T>,
+                       dim3((unsigned)std::max<int64_t>(1, (N + 256 * kProjItems - 1) / (256 * kProjItems))), dim3(256),
                        0, st, f.views, f.consts,
-                       f.n, M, params, ids, (T*)s.splats, s.rects, s.counts, s.depth_keys[0], s.depth_vals[0],
+                       f.n, (uint32_t)N, s.tile_sort ? 1 : 0, params, ids, (T*)s.splats, s.rects, s.counts, s.depth_keys[0], s.depth_vals[0],
                        s.ranges, range_words, s.hist_copies_depth, s.ctrl,
                        s.fused_emit ? &s.ctrl->hist_pair[0][0][0] : nullptr, s.hist_copies_pair);
     // Below 2^18 items the 2048-item blocks run as 1024 threads x 2 items
@@ -601,8 +614,9 @@ hipError_t launch_project_bin(const Frame<T>& f, const T* params, const int32_t*
 #ifndef DQO_DEPTH_SMALL_NT
 #define DQO_DEPTH_SMALL_NT 1024
 #endif
-    const int dnt = M < (int64_t(1) << 18) ? DQO_DEPTH_SMALL_NT : kDepthNt;
-    const int dipt = kDepthNt * depth_ipt(M) / dnt;
+    if (N == 0) return hipGetLastError();
+    const int dnt = N < (int64_t(1) << 18) ? DQO_DEPTH_SMALL_NT : kDepthNt;
+    const int dipt = kDepthNt * depth_ipt(N) / dnt;
     // Buffers of the four passes: 0 -> 1 -> 2 -> 1 -> 0, or 0 -> 1 -> 2 -> 0
     // when three passes suffice (decided on the device from the key range).
     static const int kIn[kMaxDepthPasses] = {0, 1, 2, 1}, kOut[kMaxDepthPasses] = {1, 2, 1, 0};
@@ -610,7 +624,7 @@ hipError_t launch_project_bin(const Frame<T>& f, const T* params, const int32_t*
         const DepthRel rel{p, p == 2 ? s.depth_keys[0] : nullptr, p == 2 ? s.depth_vals[0] : nullptr,
                            p + 1 < kMaxDepthPasses ? &s.ctrl->hist_depth[0][p + 1][0] : nullptr};
         hipError_t e = launch_radix_pass(s.depth_keys[kIn[p]], s.depth_vals[kIn[p]], s.depth_keys[kOut[p]],
-                                         s.depth_vals[kOut[p]], nullptr, (uint32_t)M, p * kRadixBits,
+                                         s.depth_vals[kOut[p]], nullptr, (uint32_t)N, p * kRadixBits,
                                          &s.ctrl->hist_depth[0][p][0], kMaxDepthPasses * kRadixBins, s.hist_copies_depth,
                                          s.lb_depth + (size_t)p * lb_blocks(s.depth_blocks) * kRadixBins,
                                          &s.ctrl->counters[kCounterDepth + p], s.ctrl, st, dnt, dipt, &rel);
@@ -621,14 +635,14 @@ hipError_t launch_project_bin(const Frame<T>& f, const T* params, const int32_t*
     const bool two_level = s.scan_blocks > scan_emit_resident(s.fused_emit);
     if (two_level) {
         hipLaunchKernelGGL(scan_block_sums_kernel, dim3((unsigned)s.scan_blocks), dim3(kScanThreads), 0, st,
-                           item_order(s), s.counts, (uint32_t)M, s.scan_base);
+                           item_order(s), s.counts, (uint32_t)N, (uint32_t)M, s.scan_base);
         hipLaunchKernelGGL(scan_block_base_kernel, dim3(1), dim3(kScanThreads), 0, st, s.scan_base, s.scan_blocks,
                            (uint32_t)s.capacity, s.ctrl);
     }
     auto emit = s.fused_emit ? scan_emit_kernel<T, true> : scan_emit_kernel<T, false>;
     hipLaunchKernelGGL(emit, dim3((unsigned)s.scan_blocks), dim3(kScanThreads), 0, st, item_order(s),
-                       s.counts, s.rects, s.offsets, (T*)s.splats, s.pair_keys[pf], s.pair_vals[pf], (uint32_t)M,
-                       (uint32_t)s.capacity, f.n, f.views.tiles_x, f.views.tiles_per_view, s.pair_passes,
+                       s.counts, s.rects, s.offsets, (T*)s.splats, s.pair_keys[pf], s.pair_vals[pf], (uint32_t)N,
+                       (uint32_t)M, (uint32_t)s.capacity, f.n, f.views.tiles_x, f.views.tiles_per_view, s.pair_passes,
                        s.hist_copies_pair, s.lb_scan, s.ctrl, two_level ? (const uint32_t*)s.scan_base : nullptr);
     return hipGetLastError();
 }
@@ -699,8 +713,8 @@ __global__ __launch_bounds__(kSlotWaves * kWave) void slot_sum_kernel(const uint
                                                                       const uint32_t* __restrict__ counts,
                                                                       const uint32_t* __restrict__ offsets,
                                                                       const T* __restrict__ partials,
-                                                                      const uint8_t* __restrict__ written, uint32_t M,
-                                                                      uint32_t cap, T* __restrict__ sums) {
+                                                                      const uint8_t* __restrict__ written, uint32_t listed,
+                                                                      uint32_t M, uint32_t cap, T* __restrict__ sums) {
     __shared__ T s_acc[kSlotWaves][kWave][kGradWords + 1];
     __shared__ uint16_t s_nz[kSlotWaves][kWave];
     __shared__ uint8_t s_start[kSlotWaves][kWave];
@@ -708,7 +722,7 @@ __global__ __launch_bounds__(kSlotWaves * kWave) void slot_sum_kernel(const uint
     const uint64_t lt = lane ? (~0ull >> (kWave - lane)) : 0ull;
     const uint32_t q = ((uint32_t)blockIdx.x * kSlotWaves + wave) * kWave + lane;
     uint32_t rec = 0, c = 0, off = 0;
-    if (q < M) {
+    if (q < listed) {
         rec = order ? min(order[q], M - 1) : q;  // emission order: depth order, or item order
         c = counts[rec];
         off = offsets[rec];
@@ -771,6 +785,16 @@ __global__ __launch_bounds__(kSlotWaves * kWave) void slot_sum_kernel(const uint
 #pragma unroll
         for (int k = 0; k < kGradWords; ++k) sums[(size_t)rec * kGradWords + k] = s_acc[wave][lane][k];
     }
+}
+
+template <typename T>
+static void launch_slot_sums(const Frame<T>& f, hipStream_t st) {
+    const StatePtrs& s = f.s;
+    constexpr int kItems = kSlotWaves * kWave;
+    if (s.listed == 0) return;
+    hipLaunchKernelGGL(slot_sum_kernel<T>, dim3((unsigned)((s.listed + kItems - 1) / kItems)), dim3(kItems), 0, st,
+                       item_order(s), s.counts, s.offsets, (const T*)s.partials, s.written, (uint32_t)s.listed,
+                       (uint32_t)s.items, (uint32_t)s.capacity, (T*)s.sums);
 }
 
 // Chain rule of one (view, Gaussian) item from its pair-partial totals d
@@ -986,10 +1010,7 @@ __global__ __launch_bounds__(256) void project_backward_kernel(Views<T> V, Const
 template <typename T>
 hipError_t launch_project_backward(const Frame<T>& f, const T* params, T* grads, hipStream_t st) {
     if (f.n == 0) return hipSuccess;
-    const int64_t M = f.s.items;
-    hipLaunchKernelGGL(slot_sum_kernel<T>, dim3((unsigned)((M + kSlotWaves * kWave - 1) / (kSlotWaves * kWave))),
-                       dim3(kSlotWaves * kWave), 0, st, item_order(f.s), f.s.counts, f.s.offsets,
-                       (const T*)f.s.partials, f.s.written, (uint32_t)M, (uint32_t)f.s.capacity, (T*)f.s.sums);
+    launch_slot_sums<T>(f, st);
     hipLaunchKernelGGL((project_backward_kernel<T>), dim3((unsigned)((f.n + 255) / 256)), dim3(256), 0, st,
                        f.views, f.consts, f.n, const_cast<T*>(params), f.s.counts, f.s.offsets, (const T*)f.s.sums,
                        (uint32_t)f.s.capacity, grads, (T*)nullptr, (T*)nullptr, AdamArgs<T>{}, (int64_t*)nullptr,
@@ -1078,10 +1099,7 @@ template <typename T>
 hipError_t launch_pose_backward(const Frame<T>& f, const T* params, double* pose, hipStream_t st) {
     const int V = f.views.n_views;
     if (f.n == 0) return launch_zero_words((uint32_t*)pose, 12 * (int64_t)V, st);
-    const int64_t M = f.s.items;
-    hipLaunchKernelGGL(slot_sum_kernel<T>, dim3((unsigned)((M + kSlotWaves * kWave - 1) / (kSlotWaves * kWave))),
-                       dim3(kSlotWaves * kWave), 0, st, item_order(f.s), f.s.counts, f.s.offsets,
-                       (const T*)f.s.partials, f.s.written, (uint32_t)M, (uint32_t)f.s.capacity, (T*)f.s.sums);
+    launch_slot_sums<T>(f, st);
     const int blocks = (int)((f.n + 255) / 256);
     hipLaunchKernelGGL(pose_grad_kernel<T>, dim3((unsigned)blocks, (unsigned)V), dim3(256), 0, st, f.views, f.consts,
                        f.n, params, f.s.counts, f.s.offsets, (const T*)f.s.sums, (uint32_t)f.s.capacity,
@@ -1095,10 +1113,7 @@ template <typename T>
 hipError_t launch_project_backward_adam(const Frame<T>& f, T* params, T* grads, T* m, T* v, const dqo_adam& hp,
                                         int64_t* d_step, hipStream_t st) {
     if (f.n == 0) return launch_adam<T>(params, grads, m, v, 0, hp, 1, d_step, st, kParams);  // advances the step
-    const int64_t M = f.s.items;
-    hipLaunchKernelGGL(slot_sum_kernel<T>, dim3((unsigned)((M + kSlotWaves * kWave - 1) / (kSlotWaves * kWave))),
-                       dim3(kSlotWaves * kWave), 0, st, item_order(f.s), f.s.counts, f.s.offsets,
-                       (const T*)f.s.partials, f.s.written, (uint32_t)M, (uint32_t)f.s.capacity, (T*)f.s.sums);
+    launch_slot_sums<T>(f, st);
     hipLaunchKernelGGL((project_backward_kernel<T>), dim3((unsigned)((f.n + 255) / 256)), dim3(256), 0, st,
                        f.views, f.consts, f.n, params, f.s.counts, f.s.offsets, (const T*)f.s.sums,
                        (uint32_t)f.s.capacity, grads, m, v, make_adam_args<T>(hp, 1), d_step,
