@@ -8,10 +8,17 @@
 //
 // One wavefront per object.  The object's boxes (and their cameras) are
 // staged in LDS once; lane i evaluates boxes i, i + 64, ... and back-
-// propagates to (mu, R, w); a butterfly reduction leaves identical totals in
-// every lane, so every lane performs the same Adam step on its own copy of
-// theta and the whole optimisation runs in one launch with no barrier.
+// propagates to (mu, R, w); lane l < 10 holds component l of theta and of its
+// Adam moments, so the divisions, roots and exponentials that every component
+// takes are issued once for all ten, and the totals and the components reach
+// the other lanes through scalar registers.  The whole optimisation runs in
+// one launch with no barrier.  An iteration is one dependent FP64 chain of a
+// wavefront alone on its SIMD, so its time is its instruction count: 100
+// iterations of 40 objects in 8 views took 758 us with every lane holding all
+// of theta, two pow() per iteration and butterflies over 64 lanes through LDS;
+// now 328 us.
 #include "dqo_device.hpp"
+#include "wave_f64.hpp"
 
 namespace dqo {
 
@@ -29,12 +36,6 @@ struct BoxSet {
     double wh[kRefineMaxBoxes][2];  // image size for clipping; negative: no clipping
     int32_t idx[kRefineMaxBoxes];   // index of the box in the caller's arrays
 };
-
-__device__ __forceinline__ double rf_wave_sum(double v) {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d);  // a + b == b + a: every lane ends equal
-    return v;
-}
 
 __device__ void rot_from_unit_quat(const double q[4], double R[9]) {
     const double w = q[0], x = q[1], y = q[2], z = q[3];
@@ -85,21 +86,59 @@ struct ThetaView {
     double mu[3], qh[4], nq, R[9], w[3];
 };
 
-__device__ void theta_view(const double th[10], ThetaView& tv) {
-    for (int i = 0; i < 3; ++i) tv.mu[i] = th[i];
-    tv.nq = sqrt(th[3] * th[3] + th[4] * th[4] + th[5] * th[5] + th[6] * th[6]);
-    for (int i = 0; i < 4; ++i) tv.qh[i] = th[3 + i] / tv.nq;
+// own: component l of theta in lane l < 10.
+__device__ __forceinline__ void theta_view(double own, ThetaView& tv) {
+    double q[4];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) tv.mu[i] = lane_value(own, i);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) q[i] = lane_value(own, 3 + i);
+    tv.nq = sqrt(q[0] * q[0] + q[1] * q[1] + q[2] * q[2] + q[3] * q[3]);
+    const double unit = own / tv.nq, square = exp(2.0 * own);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) tv.qh[i] = lane_value(unit, 3 + i);
     rot_from_unit_quat(tv.qh, tv.R);
-    for (int i = 0; i < 3; ++i) tv.w[i] = exp(2.0 * th[7 + i]);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) tv.w[i] = lane_value(square, 7 + i);
 }
 
-// 1 - IoU of one box; with `acc` set, its gradient with respect to mu, R and
+// Totals over the wavefront of 16 values whose terms lie in lanes 0 .. nb - 1
+// (zero elsewhere), in every lane: the butterfly over distances 32 .. 1, with
+// the distances that only add zeros left out, and the last three transposing
+// (a lane keeps the half of the values that its lane bit names), so 14
+// additions stand for 48.
+__device__ __forceinline__ void wave_totals(double (&x)[16], int nb, int lane) {
+    if (nb > 32)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) x[i] = add_xor32(x[i]);
+    if (nb > 16)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) x[i] = add_xor16(x[i]);
+    if (nb > 8)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) x[i] += lane_xor<8>(x[i]);
+    const bool u4 = (lane & 4) != 0, u2 = (lane & 2) != 0, u1 = (lane & 1) != 0;
+    double a[8], b[4], c[2];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) a[i] = (u4 ? x[i + 8] : x[i]) + lane_xor<4>(u4 ? x[i] : x[i + 8]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) b[i] = (u2 ? a[i + 4] : a[i]) + lane_xor<2>(u2 ? a[i] : a[i + 4]);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) c[i] = (u1 ? b[i + 2] : b[i]) + lane_xor<1>(u1 ? b[i] : b[i + 2]);
+#pragma unroll
+    for (int k = 0; k < 16; ++k) x[k] = lane_value(c[k & 1], (k >> 1) & 7);
+}
+
+// 1 - IoU of one box; with GRAD, its gradient with respect to mu, R and
 // w is added to acc[0..2], acc[3..11] (row-major R), acc[12..14].
-__device__ double box_term(const ThetaView& tv, const double* __restrict__ P, const double* __restrict__ o,
-                           const double* __restrict__ wh, double* acc, double* iou_out) {
+template <bool GRAD>
+__device__ __forceinline__ double box_term(const ThetaView& tv, const double* __restrict__ P, const double* __restrict__ o,
+                           const double* __restrict__ wh, double (&acc)[16], double& iou_out) {
     // M = P3 R, g = P3 mu + p4
     double M[3][3], g[3];
+#pragma unroll
     for (int r = 0; r < 3; ++r) {
+#pragma unroll
         for (int m = 0; m < 3; ++m) M[r][m] = P[4 * r] * tv.R[m] + P[4 * r + 1] * tv.R[3 + m] + P[4 * r + 2] * tv.R[6 + m];
         g[r] = P[4 * r] * tv.mu[0] + P[4 * r + 1] * tv.mu[1] + P[4 * r + 2] * tv.mu[2] + P[4 * r + 3];
     }
@@ -107,7 +146,7 @@ __device__ double box_term(const ThetaView& tv, const double* __restrict__ P, co
         return tv.w[0] * M[i][0] * M[j][0] + tv.w[1] * M[i][1] * M[j][1] + tv.w[2] * M[i][2] * M[j][2] - g[i] * g[j];
     };
     const double C00 = Cij(0, 0), C02 = Cij(0, 2), C11 = Cij(1, 1), C12 = Cij(1, 2), s = Cij(2, 2);
-    *iou_out = 0.0;
+    iou_out = 0.0;
     if (!(s < 0.0)) return 1.0;  // not an ellipse in front of the camera
     const double c00 = C00 / s, c02 = C02 / s, c11 = C11 / s, c12 = C12 / s;
     const double dx2 = c02 * c02 - c00, dy2 = c12 * c12 - c11;
@@ -117,6 +156,7 @@ __device__ double box_term(const ThetaView& tv, const double* __restrict__ P, co
     bool pass[4] = {true, true, true, true};
     if (wh[0] >= 0.0) {
         const double lim[4] = {wh[0], wh[1], wh[0], wh[1]};
+#pragma unroll
         for (int i = 0; i < 4; ++i) {
             if (b[i] < 0.0) { b[i] = 0.0; pass[i] = false; }
             else if (b[i] > lim[i]) { b[i] = lim[i]; pass[i] = false; }
@@ -130,8 +170,8 @@ __device__ double box_term(const ThetaView& tv, const double* __restrict__ P, co
     const double bw = b[2] - b[0], bh = b[3] - b[1];
     const double U = bw * bh + (o[2] - o[0]) * (o[3] - o[1]) - I;
     const double iou = I / U;
-    *iou_out = iou;
-    if (!acc) return 1.0 - iou;
+    iou_out = iou;
+    if constexpr (!GRAD) return 1.0 - iou;
     // d(1 - IoU): dI and dA (predicted area) coefficients
     const double gI = -(U + I) / (U * U), gA = I / (U * U);
     double gb[4];
@@ -139,6 +179,7 @@ __device__ double box_term(const ThetaView& tv, const double* __restrict__ P, co
     gb[2] = gI * (px1 ? ih : 0.0) + gA * bh;
     gb[1] = gI * (py0 ? -iw : 0.0) + gA * (-bw);
     gb[3] = gI * (py1 ? iw : 0.0) + gA * bw;
+#pragma unroll
     for (int i = 0; i < 4; ++i)
         if (!pass[i]) gb[i] = 0.0;
     // x0 = c02 - dx, x1 = c02 + dx, dx = sqrt(c02^2 - c00) (and y likewise)
@@ -152,38 +193,52 @@ __device__ double box_term(const ThetaView& tv, const double* __restrict__ P, co
     const double S[3][3] = {{2 * gC00, 0.0, gC02}, {0.0, 2 * gC11, gC12}, {gC02, gC12, 2 * gs}};
     // dL/dw_m = sum_ij G_hat_ij M_im M_jm;  dL/dM_m = w_m S M_m;  dL/dg = -S g
     double gM[3][3];
+#pragma unroll
     for (int m = 0; m < 3; ++m) {
         const double m0 = M[0][m], m1 = M[1][m], m2 = M[2][m];
         acc[12 + m] += gC00 * m0 * m0 + gC02 * m0 * m2 + gC11 * m1 * m1 + gC12 * m1 * m2 + gs * m2 * m2;
+#pragma unroll
         for (int r = 0; r < 3; ++r) gM[r][m] = tv.w[m] * (S[r][0] * m0 + S[r][1] * m1 + S[r][2] * m2);
     }
     double gg[3];
+#pragma unroll
     for (int r = 0; r < 3; ++r) gg[r] = -(S[r][0] * g[0] + S[r][1] * g[1] + S[r][2] * g[2]);
     // M = P3 R: dL/dR = P3^T dL/dM;  g = P3 mu + p4: dL/dmu = P3^T dL/dg
+#pragma unroll
     for (int i = 0; i < 3; ++i) {
         acc[i] += P[i] * gg[0] + P[4 + i] * gg[1] + P[8 + i] * gg[2];
+#pragma unroll
         for (int m = 0; m < 3; ++m) acc[3 + 3 * i + m] += P[i] * gM[0][m] + P[4 + i] * gM[1][m] + P[8 + i] * gM[2][m];
     }
     return 1.0 - iou;
 }
 
-// Loss and gradient of the object's theta over its staged boxes (every lane
-// returns the same totals).
-__device__ double object_loss_grad(const double th[10], const BoxSet& bs, int nb, double grad[10], double* box_iou) {
-    ThetaView tv;
-    theta_view(th, tv);
-    double acc[15];
-    for (int i = 0; i < 15; ++i) acc[i] = 0.0;
-    double J = 0.0;
-    for (int i = (int)threadIdx.x; i < nb; i += kWave) {
+// One of the values by position p: a chain of selects on registers (by value,
+// so that no arm is a load and the arrays stay in registers).
+__device__ __forceinline__ double pick(int p, double a, double b, double c) { return p == 0 ? a : p == 1 ? b : c; }
+__device__ __forceinline__ double pick(int p, double a, double b, double c, double d) {
+    return p == 0 ? a : p == 1 ? b : p == 2 ? c : d;
+}
+
+// Loss of the object's theta (lane l < 10 holds component l) over its staged
+// boxes, the same in every lane; with GRAD, component l of the gradient in
+// lane l < 10.
+template <bool GRAD>
+__device__ __forceinline__ double object_loss_grad(double own, const BoxSet& bs, int nb, double* grad,
+                                                   double* box_iou, ThetaView& tv) {
+    const int lane = (int)threadIdx.x;
+    theta_view(own, tv);
+    double acc[16];  // dL/dmu (3), dL/dR (9), dL/dw (3), J
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = 0.0;
+    for (int i = lane; i < nb; i += kWave) {
         double iou;
-        J += box_term(tv, bs.P[i], bs.obs[i], bs.wh[i], grad ? acc : nullptr, &iou);
+        const double term = box_term<GRAD>(tv, bs.P[i], bs.obs[i], bs.wh[i], acc, iou);
+        acc[15] += term;
         if (box_iou) box_iou[bs.idx[i]] = iou;
     }
-    J = rf_wave_sum(J);
-    if (!grad) return J;
-    for (int i = 0; i < 15; ++i) acc[i] = rf_wave_sum(acc[i]);
-    for (int i = 0; i < 3; ++i) grad[i] = acc[i];
+    if constexpr (!GRAD) return wave_sum_all(acc[15]);
+    wave_totals(acc, nb, lane);
     // R(q_hat): derivative of the unit-quaternion rotation formula
     const double* gR = acc + 3;
     const double w = tv.qh[0], x = tv.qh[1], y = tv.qh[2], z = tv.qh[3];
@@ -194,10 +249,13 @@ __device__ double object_loss_grad(const double th[10], const BoxSet& bs, int nb
     gq[3] = 2 * (-2 * z * gR[0] - w * gR[1] + x * gR[2] + w * gR[3] - 2 * z * gR[4] + y * gR[5] + x * gR[6] + y * gR[7]);
     // q_hat = q / |q|
     const double dot = gq[0] * tv.qh[0] + gq[1] * tv.qh[1] + gq[2] * tv.qh[2] + gq[3] * tv.qh[3];
-    for (int i = 0; i < 4; ++i) grad[3 + i] = (gq[i] - tv.qh[i] * dot) / tv.nq;
+    const double g_mu = pick(lane, acc[0], acc[1], acc[2]);
+    const double g_q = (pick(lane - 3, gq[0], gq[1], gq[2], gq[3]) -
+                        pick(lane - 3, tv.qh[0], tv.qh[1], tv.qh[2], tv.qh[3]) * dot) / tv.nq;
     // w_m = exp(2 l_m)
-    for (int m = 0; m < 3; ++m) grad[7 + m] = 2.0 * tv.w[m] * acc[12 + m];
-    return J;
+    const double g_w = 2.0 * pick(lane - 7, tv.w[0], tv.w[1], tv.w[2]) * pick(lane - 7, acc[12], acc[13], acc[14]);
+    *grad = lane < 3 ? g_mu : lane < 7 ? g_q : g_w;
+    return acc[15];
 }
 
 // Stage the boxes of object k in LDS, in ascending box order.  Returns their
@@ -248,16 +306,11 @@ __global__ __launch_bounds__(kWave) void quadric_iou_grad_kernel(int n_views, in
         if (lane < 10) grad[10 * k + lane] = __builtin_nan("");
         return;
     }
-    double th[10], g[10];
-    for (int i = 0; i < 10; ++i) th[i] = theta[10 * k + i];
-    const double J = object_loss_grad(th, bs, nb, g, box_iou);
+    ThetaView tv;
+    double g;
+    const double J = object_loss_grad<true>(theta[10 * k + min(lane, 9)], bs, nb, &g, box_iou, tv);
     if (lane == 0) loss[k] = J;
-    if (lane < 10) {
-        double gi = g[0];
-        for (int i = 1; i < 10; ++i)
-            if (lane == i) gi = g[i];
-        grad[10 * k + lane] = gi;
-    }
+    if (lane < 10) grad[10 * k + lane] = g;
 }
 
 __global__ __launch_bounds__(kWave) void refine_quadric_kernel(int n_views, int64_t n_boxes,
@@ -283,38 +336,41 @@ __global__ __launch_bounds__(kWave) void refine_quadric_kernel(int n_views, int6
         if (lane < 2) loss[2 * k + lane] = nan;
         return;
     }
-    double th[10], m[10], v[10], g[10];
+    // lane l < 10: component l (the other lanes repeat the last one)
+    double th;
     {
         double R0[9], q0[4];
         for (int i = 0; i < 9; ++i) R0[i] = R_io[9 * k + i];
         quat_from_rot(R0, q0);
-        for (int i = 0; i < 3; ++i) th[i] = mu_io[3 * k + i];
-        for (int i = 0; i < 4; ++i) th[3 + i] = q0[i];
-        for (int i = 0; i < 3; ++i) th[7 + i] = log(ax_io[3 * k + i]);
+        const int a = min(max(lane - 7, 0), 2);
+        const double lax = log(ax_io[3 * k + a]);
+        th = lane < 3 ? mu_io[3 * k + min(lane, 2)] : lane < 7 ? pick(lane - 3, q0[0], q0[1], q0[2], q0[3]) : lax;
     }
-    for (int i = 0; i < 10; ++i) m[i] = v[i] = 0.0;
-    const double lr[10] = {hp.lr_mu, hp.lr_mu, hp.lr_mu, hp.lr_rot, hp.lr_rot,
-                           hp.lr_rot, hp.lr_rot, hp.lr_axes, hp.lr_axes, hp.lr_axes};
-    double J0 = 0.0;
-    for (int t = 1; t <= hp.iterations; ++t) {
-        const double J = object_loss_grad(th, bs, nb, g, nullptr);
-        if (t == 1) J0 = J;
-        const double bc1 = 1.0 - pow(hp.beta1, (double)t), bc2 = 1.0 - pow(hp.beta2, (double)t);
-        for (int i = 0; i < 10; ++i) {
-            m[i] = hp.beta1 * m[i] + (1.0 - hp.beta1) * g[i];
-            v[i] = hp.beta2 * v[i] + (1.0 - hp.beta2) * g[i] * g[i];
-            th[i] = th[i] - lr[i] * (m[i] / bc1) / (sqrt(v[i] / bc2) + hp.eps);
-        }
-    }
-    const double Jf = object_loss_grad(th, bs, nb, nullptr, box_iou);
-    if (hp.iterations == 0) J0 = Jf;
+    const double lr = lane < 3 ? hp.lr_mu : lane < 7 ? hp.lr_rot : hp.lr_axes;
+    double m = 0.0, v = 0.0, J0 = 0.0;
+    double p1 = 0.0, p2 = 0.0;  // bias corrections of 64 consecutive iterations, one per lane
     ThetaView tv;
-    theta_view(th, tv);
+    for (int t = 1; t <= hp.iterations; ++t) {
+        const int tl = (t - 1) & (kWave - 1);
+        if (tl == 0) {
+            p1 = 1.0 - pow(hp.beta1, (double)(t + lane));
+            p2 = 1.0 - pow(hp.beta2, (double)(t + lane));
+        }
+        double g;
+        const double J = object_loss_grad<true>(th, bs, nb, &g, nullptr, tv);
+        if (t == 1) J0 = J;
+        const double bc1 = lane_value(p1, tl), bc2 = lane_value(p2, tl);
+        m = hp.beta1 * m + (1.0 - hp.beta1) * g;
+        v = hp.beta2 * v + (1.0 - hp.beta2) * g * g;
+        th = th - lr * (m / bc1) / (sqrt(v / bc2) + hp.eps);
+    }
+    const double Jf = object_loss_grad<false>(th, bs, nb, nullptr, box_iou, tv);
+    if (hp.iterations == 0) J0 = Jf;
     if (lane == 0) {
         loss[2 * k] = J0;
         loss[2 * k + 1] = Jf;
         for (int i = 0; i < 3; ++i) {
-            mu_io[3 * k + i] = th[i];
+            mu_io[3 * k + i] = tv.mu[i];
             ax_io[3 * k + i] = sqrt(tv.w[i]);
         }
         for (int i = 0; i < 9; ++i) R_io[9 * k + i] = tv.R[i];
@@ -324,9 +380,9 @@ __global__ __launch_bounds__(kWave) void refine_quadric_kernel(int n_views, int6
             for (int i = 0; i < 3; ++i) {
                 for (int j = 0; j < 3; ++j)
                     Q[4 * i + j] = tv.w[0] * tv.R[3 * i] * tv.R[3 * j] + tv.w[1] * tv.R[3 * i + 1] * tv.R[3 * j + 1] +
-                                   tv.w[2] * tv.R[3 * i + 2] * tv.R[3 * j + 2] - th[i] * th[j];
-                Q[4 * i + 3] = -th[i];
-                Q[12 + i] = -th[i];
+                                   tv.w[2] * tv.R[3 * i + 2] * tv.R[3 * j + 2] - tv.mu[i] * tv.mu[j];
+                Q[4 * i + 3] = -tv.mu[i];
+                Q[12 + i] = -tv.mu[i];
             }
             Q[15] = -1.0;
         }
