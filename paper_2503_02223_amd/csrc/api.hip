@@ -35,9 +35,8 @@ struct Geo {
     int64_t lb_words;
     // scratch sub-offsets (relative to DQO_BUF_SCRATCH)
     int64_t off_dk1, off_dv1, off_dk2, off_dv2, off_pk1, off_pv1, off_sched, off_sums, off_pose, off_written, off_sbase, off_seg,
-        off_sgbase, off_tlast, off_ckpt, off_ssum, off_lbd, off_lbs, off_lbp;
-    int64_t seg_cap, ckpt_cap;
-    int seg_len;
+        off_sgbase, off_tlast, off_ckpt, off_suf, off_suflist, off_lbd, off_lbs, off_lbp;
+    int64_t seg_cap, ckpt_cap, suf_cap;
     bool tile_sort;     // per-tile depth order (dqo_depth_order TILE)
     int tile_sort_lds;  // pairs of a tile sorted in LDS
 };
@@ -140,17 +139,18 @@ Geo geometry(const dqo_ctx* ctx, const dqo_frame_desc* d, const dqo_camera* cams
     g.off_pose = so; so = align256(so + (int64_t)d->n_views * ((d->n + 255) / 256) * 6 * 8);
     g.off_written = so; so = align256(so + cap);
     g.off_sbase = so; so = align256(so + (int64_t)scan_blocks_max * 4);
-    // segment boundaries (frames the backward segments): sum over tiles of
-    // ceil(range / L) - 1 <= cap / L
+    // segment boundaries (64-pixel tiles, frames the backward segments):
+    // sum over tiles of ceil(range / L) - 1 <= cap / L
+    g.ckpt_cap = (tw * th == kWave && tiles_total <= kSegTilesMax) ? cap / kSegLen + 1 : 0;
     const int parts = tw * th / kWave;
-    g.seg_len = tiles_total <= kSegFineTiles ? kSegLen : kSegLen * parts;
-    g.ckpt_cap = tiles_total <= kSegTilesMax ? cap / g.seg_len + 1 : 0;
-    g.seg_cap = tiles_total + g.ckpt_cap;
+    g.suf_cap = tiles_total * parts <= kSegTilesMax && (parts > 1 || d->K > 0) ? cap / kSegLen + 1 : 0;
+    g.seg_cap = tiles_total + std::max(g.ckpt_cap, g.suf_cap);
     g.off_seg = so; so = align256(so + g.seg_cap * 16);
     g.off_sgbase = so; so = align256(so + tiles_total * 4);
     g.off_tlast = so; so = align256(so + tiles_total * parts * 4);
-    g.off_ckpt = so; so = align256(so + g.ckpt_cap * parts * 6 * kWave * ts);
-    g.off_ssum = so; so = align256(so + (d->K > 0 ? g.ckpt_cap * parts * kWave * ts : 0));
+    g.off_ckpt = so; so = align256(so + g.ckpt_cap * 6 * kWave * ts);
+    g.off_suf = so; so = align256(so + g.suf_cap * 2 * tw * th * ts);
+    g.off_suflist = so; so = align256(so + (g.suf_cap ? g.seg_cap * 8 : 0));
     // look-back words: every block's, then every group's (grouped look-back)
     g.off_lbd = so; so = align256(so + (int64_t)kMaxDepthPasses * lb_blocks(depth_blocks_max) * kRadixBins * 8);
     g.off_lbs = so; so = align256(so + (int64_t)lb_blocks(scan_blocks_max) * (kRadixBins + 1) * 8);
@@ -196,8 +196,9 @@ StatePtrs state_ptrs(const Geo& g, void* state) {
     s.seg_base = (uint32_t*)(sc + g.off_sgbase);
     s.tile_last = (int32_t*)(sc + g.off_tlast);
     s.ckpt = sc + g.off_ckpt;
-    s.seg_sums = sc + g.off_ssum;
-    s.seg_len = g.seg_len;
+    s.suffix = sc + g.off_suf;
+    s.suf_list = (uint2*)(sc + g.off_suflist);
+    s.suf_cap = g.suf_cap;
     s.seg_cap = g.seg_cap;
     s.ckpt_cap = g.ckpt_cap;
     s.ctrl = (Ctrl*)(b + g.L.offset[DQO_BUF_CONTROL]);

@@ -59,7 +59,7 @@ inline int depth_ipt(int64_t items) {
 // 8 wavefronts emits the pairs of its own 64 records (with the first pair
 // pass fused, two blocks share a CU: 35.8 -> 34.4 us at the 200k view against
 // 1024; 256 per block: 46.5 us).
-constexpr int kSegLen = 64;        // pairs per backward segment and 64 pixels of its tile
+constexpr int kSegLen = 64;        // pairs per backward segment of a 64-pixel tile
 constexpr int kSegMax = 255;       // segments per tile (the last one takes the rest of the range)
 constexpr uint32_t kNoBoundary = 0xFFFFFFFFu;  // segment-list entry of a tile's last segment: no restart
 // Pair values are item indices; the render forward sets this bit on the pairs
@@ -177,20 +177,14 @@ struct Consts {
 // only add work (measured: 1M Gaussians at 1200x680, 12750 tiles, backward
 // 11% slower segmented).
 constexpr int kSegTilesMax = 8192;
-// A tile's pairs are segmented every L pairs: kSegLen where the tiles are few
-// (then the segments are what fills the machine), else kSegLen times the
-// tile's 64-pixel parts, so that the boundary states take 24 B per pair of
-// capacity at any tile shape.  The boundary state at pair position b (a multiple of L past its tile's first
-// position rs) is record rs / L + (b - rs) / L: the records of different
-// tiles never meet (a tile of n pairs has fewer than n / L boundaries and the
-// next starts n positions later), and they stay below capacity / L + 1.  A
-// record holds one state per part.
-constexpr int kSegFineTiles = 2048;
-__host__ __device__ constexpr uint32_t boundary_record(uint32_t rs, uint32_t k, uint32_t seg_len) {
-    return rs / seg_len + k;
-}
-__device__ __forceinline__ uint32_t tile_segments(uint32_t range, uint32_t seg_len) {
-    return min((range + seg_len - 1u) / seg_len, (uint32_t)kSegMax);
+// The boundary state at pair position b (a multiple of kSegLen past its
+// tile's first position rs) is record rs / kSegLen + (b - rs) / kSegLen: the
+// records of different tiles never meet (a tile of n pairs has fewer than
+// n / kSegLen boundaries and the next starts n positions later), and they
+// stay below capacity / kSegLen + 1.
+__host__ __device__ constexpr uint32_t boundary_record(uint32_t rs, uint32_t k) { return rs / kSegLen + k; }
+__device__ __forceinline__ uint32_t tile_segments(uint32_t range) {
+    return min((range + kSegLen - 1) / (uint32_t)kSegLen, (uint32_t)kSegMax);
 }
 
 // Look-back words: [flag:2 | epoch:30 | value:32].
@@ -382,16 +376,21 @@ struct StatePtrs {
     uint32_t* pair_vals[2];
     uint32_t* ranges;
     uint32_t* schedule;   // [V*tiles] launch order of the render workgroups
-    // Segmented backward: a tile's pair range is walked in segments of seg_len
-    // pairs, one wavefront each, restarted from per-pixel states the forward
-    // stores at the segment boundaries.
+    // Segmented backward of 64-pixel tiles: a tile's pair range is walked in
+    // segments of kSegLen pairs, one wavefront each, restarted from
+    // per-pixel states the forward stores at the segment boundaries.
     uint4* seg_list;      // [seg_cap] (tile, first position, walk end, boundary record) in launch order (after the forward)
     uint32_t* seg_base;   // [V*tiles] first entry of each tile's segments in the backward's list
-    int32_t* tile_last;   // [V*tiles][parts] last blended position in each 64-pixel part of a tile (forward)
-    void* ckpt;           // [ckpt_cap][parts][6][64] T, colour (3), depth, target probability before each boundary
-    void* seg_sums;       // [ckpt_cap][parts][64] a segment's sum of w dL/dw (instance-channel gradients only)
+    int32_t* tile_last;   // [V*tiles][parts] last blended position in each 64-pixel part of a tile
+    void* ckpt;           // [ckpt_cap][6][64] T, colour (3), depth, target probability before each boundary
     int64_t seg_cap, ckpt_cap;
-    int seg_len;          // pairs per segment (a power of two)
+    // Tiles of several 64-pixel parts, and instance-channel gradients: a pass
+    // runs the backward's transmittance and suffix recurrence alone and stores
+    // them at every kSegLen-th pair, and the gradients of the pairs between
+    // are then taken side by side.
+    uint2* suf_list;      // [seg_cap] (tile, segment) in launch order
+    void* suffix;         // [suf_cap][2][pixels of a tile] T and suffix sum behind each boundary
+    int64_t suf_cap;
     void* partials;
     void* sums;           // [V*n][kGradWords] per-item totals of the pair partials
     double* pose_partials;  // [V][ceil(n/256)][6] per-block camera-pose gradient sums
@@ -489,11 +488,15 @@ inline int resident_blocks() {
     return n;
 }
 hipError_t launch_clear_written(const StatePtrs& s, hipStream_t st);
-// Whether the backward of a frame with these tiles runs segmented (the forward then stores boundary states and the sort their
+// Whether the 64-pixel-tile backward of a frame with these tiles runs
+// segmented (the forward then stores boundary states and the sort their
 // offsets).
 inline bool segmented_backward(const StatePtrs& s, int tiles_total) {
     return s.ckpt_cap > 0 && tiles_total > 0 && tiles_total <= kSegTilesMax;
 }
+// Whether the backward through the suffix pass is taken: where the tiles'
+// wavefronts are few for the machine.
+inline bool suffix_backward(const StatePtrs& s) { return s.suf_cap > 0; }
 hipError_t launch_associate(int n_obj, const double* mu, const double* R, const double* ax, int64_t n_det,
                             const double* boxes, const int32_t* det_frame, int n_frames, const double* P,
                             const int32_t* img_wh, double iou_min, double* iou, int32_t* match, double* occ,

@@ -1,13 +1,13 @@
 // Tile rasterization: forward alpha blending and its adjoint.
 //
-// The unit of work is a wavefront on 8 x 8 pixels, one lane per pixel.  A tile
-// (8x8, 16x8, 16x16, 32x8 or 8x32: the granularity of the binning) has one to
-// four such parts.  In the forward each part is a workgroup of its own that
-// streams the tile's sorted pair range through LDS in batches of 64 records,
-// keeps those that can contribute in its 8 x 8 pixels and walks them from LDS
-// (broadcast reads); it never waits for the other parts.  Blending is a
-// per-pixel recurrence, not a dense contraction, so this path is VALU and
-// transcendental bound and uses no matrix cores.
+// The unit of work is a wavefront on 64 pixels, one lane per pixel.  In the
+// forward a tile (8x8, 16x8, 16x16, 32x8 or 8x32: the granularity of the
+// binning) is one to four workgroups of 8 x 8 pixels, each of which streams the
+// tile's sorted pair range through LDS in batches of 64 records, keeps those
+// that can contribute in its pixels and walks them from LDS (broadcast reads);
+// it never waits for the others.  Blending is a per-pixel recurrence, not a
+// dense contraction, so this path is VALU and transcendental bound and uses no
+// matrix cores.
 //
 // The inner loops are written without divergent branches: every lane computes
 // the contribution test, non-contributing lanes carry a zero weight, and whole
@@ -17,15 +17,14 @@
 // The forward keeps only T_final and the position of the last blended
 // Gaussian per pixel.  The backward walks each pixel from that position back to
 // the front of its tile's range, recomputing alpha exactly as the forward did
-// and the transmittance by division (T_i = T_{i+1} / (1 - alpha_i)).  One
-// wavefront takes all parts of a tile (a lane holds a pixel of each), so a
-// Gaussian's gradients are summed over the parts in the lane first and then
-// once over the wavefront: six Gaussians x ten values are transposed-and-summed
-// across the 64 lanes (each lane ends up owning one value) and written once
-// per (tile, Gaussian) pair to its own slot, which is marked written (pairs
-// left unwritten count as zero); the per-Gaussian totals are formed later in a
-// fixed order, so no atomics and no barriers are needed and the result is
-// deterministic.
+// and the transmittance by division (T_i = T_{i+1} / (1 - alpha_i)), and
+// reduces the per-pixel gradients of each Gaussian over the tile: six
+// Gaussians x ten values are transposed-and-summed across the 64 lanes of a
+// wave (each lane ends up owning one value), then, in tiles of more than one
+// wave, summed over the waves in LDS, and written once per (tile, Gaussian)
+// pair to its own slot, which is marked written (pairs left unwritten count as
+// zero); the per-Gaussian totals are formed later in a fixed order, so no
+// atomics are needed and the result is deterministic.
 #include "dqo_device.hpp"
 
 namespace dqo {
@@ -205,8 +204,8 @@ __device__ __forceinline__ int rank_below(uint64_t bal) {
 template <typename T>
 constexpr int fwd_group() { return (sizeof(T) == 8 && DQO_FWD_GROUP > 4) ? 4 : DQO_FWD_GROUP; }
 
-// The 64-pixel parts of a tile: part q covers columns 8 (q mod kAcross) .. + 7
-// and rows 8 (q / kAcross) .. + 7 of the tile.
+// The forward's 8 x 8 pixel parts of a tile: part q covers columns
+// 8 (q mod kAcross) .. + 7 and rows 8 (q / kAcross) .. + 7 of the tile.
 template <int TW, int TH>
 struct Parts {
     static constexpr int kCount = TW * TH / kWave, kAcross = TW / 8;
@@ -216,8 +215,8 @@ struct Parts {
 };
 
 // PROBS: with the instance channels (an LDS column per lane); NB: with the
-// per-pixel blend count.  Workgroup b runs on XCD b mod 8: the parts of a tile, which gather the same
-// records, are consecutive workgroups of one XCD.
+// per-pixel blend count.  Workgroup b runs on XCD b mod 8: the parts of a
+// tile, which gather the same records, are consecutive workgroups of one XCD.
 // One workgroup per tile with its waves in step (a barrier per batch, every
 // wave walking every record that touches the tile) took 202 us on 30k
 // Gaussians at 333x251 in 16x16 tiles with instance channels, 593 us on eight
@@ -230,10 +229,10 @@ __global__ __launch_bounds__(kWave) void render_forward_kernel(
     const int32_t* __restrict__ target, T* __restrict__ ptarget, int32_t* __restrict__ nblend, uint32_t cap,
     uint32_t M, T* __restrict__ ckpt, uint32_t ckpt_cap,
     int32_t* __restrict__ tile_last, const uint32_t* __restrict__ seg_base, uint4* __restrict__ seg_list,
-    uint32_t seg_cap, uint32_t seg_len, Ctrl* __restrict__ ctrl) {
+    uint32_t seg_cap, Ctrl* __restrict__ ctrl) {
     using P = Parts<TW, TH>;
     constexpr int BLOCK = kWave;
-    if constexpr (P::kCount == 1) seg_len = kSegLen;
+    constexpr bool kSeg = P::kCount == 1;  // 64-pixel tiles can store the segmented backward's states
     __shared__ __align__(16) T s_sp[BLOCK * kWalkWords];
     extern __shared__ unsigned char s_dyn[];
     T* s_P = reinterpret_cast<T*>(s_dyn);  // [K][BLOCK] when PROBS
@@ -263,10 +262,10 @@ __global__ __launch_bounds__(kWave) void render_forward_kernel(
     const T u = T(lx) + T(0.5), v = T(ly) + T(0.5);
     const T ox = T(tx * TW), oy = T(ty * TH);
     const uint32_t re = min(ranges[2 * tile + 1], cap), rs = min(ranges[2 * tile], re);
-    const uint32_t sbase = ckpt ? seg_base[tile] : 0u;  // used at the end
+    const uint32_t sbase = (kSeg && ckpt) ? seg_base[tile] : 0u;  // used at the end
     int tgt = -2;
     if (target && in_img) tgt = job_target(V.cam[view].job, target[view * HW + pix]);
-    if constexpr (PROBS)
+    if (PROBS)
         for (int k = 0; k < K; ++k) s_P[k * BLOCK + tid] = T(0);
 
     T Tt = T(1), c0 = T(0), c1 = T(0), c2 = T(0), dd = T(0), pt = T(0);
@@ -292,14 +291,14 @@ __global__ __launch_bounds__(kWave) void render_forward_kernel(
     if (rs + BLOCK + tid < re) rec2 = pvals[rs + BLOCK + tid];
     for (uint32_t b0 = rs; b0 < re; b0 += BLOCK) {
         if (!wave_any(!done)) break;
-        {
+        if constexpr (kSeg) {
             // State before each segment boundary of the pair range, for the
             // segmented backward (which restarts there).
             const uint32_t rel = b0 - rs;
-            if (ckpt && rel > 0 && (rel & (seg_len - 1u)) == 0 && rel / seg_len < (uint32_t)kSegMax) {
-                const uint32_t e = boundary_record(rs, rel / seg_len, seg_len);
+            if (ckpt && rel > 0 && rel % kSegLen == 0 && rel / kSegLen < (uint32_t)kSegMax) {
+                const uint32_t e = boundary_record(rs, rel / kSegLen);
                 if (e < ckpt_cap) {
-                    T* c = ckpt + ((size_t)e * P::kCount + part) * 6 * kWave + tid;
+                    T* c = ckpt + (size_t)e * 6 * kWave + tid;
                     c[0 * kWave] = Tt;
                     c[1 * kWave] = c0;
                     c[2 * kWave] = c1;
@@ -397,41 +396,39 @@ __global__ __launch_bounds__(kWave) void render_forward_kernel(
             if (!wave_any(!done)) break;
         }
     }
-    if (ckpt) {
-        // The part's last blended position: how far its backward has work.
-        int m = lastpos;
+    if constexpr (kSeg) {
+        if (ckpt) {
+            // The tile's last blended position: how far its backward has work.
+            int m = lastpos;
 #pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) m = max(m, __shfl_xor(m, d));
-        if (tid == 0) tile_last[tile * P::kCount + part] = m;
-        // The tile's entries of the backward's segment list, at the place the
-        // sort reserved for its segments: the segment, the end of its walk
-        // and the boundary record at its end (none for the range's last).
-        // With one part the walk ends one past the last blended position where
-        // that lies in the segment (then nothing restarts at its end), and
-        // the segments behind are marked empty (no walk); with several, the
-        // backward takes the end from the parts' last positions.
-        const uint32_t nseg = tile_segments(re - rs, seg_len);
-        constexpr bool kTrim = P::kCount == 1;
-        const uint32_t k = !kTrim ? nseg
-                           : (m >= (int)rs && m < (int)re) ? min(((uint32_t)m - rs) / seg_len + 1u, nseg)
-                                                           : 0u;
-        const uint32_t last_end = kTrim ? (uint32_t)m + 1u : 0xFFFFFFFFu;
-        for (uint32_t j = (uint32_t)tid; part == 0 && j < nseg; j += kWave) {
-            const uint32_t pos = sbase + j;
-            if (pos >= seg_cap) break;
-            const uint32_t s0 = rs + j * seg_len;
-            const bool tail = j + 1u >= nseg;  // the last segment takes the rest of the range
-            const uint32_t s1 = tail ? re : s0 + seg_len;
-            const bool past = !tail && last_end > s1;
-            seg_list[pos] = j < k ? make_uint4((uint32_t)tile, s0, min(last_end, s1),
-                                               past ? boundary_record(rs, j + 1u, seg_len) : kNoBoundary)
-                                  : make_uint4((uint32_t)tile, 0u, 0u, kNoBoundary);
-        }
-        if (blockIdx.x == 0 && tid == 0) {
-            // the forward these states belong to (checked by the backward)
-            ctrl->seg_stamp[0] = ctrl->epoch;
-            ctrl->seg_stamp[1] = (uint64_t)(uintptr_t)last;
-            ctrl->seg_stamp[2] = (uint64_t)(uintptr_t)target;
+            for (int d = 32; d >= 1; d >>= 1) m = max(m, __shfl_xor(m, d));
+            if (tid == 0) tile_last[tile] = m;
+            // The tile's entries of the backward's segment list, at the place
+            // the sort reserved for its segments: every 64-pair segment up to
+            // the last blended position, with the end of its walk (one past
+            // that position when it lies in the segment) and the boundary
+            // record at its end (none where no pixel blends past it: the
+            // segment holding the last blended position and the range's
+            // last); the segments behind are marked empty (no walk).
+            const uint32_t nseg = tile_segments(re - rs);
+            const uint32_t k = (m >= (int)rs && m < (int)re) ? min(((uint32_t)m - rs) / (uint32_t)kSegLen + 1u, nseg) : 0u;
+            const uint32_t last_end = (uint32_t)m + 1u;
+            for (uint32_t j = (uint32_t)tid; j < nseg; j += kWave) {
+                const uint32_t pos = sbase + j;
+                if (pos >= seg_cap) break;
+                const uint32_t s0 = rs + j * (uint32_t)kSegLen;
+                const bool tail = j + 1u >= nseg;  // the last segment takes the rest of the range
+                const uint32_t s1 = tail ? re : s0 + (uint32_t)kSegLen;
+                const bool past = !tail && last_end > s1;
+                seg_list[pos] = j < k ? make_uint4((uint32_t)tile, s0, min(last_end, s1), past ? boundary_record(rs, j + 1u) : kNoBoundary)
+                                      : make_uint4((uint32_t)tile, 0u, 0u, kNoBoundary);
+            }
+            if (blockIdx.x == 0 && tid == 0) {
+                // the forward these states belong to (checked by the backward)
+                ctrl->seg_stamp[0] = ctrl->epoch;
+                ctrl->seg_stamp[1] = (uint64_t)(uintptr_t)last;
+                ctrl->seg_stamp[2] = (uint64_t)(uintptr_t)target;
+            }
         }
     }
     if (!in_img) return;
@@ -444,7 +441,7 @@ __global__ __launch_bounds__(kWave) void render_forward_kernel(
     last[o] = lastpos;
     if (NB && nblend) nblend[o] = nb_count;
     if (ptarget && target) ptarget[o] = (tgt == -1) ? Tt : pt;
-    if constexpr (PROBS) {
+    if (PROBS) {
         int best = K;
         T bv = Tt;
         for (int k = K - 1; k >= 0; --k) {
@@ -566,24 +563,20 @@ __device__ __forceinline__ void flush_slots(T (&v)[64], uint32_t chunk, T* __res
     }
 }
 
-// Sum of w dL/dw over a tile's segments behind boundary record bnd, which ends
-// the segment [s0, s1) of a range starting at rs: records bnd, bnd + 1, ...
-// up to the segment of the tile's last blended position (the range's segment
-// kSegMax - 1 is its last).
-template <typename T>
-__device__ __forceinline__ T sum_of_later_segments(const T* __restrict__ sums, int stride, uint32_t bnd, uint32_t s0,
-                                                   uint32_t s1, uint32_t rs, uint32_t seg_len, int tlast,
-                                                   uint32_t ckpt_cap) {
-    const uint32_t next = (s0 - rs) / seg_len + 1u;
-    const uint32_t n = min(((uint32_t)tlast - s1) / seg_len, (uint32_t)kSegMax - 1u - next) + 1u;
-    T a = T(0);
-    for (uint32_t k = 0; k < n; ++k) a += sums[(size_t)min(bnd + k, ckpt_cap - 1u) * stride];
-    return a;
-}
-
-#ifndef DQO_BWD_PARTS_OCC
-#define DQO_BWD_PARTS_OCC 3
+// Segment units in chunks of 16 consecutive list entries (a tile's segments,
+// which read the same pixel inputs) on one XCD: workgroup b runs on XCD b % 8,
+// and the chunks are dealt to the XCDs round-robin, so the heavy tiles at the
+// head of the list still spread over the device.  Each XCD has its own L2; at
+// the 200k view this cut the backward's HBM reads from 148 to 103 MB (chunks
+// of 4: 116 MB, of 64: 99 MB but slower).
+#ifndef DQO_BWD_XCD_CHUNK
+#define DQO_BWD_XCD_CHUNK 16
 #endif
+__device__ __forceinline__ uint32_t seg_unit(uint32_t b) {
+    constexpr uint32_t c = DQO_BWD_XCD_CHUNK;
+    const uint32_t x = b % 8u, r = b / 8u;
+    return ((r / c) * 8u + x) * c + r % c;
+}
 template <int C>
 struct SlotIdx {
     static constexpr int value = C;
@@ -597,8 +590,8 @@ __device__ __forceinline__ void backward_unit(
     const int32_t* __restrict__ target, const T* __restrict__ dC, const T* __restrict__ dD, const T* __restrict__ dT,
     const T* __restrict__ dP, const T* __restrict__ dPt, T* __restrict__ partials, uint8_t* __restrict__ written,
     uint32_t cap, uint32_t M, const uint4* __restrict__ seg_list, const T* __restrict__ ckpt, uint32_t ckpt_cap,
-    const T* __restrict__ color, const T* __restrict__ depth, const T* __restrict__ ptarget,
-    const T* __restrict__ seg_sums, const int32_t* __restrict__ tile_last, T* s_sp, uint32_t* s_slot, uint32_t unit) {
+    const T* __restrict__ color, const T* __restrict__ depth, const T* __restrict__ ptarget, T* s_sp,
+    uint32_t* s_slot, uint32_t unit) {
     const int lane = threadIdx.x;
     const uint32_t n_tiles = (uint32_t)(V.n_views * V.tiles_per_view);
     // A listed segment comes with its walk [s0, hi) and the boundary record
@@ -642,7 +635,7 @@ __device__ __forceinline__ void backward_unit(
     int lastp = -1;
     T Tcur = T(1), gc0 = T(0), gc1 = T(0), gc2 = T(0), gd = T(0), gt = T(0), gpt = T(0);
     int tgt = -2, tgt_raw = -1;
-    T ck[6] = {}, later = T(0), col0 = T(0), col1 = T(0), col2 = T(0), dep = T(0), ptg = T(0);
+    T ck[6] = {}, col0 = T(0), col1 = T(0), col2 = T(0), dep = T(0), ptg = T(0);
     if (inside) {
         lastp = last[o];
         Tcur = tfinal[o];
@@ -660,19 +653,13 @@ __device__ __forceinline__ void backward_unit(
             // from the state the forward stored there (loaded for every
             // pixel, beside the values above).
             const T* c = ckpt + (size_t)min(bnd, ckpt_cap - 1u) * 6 * kWave + lane;
-            ck[0] = c[0];
-            if constexpr (PROBS) {
-                later = sum_of_later_segments<T>(seg_sums + lane, kWave, bnd, s0, s1, ranges[2 * tile], kSegLen,
-                                                 tile_last[tile], ckpt_cap);
-            } else {
 #pragma unroll
-            for (int q = 1; q < 6; ++q) ck[q] = c[q * kWave];
+            for (int q = 0; q < 6; ++q) ck[q] = c[q * kWave];
             col0 = color[(view * 3 + 0) * HW + pix];
             col1 = color[(view * 3 + 1) * HW + pix];
             col2 = color[(view * 3 + 2) * HW + pix];
             dep = depth[o];
             ptg = ptarget ? ptarget[o] : T(0);
-            }
         }
     }
     // A lane's record of a batch and its pair slot (kNoSlot: a pair the
@@ -697,10 +684,10 @@ __device__ __forceinline__ void backward_unit(
         if (bnd != kNoBoundary) {
             // The sum behind the boundary is the total minus the part in front
             // of it (colour without the background term, depth, target
-            // probability), or with instance channels the later segments' sums.
+            // probability).
             if (lastp >= (int)s1) {
                 const T Tf = Tcur;
-                const T behind = PROBS ? later : gc0 * ((col0 - Tf * cs.bg[0]) - ck[1]) + gc1 * ((col1 - Tf * cs.bg[1]) - ck[2]) +
+                const T behind = gc0 * ((col0 - Tf * cs.bg[0]) - ck[1]) + gc1 * ((col1 - Tf * cs.bg[1]) - ck[2]) +
                                  gc2 * ((col2 - Tf * cs.bg[2]) - ck[3]) + gd * (dep - ck[4]) +
                                  (tgt >= 0 ? gpt * (ptg - ck[5]) : T(0));
                 S_restart = behind + Tf * (gc0 * cs.bg[0] + gc1 * cs.bg[1] + gc2 * cs.bg[2] + gt);
@@ -895,317 +882,177 @@ __device__ __forceinline__ void backward_unit(
     }
 }
 
-// The backward of a tile of several 64-pixel parts, by one wavefront: lane l
-// holds pixel l of every part.  A record is read from LDS and controlled once
-// for all parts, tested only on the parts that its bounds reach (a mask per
-// record, found when the batch is staged), and the parts' gradients meet in the
-// lane before the transposed sums, so those cost one part's work per Gaussian.
-// With a workgroup of one wavefront per 64 pixels of the tile in step (every
-// wave testing every record, sums over the waves through LDS with a barrier
-// per six Gaussians) the backward of 30k Gaussians at 333x251 in 16x16 tiles
-// took 445 us, of eight keyframes of 1.2M in 16x8 tiles 1375 us; now 66 (and 20 for
-// the segments' sums of the instance channels) and 927 us.
-template <typename T, int TW, int TH, bool PROBS, bool PREFETCH>
-__device__ __forceinline__ void backward_parts(
-    const Views<T>& V, const Consts<T>& cs, int K, const T* __restrict__ splats,
-    const uint32_t* __restrict__ pvals, const uint32_t* __restrict__ ranges,
-    const uint32_t* __restrict__ schedule, const T* __restrict__ tfinal, const int32_t* __restrict__ last,
-    const int32_t* __restrict__ target, const T* __restrict__ dC, const T* __restrict__ dD, const T* __restrict__ dT,
-    const T* __restrict__ dP, const T* __restrict__ dPt, T* __restrict__ partials, uint8_t* __restrict__ written,
-    uint32_t cap, uint32_t M, const uint4* __restrict__ seg_list, const T* __restrict__ ckpt, uint32_t ckpt_cap,
-    const T* __restrict__ color, const T* __restrict__ depth, const T* __restrict__ ptarget,
-    const T* __restrict__ seg_sums, const int32_t* __restrict__ tile_last, uint32_t seg_len, T* s_sp, uint32_t* s_slot,
-    uint32_t* s_mask, uint32_t unit) {
+// PROBS: with gradients of the instance channels; SEG: a launch over the
+// segment list (instantiations of their own)
+template <typename T, int TW, int TH, bool PROBS, bool SEG>
+__global__ __launch_bounds__(kWave, 4) void render_backward_wave_kernel(
+    Views<T> V, Consts<T> cs, int K, const T* __restrict__ splats,
+    const uint32_t* __restrict__ pvals, const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ schedule,
+    const T* __restrict__ tfinal, const int32_t* __restrict__ last, const int32_t* __restrict__ target,
+    const T* __restrict__ dC, const T* __restrict__ dD, const T* __restrict__ dT, const T* __restrict__ dP,
+    const T* __restrict__ dPt, T* __restrict__ partials, uint8_t* __restrict__ written, uint32_t cap, uint32_t M,
+    const uint4* __restrict__ seg_list, const T* __restrict__ ckpt, uint32_t ckpt_cap, const T* __restrict__ color,
+    const T* __restrict__ depth, const T* __restrict__ ptarget, const Ctrl* __restrict__ ctrl) {
+    static_assert(TW * TH == kWave, "one wavefront per tile");
+    __shared__ __align__(16) T s_sp[kWave * kWalkWords];
+    __shared__ uint32_t s_slot[kWave];
+
+    const int lane = threadIdx.x;
+    // One wavefront per tile, or (with a segment list) per listed segment of
+    // a tile's pair range, [s0, s1) of [rs, re); the list is built after the
+    // forward, so its length is read here and the rest of the grid, sized for
+    // the longest possible list, exits at once.  (A resident grid drawing
+    // entries from a work counter was measured slower: the loop around the
+    // walk raised its register demand past the budget and spilled.)
+    // The segments restart from states stored by one particular forward; if
+    // the frame was binned again since, or the images are another forward's,
+    // those states are not this backward's and every tile is walked whole
+    // instead (the grid holds at least one workgroup per tile).
+    const uint32_t n_tiles = (uint32_t)(V.n_views * V.tiles_per_view);
+    if (seg_list && (ctrl->seg_stamp[0] != (uint64_t)ctrl->epoch || ctrl->seg_stamp[1] != (uint64_t)(uintptr_t)last ||
+                     ctrl->seg_stamp[2] != (uint64_t)(uintptr_t)target))
+        seg_list = nullptr;
+    const uint32_t n_units = seg_list ? ctrl->counters[kCounterSegTotal] : n_tiles;
+    uint32_t unit = blockIdx.x;
+    if (SEG && seg_list) unit = seg_unit(blockIdx.x);
+    if (unit >= n_units) return;
+    // (a segmented launch walks a stale frame's whole tiles without prefetch)
+    backward_unit<T, TW, TH, PROBS, !SEG>(V, cs, K, splats, pvals, ranges, schedule, tfinal, last, target, dC, dD, dT,
+                                          dP, dPt, partials, written, cap, M, seg_list, ckpt, ckpt_cap, color, depth,
+                                          ptarget, s_sp, s_slot, unit);
+}
+
+// The backward of a tile of more than 64 pixels: a workgroup of NW waves, each
+// on a strip of 64 consecutive pixels of the tile in row order.  The waves
+// share one pass over the pair range in batches of 64, but within a batch each
+// walks alone: it keeps the records that can reach its strip, finds the next
+// one that contributes there, and sums six of them at a time over its lanes
+// into its own LDS rows; one barrier per batch, then the waves' sums of a
+// record are added in wave order and written once per pair.  (The waves in
+// step, every wave testing every record that touches the tile, the sums through
+// LDS with a barrier for every six, took 445 us on 30k Gaussians at 333x251 in
+// 16x16 tiles with instance channels and 1375 us on eight keyframes of 1.2M in
+// 16x8 tiles; now 52 us, behind
+// 85 us of the recurrence, and 1267 us.  The same sums in the same order.)
+template <int NS, typename T>
+__device__ __forceinline__ void flush_rows(T (&v)[64], uint32_t chunk, T* __restrict__ rows) {
+    int lane = (int)__lane_id();
+    asm volatile("" : "+v"(lane));
+    const int lane_slot = (lane * 205) >> 11;  // lane / kGradWords for lane < 64
+    const int word = lane - lane_slot * kGradWords;
+#pragma unroll
+    for (int k = NS * kGradWords; k < 64; ++k) v[k] = T(0);
+    wave_transpose_sum<T>(v, lane);
+    const uint32_t rec = (uint32_t)__shfl((int)chunk, lane_slot);
+    if (lane < NS * kGradWords) rows[rec * kGradWords + word] = v[0];
+}
+
+// A wave's share of the backward of a tile: its pixel's upstream gradients and
+// the state of its walk.
+template <typename T>
+struct BwdPixel {
+    int lastp, tgt;
+    T Tcur, S, gc0, gc1, gc2, gd, gpt;  // gpt: zero unless the pixel's target is an object
+};
+template <typename T>
+__device__ __forceinline__ BwdPixel<T> load_bwd_pixel(const Views<T>& V, const Consts<T>& cs, int view, int px, int py,
+                                                      uint32_t rs, uint32_t re, const T* __restrict__ tfinal,
+                                                      const int32_t* __restrict__ last,
+                                                      const int32_t* __restrict__ target, const T* __restrict__ dC,
+                                                      const T* __restrict__ dD, const T* __restrict__ dT,
+                                                      const T* __restrict__ dPt) {
+    BwdPixel<T> b{-1, -2, T(1), T(0), T(0), T(0), T(0), T(0), T(0)};
+    const int64_t HW = (int64_t)V.W * V.H, pix = (int64_t)py * V.W + px, o = view * HW + pix;
+    T gt = T(0);
+    if (px < V.W && py < V.H && in_window(V.cam[view], px, py)) {
+        b.lastp = last[o];
+        if (b.lastp < (int)rs || b.lastp >= (int)re) b.lastp = -1;  // not from this frame's forward: no work
+        b.Tcur = tfinal[o];
+        b.gc0 = dC[(view * 3 + 0) * HW + pix];
+        b.gc1 = dC[(view * 3 + 1) * HW + pix];
+        b.gc2 = dC[(view * 3 + 2) * HW + pix];
+        b.gd = dD ? dD[o] : T(0);
+        gt = dT ? dT[o] : T(0);
+        if (dPt && target) {
+            b.tgt = job_target(V.cam[view].job, target[o]);
+            b.gpt = dPt[o];
+            if (b.tgt == -1) gt += b.gpt;
+            if (b.tgt < 0) b.gpt = T(0);
+        }
+    }
+    b.S = b.Tcur * (b.gc0 * cs.bg[0] + b.gc1 * cs.bg[1] + b.gc2 * cs.bg[2] + gt);
+    return b;
+}
+// dL/dw of a Gaussian at a pixel: its colour, depth and object against the
+// upstream gradients (w: its walk record).
+template <typename T, bool PROBS>
+__device__ __forceinline__ T blend_grad(const BwdPixel<T>& b, const T* w, T a, const T* __restrict__ dP, int64_t plane0,
+                                        int64_t HW, int64_t pix, int K) {
+    const int id = word_to_id<T>(w[kWId]);
+    T vv = fmadd(b.gc0, w[kWR], fmadd(b.gc1, w[kWG], fmadd(b.gc2, w[kWB], b.gd * w[kWZ])));
+    vv += (id == b.tgt) ? b.gpt : T(0);
+    if constexpr (PROBS) {
+        if (a != T(0) && id >= 0 && id < K) vv += dP[(plane0 + id) * HW + pix];
+    }
+    return vv;
+}
+
+// The backward's recurrence by itself: every 8 x 8 pixel part of a tile walks
+// its range from the last blended position to the front, with the arithmetic
+// of the gradient walk (so the states are the ones it would reach), and stores
+// T and the suffix sum S behind every kSegLen-th pair.  That is the serial part
+// of the backward; without the gradients' ten words and their sums over the
+// wave it runs like the forward (groups of records tested side by side), and
+// the segments between the boundaries then go side by side.  Also writes the
+// segment list (the place of each tile's entries comes from the sort) and the
+// parts' last blended positions.
+template <typename T, int TW, int TH, bool PROBS>
+__global__ __launch_bounds__(kWave) void suffix_state_kernel(
+    Views<T> V, Consts<T> cs, int K, const T* __restrict__ splats, const uint32_t* __restrict__ pvals,
+    const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ schedule, const T* __restrict__ tfinal,
+    const int32_t* __restrict__ last, const int32_t* __restrict__ target, const T* __restrict__ dC,
+    const T* __restrict__ dD, const T* __restrict__ dT, const T* __restrict__ dP, const T* __restrict__ dPt,
+    uint32_t cap, uint32_t M, const uint32_t* __restrict__ seg_base, uint2* __restrict__ suf_list, uint32_t seg_cap,
+    T* __restrict__ suffix, uint32_t suf_cap, int32_t* __restrict__ tile_last) {
     using P = Parts<TW, TH>;
-    constexpr int N = P::kCount;
+    __shared__ __align__(16) T s_sp[kWave * kWalkWords];
+    extern __shared__ unsigned char s_dyn[];
+    T* s_dP = reinterpret_cast<T*>(s_dyn);  // [K][64] the pixels' channel gradients with PROBS (a gather per record waits longer)
     const int lane = threadIdx.x;
     const uint32_t n_tiles = (uint32_t)(V.n_views * V.tiles_per_view);
-    int tile;
-    uint32_t s0, s1, hi = 0u, bnd = kNoBoundary;
-    int tlast = -1;
-    if (seg_list) {
-        const uint4 en = seg_list[unit];
-        tile = (int)min(en.x, n_tiles - 1u);
-        s0 = min(en.y, cap);
-        s1 = min(max(en.z, s0), cap);
-#pragma unroll
-        for (int q = 0; q < N; ++q) tlast = max(tlast, tile_last[tile * N + q]);
-        if (tlast < (int)s0) return;  // behind every pixel's last blended position (uniform)
-        hi = min((uint32_t)tlast + 1u, s1);
-        bnd = tlast >= (int)s1 ? en.w : kNoBoundary;
-    } else {
-        tile = (int)min(schedule[unit], n_tiles - 1u);
-        s0 = min(ranges[2 * tile], cap);
-        s1 = min(ranges[2 * tile + 1], cap);
+    uint32_t rank = blockIdx.x;
+    int part = 0;
+    if constexpr (P::kCount > 1) {
+        const uint32_t x = blockIdx.x % 8u, r = blockIdx.x / 8u;
+        part = (int)(r % P::kCount);
+        rank = (r / P::kCount) * 8u + x;
+        if (rank >= n_tiles) return;
     }
+    const int tile = (int)min(schedule[rank], n_tiles - 1u);
     const int view = tile / V.tiles_per_view;
     const int t = tile - view * V.tiles_per_view;
     const int ty = t / V.tiles_x, tx = t - ty * V.tiles_x;
-    const int64_t HW = (int64_t)V.W * V.H;
-    const T ox = T(tx * TW), oy = T(ty * TH);
-    auto batch_lo = [&](uint32_t e) { return (e - s0 > (uint32_t)kWave) ? e - kWave : s0; };
-    uint32_t rec_first = 0u;
-    if (seg_list && lane < (int)(hi - batch_lo(hi))) rec_first = pvals[batch_lo(hi) + lane];
-
-    int lastp[N], tgt[N];
-    T Tcur[N], S[N], gc0[N], gc1[N], gc2[N], gd[N], gpt[N];
-    int64_t at[N];
-    int maxlast = -1;
-#pragma unroll
-    for (int q = 0; q < N; ++q) {
-        const int px = tx * TW + P::x0(q) + (lane & 7), py = ty * TH + P::y0(q) + (lane >> 3);
-        const int64_t pix = (int64_t)py * V.W + px, o = view * HW + pix;
-        at[q] = pix;
-        lastp[q] = -1;
-        tgt[q] = -2;
-        Tcur[q] = T(1);
-        S[q] = gc0[q] = gc1[q] = gc2[q] = gd[q] = gpt[q] = T(0);
-        if (!(px < V.W && py < V.H && in_window(V.cam[view], px, py))) continue;
-        lastp[q] = last[o];
-        Tcur[q] = tfinal[o];
-        gc0[q] = dC[(view * 3 + 0) * HW + pix];
-        gc1[q] = dC[(view * 3 + 1) * HW + pix];
-        gc2[q] = dC[(view * 3 + 2) * HW + pix];
-        gd[q] = dD ? dD[o] : T(0);
-        T gt = dT ? dT[o] : T(0);
-        if (dPt && target) {
-            tgt[q] = job_target(V.cam[view].job, target[o]);
-            gpt[q] = dPt[o];
-            if (tgt[q] == -1) gt += gpt[q];
-        }
-        if (lastp[q] < (int)s0 || (!seg_list && lastp[q] >= (int)s1)) lastp[q] = -1;
-        const T Tf = Tcur[q];
-        T behind = T(0);
-        if (bnd != kNoBoundary && lastp[q] >= (int)s1) {
-            // the pixel blends past this segment: it restarts at its end
-            const uint32_t e = min(bnd, ckpt_cap - 1u);
-            const T* c = ckpt + ((size_t)e * N + q) * 6 * kWave + lane;
-            if constexpr (PROBS) {
-                behind = sum_of_later_segments<T>(seg_sums + q * kWave + lane, N * kWave, bnd, s0, s1, ranges[2 * tile],
-                                                  seg_len, tlast, ckpt_cap);
-            } else {
-                behind = gc0[q] * ((color[(view * 3 + 0) * HW + pix] - Tf * cs.bg[0]) - c[1 * kWave]) +
-                         gc1[q] * ((color[(view * 3 + 1) * HW + pix] - Tf * cs.bg[1]) - c[2 * kWave]) +
-                         gc2[q] * ((color[(view * 3 + 2) * HW + pix] - Tf * cs.bg[2]) - c[3 * kWave]) +
-                         gd[q] * (depth[o] - c[4 * kWave]) +
-                         (tgt[q] >= 0 ? gpt[q] * ((ptarget ? ptarget[o] : T(0)) - c[5 * kWave]) : T(0));
-            }
-            Tcur[q] = c[0];
-            lastp[q] = (int)s1 - 1;
-        }
-        S[q] = behind + Tf * (gc0[q] * cs.bg[0] + gc1[q] * cs.bg[1] + gc2[q] * cs.bg[2] + gt);
-        // the target-probability gradient joins a Gaussian's colour sum where
-        // its object is the pixel's target (tgt -1: T_final's gradient carries it)
-        if (tgt[q] < 0) gpt[q] = T(0);
-        maxlast = max(maxlast, lastp[q]);
-    }
-    if (!seg_list) {
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) maxlast = max(maxlast, __shfl_xor(maxlast, d));
-        maxlast = __builtin_amdgcn_readfirstlane(maxlast);  // uniform: scalar walk bounds
-        hi = (maxlast >= (int)s0) ? (uint32_t)(maxlast + 1) : s0;
-    }
-    T pf[kRecWords];
-    uint32_t pf_slot = kNoSlot;
-    auto load_pair = [&](uint32_t pv) {
-        if (pv & kPairSkip) pf_slot = kNoSlot;
-        else pf_slot = load_splat_slot<T>(pf, splats + (size_t)min(pv, M - 1) * kSplatWords, tx, ty);
-    };
-    int bx0, bx1, by0, by1;
-    tile_pixel_box<T>(V, view, tx, ty, TW, TH, bx0, bx1, by0, by1);
-
-    T v[64];
-#pragma unroll
-    for (int k = 0; k < 64; ++k) v[k] = T(0);
-    uint32_t chunk = 0u;
-    int filled = 0;  // reduction slots in use
-    uint32_t a_e = hi, a_s = batch_lo(hi);
-    if (lane < (int)(a_e - a_s)) load_pair(seg_list ? rec_first : pvals[a_s + lane]);
-    while (a_e > a_s) {
-        const uint32_t bstart = a_s;
-        const int nbr = (int)(a_e - a_s);
-        uint32_t mask = 0u;
-        if (lane < nbr && pf_slot != kNoSlot) {
-#pragma unroll
-            for (int q = 0; q < N; ++q) {
-                const int x0 = tx * TW + P::x0(q), y0 = ty * TH + P::y0(q);
-                if (tile_may_contribute<T>(pf, max(bx0, x0), min(bx1, x0 + 7), max(by0, y0), min(by1, y0 + 7), cs))
-                    mask |= 1u << q;
-            }
-        }
-        __syncthreads();
-        const uint64_t bal = __builtin_amdgcn_ballot_w64(mask != 0u);
-        if (mask) {
-            const int k = rank_below(bal);
-            store_walk_record<T>(s_sp + k * kWalkWords, pf, ox, oy, (int)(bstart + lane), cs);
-            s_slot[k] = pf_slot;
-            s_mask[k] = mask;
-        }
-        __syncthreads();
-        const int nb = __popcll(bal);
-        const uint32_t mine = lane < nb ? s_mask[lane] : 0u;
-        uint64_t reach[N];  // bit j: record j reaches part q
-#pragma unroll
-        for (int q = 0; q < N; ++q) reach[q] = __builtin_amdgcn_ballot_w64((mine >> q) & 1u);
-        // the next batch (its records in flight during the walk with PREFETCH)
-        a_e = a_s;
-        a_s = batch_lo(a_s);
-        uint32_t next_pv = 0u;
-        if (lane < (int)(a_e - a_s)) next_pv = pvals[a_s + lane];
-        if constexpr (PREFETCH) {
-            if (lane < (int)(a_e - a_s)) load_pair(next_pv);
-        }
-        for (int jl = nb - 1; jl >= 0; --jl) {
-            const T* rec = s_sp + jl * kWalkWords;
-            T w[kWB + 1];
-#pragma unroll
-            for (int k = 0; k <= kWB; ++k) w[k] = rec[k];
-            T g[kGradWords];
-#pragma unroll
-            for (int k = 0; k < kGradWords; ++k) g[k] = T(0);
-            bool any = false;
-            const int id = word_to_id<T>(w[kWId]), pos = word_to_id<T>(w[kWPos]);
-#pragma unroll
-            for (int q = 0; q < N; ++q) {
-                if (!((reach[q] >> jl) & 1ull)) continue;  // uniform
-                const T u = T(P::x0(q) + (lane & 7)) + T(0.5), vp = T(P::y0(q) + (lane >> 3)) + T(0.5);
-                T dx, dy, pp, rr;
-                const T E = walk_exponent(w, u, vp, dx, dy, pp, rr);
-                const T araw = exp2_of<T>(E);
-                const bool clamped = !(araw < cs.alpha_max);
-                const bool contrib = (E >= w[kWThr]) & (pos <= lastp[q]);
-                const T a = contrib ? (clamped ? cs.alpha_max : araw) : T(0);
-                if (__builtin_amdgcn_ballot_w64(a != T(0)) == 0ull) continue;
-                any = true;
-                const T a_free = clamped ? T(0) : a;
-                const T roma = fast_rcp<T>(T(1) - a);
-                const T Ti = Tcur[q] * roma;
-                const T wt = a * Ti;
-                T vv = fmadd(gc0[q], w[kWR], fmadd(gc1[q], w[kWG], fmadd(gc2[q], w[kWB], gd[q] * w[kWZ])));
-                vv += (id == tgt[q]) ? gpt[q] : T(0);
-                if constexpr (PROBS) {
-                    if (a != T(0) && id >= 0 && id < K) vv += dP[((int64_t)view * K + id) * HW + at[q]];
-                }
-                const T dalpha = fmadd(Ti, vv, -(S[q] * roma));
-                S[q] = fmadd(wt, vv, S[q]);
-                Tcur[q] = Ti;
-                const T dq = dalpha * a_free;
-                const T t1 = dq * dx, t2 = dq * dy;
-                g[0] = fmadd(dq, pp, g[0]);
-                g[1] = fmadd(dq, rr, g[1]);
-                g[2] = fmadd(t1, dx, g[2]);
-                g[3] = fmadd(t1, dy, g[3]);
-                g[4] = fmadd(t2, dy, g[4]);
-                g[5] += dq;
-                g[6] = fmadd(gc0[q], wt, g[6]);
-                g[7] = fmadd(gc1[q], wt, g[7]);
-                g[8] = fmadd(gc2[q], wt, g[8]);
-                g[9] = fmadd(gd[q], wt, g[9]);
-            }
-            if (!any) continue;
-            const uint32_t pslot = s_slot[jl];
-            chunk = (lane == filled) ? pslot : chunk;
-#pragma unroll
-            for (int c = 0; c < kChunk; ++c)
-                if (filled == c) {  // uniform
-#pragma unroll
-                    for (int k = 0; k < kGradWords; ++k) v[c * kGradWords + k] = g[k];
-                }
-            if (++filled == kChunk) {
-                flush_slots<kChunk>(v, chunk, partials, written, cap);
-                filled = 0;
-            }
-        }
-        if constexpr (!PREFETCH) {
-            if (lane < (int)(a_e - a_s)) load_pair(next_pv);
-        }
-    }
-    if (filled == 1) flush_slots<1>(v, chunk, partials, written, cap);
-    else if (filled == 2) flush_slots<2>(v, chunk, partials, written, cap);
-    else if (filled == 3) flush_slots<3>(v, chunk, partials, written, cap);
-    else if (filled == 4) flush_slots<4>(v, chunk, partials, written, cap);
-    else if (filled == 5) flush_slots<5>(v, chunk, partials, written, cap);
-}
-
-// The segmented backward's states belong to one particular forward; if the
-// frame was binned again since, or the images are another forward's, they are
-// not this backward's and every tile is walked whole instead.
-__device__ __forceinline__ bool seg_states_valid(const Ctrl* ctrl, const void* last, const void* target) {
-    return ctrl->seg_stamp[0] == (uint64_t)ctrl->epoch && ctrl->seg_stamp[1] == (uint64_t)(uintptr_t)last &&
-           ctrl->seg_stamp[2] == (uint64_t)(uintptr_t)target;
-}
-
-// Segment units in chunks of 16 consecutive list entries (a tile's segments,
-// which read the same pixel inputs) on one XCD: workgroup b runs on XCD b % 8,
-// and the chunks are dealt to the XCDs round-robin, so the heavy tiles at the
-// head of the list still spread over the device.  Each XCD has its own L2; at
-// the 200k view this cut the backward's HBM reads from 148 to 103 MB (chunks
-// of 4: 116 MB, of 64: 99 MB but slower).
-#ifndef DQO_BWD_XCD_CHUNK
-#define DQO_BWD_XCD_CHUNK 16
-#endif
-__device__ __forceinline__ uint32_t seg_unit(uint32_t b) {
-    constexpr uint32_t c = DQO_BWD_XCD_CHUNK;
-    if constexpr (c == 0) return b;
-    const uint32_t x = b % 8u, r = b / 8u;
-    return ((r / c) * 8u + x) * c + r % c;
-}
-
-// Instance-channel gradients, segmented: the part of a pixel's suffix sum that
-// a segment holds, sum of w dL/dw over the pairs it blends there, from the
-// state the forward stored at the segment's start (the forward cannot know
-// these: they need the upstream gradients).  The segments of a tile run side
-// by side, and a backward segment then starts from the sum of the later ones
-// (a tile's first segment is nobody's later one and is left out).
-// A wavefront takes one 64-pixel part of one segment.
-template <typename T, int TW, int TH>
-__global__ __launch_bounds__(kWave) void segment_sums_kernel(
-    Views<T> V, Consts<T> cs, int K, const T* __restrict__ splats, const uint32_t* __restrict__ pvals,
-    const uint32_t* __restrict__ ranges, const int32_t* __restrict__ last, const int32_t* __restrict__ target,
-    const T* __restrict__ dC, const T* __restrict__ dD, const T* __restrict__ dP, const T* __restrict__ dPt,
-    uint32_t cap, uint32_t M, const uint4* __restrict__ seg_list, const T* __restrict__ ckpt, uint32_t ckpt_cap,
-    const int32_t* __restrict__ tile_last, uint32_t seg_len, T* __restrict__ seg_sums, const Ctrl* __restrict__ ctrl) {
-    using P = Parts<TW, TH>;
-    constexpr uint32_t N = P::kCount;
-    __shared__ __align__(16) T s_sp[kWave * kWalkWords];
-    if (!seg_states_valid(ctrl, last, target)) return;
-    const uint32_t b = seg_unit(blockIdx.x), unit = b / N;
-    const int part = (int)(b % N);
-    if (unit >= ctrl->counters[kCounterSegTotal]) return;
-    const int lane = threadIdx.x;
-    const uint4 en = seg_list[unit];
-    if (en.z <= en.y) return;
-    const int tile = (int)min(en.x, (uint32_t)(V.n_views * V.tiles_per_view) - 1u);
-    const uint32_t rs = min(ranges[2 * tile], cap), s0 = min(en.y, cap), s1 = min(max(en.z, s0), cap);
-    int tlast = -1;
-#pragma unroll
-    for (int q = 0; q < (int)N; ++q) tlast = max(tlast, tile_last[tile * (int)N + q]);
-    if (s0 <= rs || tlast < (int)s0) return;  // nobody's later segment
-    const int plast = tile_last[tile * (int)N + part];
-    const uint32_t hi = plast < (int)s0 ? s0 : min((uint32_t)plast + 1u, s1);  // (a part that ends before: zeros)
-    const uint32_t e = min(boundary_record(rs, (s0 - rs) / seg_len, seg_len), ckpt_cap - 1u);
-    const int view = tile / V.tiles_per_view;
-    const int t = tile - view * V.tiles_per_view;
-    const int ty = t / V.tiles_x, tx = t - ty * V.tiles_x;
-    const int64_t HW = (int64_t)V.W * V.H;
-    const T ox = T(tx * TW), oy = T(ty * TH);
     const int lx = P::x0(part) + (lane & 7), ly = P::y0(part) + (lane >> 3);
     const int px = tx * TW + lx, py = ty * TH + ly;
     const T u = T(lx) + T(0.5), vp = T(ly) + T(0.5);
-    const int64_t pix = (int64_t)py * V.W + px, o = view * HW + pix;
-    int lastp = -1, tgt = -2;
-    T Tt = T(0), A = T(0), gc0 = T(0), gc1 = T(0), gc2 = T(0), gd = T(0), gpt = T(0);
-    if (hi > s0 && px < V.W && py < V.H && in_window(V.cam[view], px, py)) {
-        lastp = last[o];
-        Tt = ckpt[((size_t)e * N + part) * 6 * kWave + lane];
-        gc0 = dC[(view * 3 + 0) * HW + pix];
-        gc1 = dC[(view * 3 + 1) * HW + pix];
-        gc2 = dC[(view * 3 + 2) * HW + pix];
-        gd = dD ? dD[o] : T(0);
-        if (dPt && target) {
-            tgt = job_target(V.cam[view].job, target[o]);
-            gpt = tgt >= 0 ? dPt[o] : T(0);
-        }
+    const T ox = T(tx * TW), oy = T(ty * TH);
+    const int64_t HW = (int64_t)V.W * V.H, pix = (int64_t)py * V.W + px;
+    const uint32_t re = min(ranges[2 * tile + 1], cap), rs = min(ranges[2 * tile], re);
+    if (part == 0) {
+        const uint32_t nseg = tile_segments(re - rs), base = seg_base[tile];
+        for (uint32_t j = (uint32_t)lane; j < nseg; j += kWave)
+            if (base + j < seg_cap) suf_list[base + j] = make_uint2((uint32_t)tile, j);
+    }
+    BwdPixel<T> b = load_bwd_pixel<T>(V, cs, view, px, py, rs, re, tfinal, last, target, dC, dD, dT, dPt);
+    int m = b.lastp;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) m = max(m, __shfl_xor(m, d));
+    m = __builtin_amdgcn_readfirstlane(m);
+    if (lane == 0) tile_last[tile * P::kCount + part] = m;
+    if (m < (int)rs + kSegLen) return;  // (nothing restarts in front of the first segment)
+    if constexpr (PROBS) {
+        const bool in_img = px < V.W && py < V.H;
+        for (int c = 0; c < K; ++c) s_dP[c * kWave + lane] = in_img ? dP[((int64_t)view * K + c) * HW + pix] : T(0);
     }
     int bx0, bx1, by0, by1;
     tile_pixel_box<T>(V, view, tx, ty, TW, TH, bx0, bx1, by0, by1);
@@ -1213,78 +1060,331 @@ __global__ __launch_bounds__(kWave) void segment_sums_kernel(
     bx1 = min(bx1, tx * TW + P::x0(part) + 7);
     by0 = max(by0, ty * TH + P::y0(part));
     by1 = min(by1, ty * TH + P::y0(part) + 7);
-    for (uint32_t b0 = s0; b0 < hi; b0 += kWave) {
-        T pf[kRecWords];
-        bool cand = false;
-        const uint32_t pv = b0 + lane < hi ? pvals[b0 + lane] : kPairSkip;
-        if (!(pv & kPairSkip)) {
-            load_splat_global<T>(pf, splats + (size_t)min(pv, M - 1) * kSplatWords);
-            cand = N == 1 || tile_may_contribute<T>(pf, bx0, bx1, by0, by1, cs);
-        }
-        __syncthreads();
+    const uint32_t hi = (uint32_t)m + 1u;
+    // batches [rs + 64 k, + 64), from the one that holds the last blended
+    // position; the next one's records are in flight during the walk
+    int k = (int)((hi - 1u - rs) / (uint32_t)kSegLen);
+    static_assert(kSegLen == kWave, "a batch per segment");
+    T pf[kRecWords];
+    bool have = false;
+    auto load_rec = [&](uint32_t pv) {
+        have = !(pv & kPairSkip);
+        if (have) load_splat_global<T>(pf, splats + (size_t)min(pv, M - 1) * kSplatWords);
+    };
+    auto pair_at = [&](int kk) {
+        const uint32_t at = rs + (uint32_t)(kk * kSegLen + lane);
+        return kk >= 0 && at < hi ? pvals[at] : kPairSkip;
+    };
+    load_rec(pair_at(k));
+    uint32_t pv_next = pair_at(k - 1);
+    for (; k > 0; --k) {
+        const uint32_t b0 = rs + (uint32_t)(k * kSegLen);
+        const bool cand = have && tile_may_contribute<T>(pf, bx0, bx1, by0, by1, cs);
         const uint64_t bal = __builtin_amdgcn_ballot_w64(cand);
+        const int nb = __popcll(bal);
+        __syncthreads();
         if (cand) store_walk_record<T>(s_sp + rank_below(bal) * kWalkWords, pf, ox, oy, (int)(b0 + lane), cs);
         __syncthreads();
-        const int nb = __popcll(bal);
-        for (int jl = 0; jl < nb; ++jl) {
-            const T* rec = s_sp + jl * kWalkWords;
-            T w[kWB + 1];
+        load_rec(pv_next);
+        pv_next = pair_at(k - 2);
+        // groups of records as in the forward: tests side by side, the blending
+        // words read together, then the recurrence
+        constexpr int G = fwd_group<T>();
+        for (int j0 = nb - 1; j0 >= 0; j0 -= G) {
+            T rec[G][kWPos + 1], a[G], vv[G];
+            bool any = false;
 #pragma unroll
-            for (int k = 0; k <= kWB; ++k) w[k] = rec[k];
-            const int id = word_to_id<T>(w[kWId]), pos = word_to_id<T>(w[kWPos]);
-            T dx, dy, pp, rr;
-            const T E = walk_exponent(w, u, vp, dx, dy, pp, rr);
-            const bool contrib = (E >= w[kWThr]) & (pos <= lastp);
-            const T a = contrib ? min(exp2_of<T>(E), cs.alpha_max) : T(0);
-            if (__builtin_amdgcn_ballot_w64(a != T(0)) == 0ull) continue;
-            T vv = fmadd(gc0, w[kWR], fmadd(gc1, w[kWG], fmadd(gc2, w[kWB], gd * w[kWZ])));
-            vv += (id == tgt) ? gpt : T(0);
-            if (a != T(0) && id >= 0 && id < K) vv += dP[((int64_t)view * K + id) * HW + pix];
-            A = fmadd(a * Tt, vv, A);
-            Tt = Tt * (T(1) - a);
+            for (int q = 0; q < G; ++q) {
+                const T* w = s_sp + max(j0 - q, 0) * kWalkWords;
+#pragma unroll
+                for (int c = 0; c <= kWPos; ++c) rec[q][c] = w[c];
+            }
+#pragma unroll
+            for (int q = 0; q < G; ++q) {
+                T dx, dy, pp, rr;
+                const T E = walk_exponent(rec[q], u, vp, dx, dy, pp, rr);
+                const T araw = exp2_of<T>(E);
+                const bool contrib = (j0 - q >= 0) & (E >= rec[q][kWThr]) & (word_to_id<T>(rec[q][kWPos]) <= b.lastp);
+                a[q] = contrib ? (!(araw < cs.alpha_max) ? cs.alpha_max : araw) : T(0);
+                any = any || contrib;
+            }
+            if (!wave_any(any)) continue;
+            T bl[G][kWB - kWZ + 1], dp[G];
+#pragma unroll
+            for (int q = 0; q < G; ++q) {
+                const T* w = s_sp + max(j0 - q, 0) * kWalkWords;
+#pragma unroll
+                for (int c = kWZ; c <= kWB; ++c) bl[q][c - kWZ] = w[c];
+            }
+#pragma unroll
+            for (int q = 0; q < G; ++q)
+#pragma unroll
+                for (int c = 0; c <= kWB - kWZ; ++c) asm volatile("" : "+v"(bl[q][c]));
+#pragma unroll
+            for (int q = 0; q < G; ++q) {
+                const int id = word_to_id<T>(bl[q][kWId - kWZ]);
+                dp[q] = T(0);
+                if constexpr (PROBS) {
+                    if ((uint32_t)id < (uint32_t)K) dp[q] = s_dP[id * kWave + lane];
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < G; ++q) {
+                const T* w = bl[q] - kWZ;
+                vv[q] = fmadd(b.gc0, w[kWR], fmadd(b.gc1, w[kWG], fmadd(b.gc2, w[kWB], b.gd * w[kWZ])));
+                vv[q] += (word_to_id<T>(w[kWId]) == b.tgt) ? b.gpt : T(0);
+                if constexpr (PROBS) vv[q] += dp[q];
+            }
+#pragma unroll
+            for (int q = 0; q < G; ++q) {
+                const T Ti = b.Tcur * fast_rcp<T>(T(1) - a[q]);
+                b.S = fmadd(a[q] * Ti, vv[q], b.S);
+                b.Tcur = Ti;
+            }
+        }
+        if (k < kSegMax) {
+            // the state behind boundary k (pixel-major, as the gradient walk reads it)
+            const uint32_t e = boundary_record(rs, (uint32_t)k);
+            if (e < suf_cap) {
+                T* st = suffix + (size_t)e * 2 * TW * TH + ly * TW + lx;
+                st[0] = b.Tcur;
+                st[TW * TH] = b.S;
+            }
         }
     }
-    seg_sums[((size_t)e * N + part) * kWave + lane] = A;
 }
 
-// PROBS: with gradients of the instance channels; SEG: a launch over the
-// segment list (instantiations of their own)
-template <typename T, int TW, int TH, bool PROBS, bool SEG>
-__global__ __launch_bounds__(kWave, TW* TH == kWave ? 4 : DQO_BWD_PARTS_OCC) void render_backward_wave_kernel(
+// SUF: a workgroup per listed segment, starting from the suffix pass's states;
+// else per tile.  Waves per SIMD: three without spills for the segments, whose
+// frames leave the machine half empty (of four, 14% slower), four with 60
+// bytes of spills for the frames that fill it (of three, 6% slower).
+template <typename T, int TW, int TH, bool PROBS, bool SUF>
+__global__ __launch_bounds__(TW* TH, sizeof(T) == 8 ? 1 : SUF ? 3 : 4) void render_backward_tile_kernel(
     Views<T> V, Consts<T> cs, int K, const T* __restrict__ splats,
     const uint32_t* __restrict__ pvals, const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ schedule,
     const T* __restrict__ tfinal, const int32_t* __restrict__ last, const int32_t* __restrict__ target,
     const T* __restrict__ dC, const T* __restrict__ dD, const T* __restrict__ dT, const T* __restrict__ dP,
     const T* __restrict__ dPt, T* __restrict__ partials, uint8_t* __restrict__ written, uint32_t cap, uint32_t M,
-    const uint4* __restrict__ seg_list, const T* __restrict__ ckpt, uint32_t ckpt_cap, const T* __restrict__ color,
-    const T* __restrict__ depth, const T* __restrict__ ptarget, const T* __restrict__ seg_sums,
-    const int32_t* __restrict__ tile_last, uint32_t seg_len, const Ctrl* __restrict__ ctrl) {
-    __shared__ __align__(16) T s_sp[kWave * kWalkWords];
-    __shared__ uint32_t s_slot[kWave];
+    const uint2* __restrict__ suf_list, const T* __restrict__ suffix, uint32_t suf_cap,
+    const int32_t* __restrict__ tile_last, const Ctrl* __restrict__ ctrl) {
+    constexpr int NW = TW * TH / kWave, kRows = kWave / TW;
+    static_assert(NW >= 1 && NW <= 4 && kWave % TW == 0, "strips of whole rows");
+    constexpr int kBufs = SUF ? 1 : 2;                // a listed segment is one batch (but the last of a long range)
+    __shared__ __align__(16) T s_sp[NW][kWave * kWalkWords];
+    __shared__ uint8_t s_idx[NW][kWave];              // the batch index of each kept record
+    __shared__ T s_acc[kBufs][NW][kWave * kGradWords];  // per wave and batch record: the strip's sums
+    __shared__ uint64_t s_taken[kBufs][NW];           // the batch records with sums
+    __shared__ uint32_t s_slot[kBufs][kWave];         // their pair slots
+    __shared__ int s_last[NW];
 
-    // One wavefront per tile, or (with a segment list) per listed segment of
-    // a tile's pair range; the list is built after the forward, so its length
-    // is read here and the rest of the grid, sized for the longest possible
-    // list, exits at once (it holds at least one workgroup per tile).  (A
-    // resident grid drawing entries from a work counter was measured slower:
-    // the loop around the walk raised its register demand past the budget and
-    // spilled.)
+    const int tid = threadIdx.x;
+    const int lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t n_tiles = (uint32_t)(V.n_views * V.tiles_per_view);
-    if (seg_list && !seg_states_valid(ctrl, last, target)) seg_list = nullptr;
-    const uint32_t n_units = seg_list ? ctrl->counters[kCounterSegTotal] : n_tiles;
-    uint32_t unit = blockIdx.x;
-    if (SEG && seg_list) unit = seg_unit(blockIdx.x);
-    if (unit >= n_units) return;
-    // (a segmented launch walks a stale frame's whole tiles without prefetch)
-    if constexpr (TW * TH == kWave) {
-        backward_unit<T, TW, TH, PROBS, !SEG>(V, cs, K, splats, pvals, ranges, schedule, tfinal, last, target, dC, dD,
-                                              dT, dP, dPt, partials, written, cap, M, seg_list, ckpt, ckpt_cap, color,
-                                              depth, ptarget, seg_sums, tile_last, s_sp, s_slot, unit);
+    int tile;
+    uint32_t seg = 0u;
+    if constexpr (SUF) {
+        const uint32_t unit = seg_unit(blockIdx.x);
+        if (unit >= ctrl->counters[kCounterSegTotal]) return;
+        const uint2 en = suf_list[unit];
+        tile = (int)min(en.x, n_tiles - 1u);
+        seg = en.y;
     } else {
-        __shared__ uint32_t s_mask[kWave];
-        backward_parts<T, TW, TH, PROBS, !SEG>(V, cs, K, splats, pvals, ranges, schedule, tfinal, last, target, dC, dD,
-                                               dT, dP, dPt, partials, written, cap, M, seg_list, ckpt, ckpt_cap, color,
-                                               depth, ptarget, seg_sums, tile_last, seg_len, s_sp, s_slot, s_mask, unit);
+        tile = (int)min(schedule[blockIdx.x], n_tiles - 1u);
+    }
+    const uint32_t re = min(ranges[2 * tile + 1], cap), rs = min(ranges[2 * tile], re);
+    // the pairs walked here: [s0, hi), up to the tile's last blended position;
+    // pixels that blend past s1 start from the state stored behind it
+    uint32_t s0 = rs, s1 = re, hi = rs;
+    bool past = false;
+    if constexpr (SUF) {
+        int tl = -1;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) tl = max(tl, tile_last[tile * NW + w]);
+        s0 = rs + seg * (uint32_t)kSegLen;
+        const bool tail = seg + 1u >= tile_segments(re - rs);  // takes the rest of the range
+        s1 = tail ? re : s0 + (uint32_t)kSegLen;
+        if (tl < (int)s0) return;  // behind every pixel's last blended position (uniform)
+        hi = min((uint32_t)tl + 1u, s1);
+        past = tl >= (int)s1;
+    }
+    const int view = tile / V.tiles_per_view;
+    const int t = tile - view * V.tiles_per_view;
+    const int ty = t / V.tiles_x, tx = t - ty * V.tiles_x;
+    const int px = tx * TW + (tid % TW), py = ty * TH + (tid / TW);
+    const int64_t HW = (int64_t)V.W * V.H;
+    const int64_t pix = (int64_t)py * V.W + px;
+    // the pixel centre relative to the tile's corner
+    const T u = T(tid % TW) + T(0.5), v_px = T(tid / TW) + T(0.5);
+    const T ox = T(tx * TW), oy = T(ty * TH);
+
+    // A lane's record of the next batch is held in registers while the current
+    // one is walked (pf_slot kNoSlot: a pair the forward marked, not loaded).
+    auto batch_lo = [&](uint32_t e) { return (e - s0 > (uint32_t)kWave) ? e - kWave : s0; };
+    T pf[kRecWords];
+    uint32_t pf_slot = kNoSlot;
+    auto load_pair = [&](uint32_t pv) {
+        if (pv & kPairSkip) pf_slot = kNoSlot;
+        else pf_slot = load_splat_slot<T>(pf, splats + (size_t)min(pv, M - 1) * kSplatWords, tx, ty);
+    };
+    uint32_t rec_b = 0u;
+    if (SUF && lane < (int)(hi - batch_lo(hi))) rec_b = pvals[batch_lo(hi) + lane];
+    BwdPixel<T> b = load_bwd_pixel<T>(V, cs, view, px, py, rs, re, tfinal, last, target, dC, dD, dT, dPt);
+    if (SUF && past && b.lastp >= (int)s1) {
+        const T* st = suffix + (size_t)min(boundary_record(rs, seg + 1u), suf_cap - 1u) * 2 * TW * TH + tid;
+        b.Tcur = st[0];
+        b.S = st[TW * TH];
+    }
+    int mylast = b.lastp;  // the strip's last blended position, uniform over the wave
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) mylast = max(mylast, __shfl_xor(mylast, d));
+    mylast = __builtin_amdgcn_readfirstlane(mylast);
+    if constexpr (!SUF) {
+        if (lane == 0) s_last[wave] = mylast;
+        __syncthreads();
+        int maxlast = -1;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) maxlast = max(maxlast, s_last[w]);
+        maxlast = __builtin_amdgcn_readfirstlane(maxlast);
+        // Pairs behind every pixel's last blended Gaussian are not written and
+        // stay unmarked (their partials count as zero).
+        hi = (maxlast >= (int)rs) ? (uint32_t)(maxlast + 1) : rs;
+        if (lane < (int)(hi - batch_lo(hi))) rec_b = pvals[batch_lo(hi) + lane];
+    }
+    const T iq = T(1) / neg_half_log2e<T>();
+
+    // the strip's pixels
+    int bx0, bx1, by0, by1;
+    tile_pixel_box<T>(V, view, tx, ty, TW, TH, bx0, bx1, by0, by1);
+    by0 = max(by0, ty * TH + wave * kRows);
+    by1 = min(by1, ty * TH + wave * kRows + kRows - 1);
+
+    uint32_t a_e = hi, a_s = batch_lo(hi);
+    if (lane < (int)(a_e - a_s)) load_pair(rec_b);
+    uint32_t b_s = batch_lo(a_s);
+    if (lane < (int)(a_s - b_s)) rec_b = pvals[b_s + lane];
+
+    T* sp_w = s_sp[wave];
+    T v[64];
+#pragma unroll
+    for (int k = 0; k < 64; ++k) v[k] = T(0);
+    for (int buf = 0; a_e > a_s; buf ^= kBufs - 1) {
+        const int nbr = (int)(a_e - a_s);
+        const bool work = mylast >= (int)a_s;  // uniform over the wave
+        const bool cand = work && lane < nbr && pf_slot != kNoSlot &&
+                          (NW == 1 || tile_may_contribute<T>(pf, bx0, bx1, by0, by1, cs));
+        const uint64_t bal = __builtin_amdgcn_ballot_w64(cand);
+        __builtin_amdgcn_wave_barrier();
+        if (cand) {
+            const int q = rank_below(bal);
+            store_walk_record<T>(sp_w + q * kWalkWords, pf, ox, oy, (int)(a_s + lane), cs);
+            s_idx[wave][q] = (uint8_t)lane;
+        }
+        if (wave == 0 && lane < nbr) s_slot[buf][lane] = pf_slot;
+        __builtin_amdgcn_wave_barrier();
+        // the batch after the next: pair indices; the next: records
+        a_e = a_s;
+        a_s = b_s;
+        b_s = batch_lo(a_s);
+        if (lane < (int)(a_e - a_s)) load_pair(rec_b);
+        if (lane < (int)(a_s - b_s)) rec_b = pvals[b_s + lane];
+        uint64_t taken = 0ull;
+        uint32_t chunk = 0u;  // lane c < kChunk: the batch record in reduction slot c
+        int jl = __popcll(bal) - 1;
+        T* rows = s_acc[buf][wave];
+        const T* sp = sp_w;
+        T cur[kWPos + 1];
+        T dx = T(0), dy = T(0), a = T(0), pp = T(0), rr = T(0);
+        bool clamped = false;
+        // Advances to the next record (descending) that contributes in the strip.
+        auto next = [&]() -> bool {
+            for (; jl >= 0; --jl) {
+                sp = sp_w + jl * kWalkWords;
+#pragma unroll
+                for (int k = 0; k <= kWPos; ++k) cur[k] = sp[k];
+                const T E = walk_exponent(cur, u, v_px, dx, dy, pp, rr);
+                const T araw = exp2_of<T>(E);
+                clamped = !(araw < cs.alpha_max);
+                const bool contrib = (E >= cur[kWThr]) & (word_to_id<T>(cur[kWPos]) <= b.lastp);
+                a = contrib ? (clamped ? cs.alpha_max : araw) : T(0);
+                if (__builtin_amdgcn_ballot_w64(a != T(0)) != 0ull) return true;
+            }
+            return false;
+        };
+        auto take = [&](auto cidx) {
+            constexpr int C = decltype(cidx)::value;
+            const T roma = fast_rcp<T>(T(1) - a);
+            const T Ti = b.Tcur * roma;
+            const T w = a * Ti;
+            const T vv = blend_grad<T, PROBS>(b, sp, a, dP, (int64_t)view * K, HW, pix, K);
+            const T dalpha = NW == 1 ? fmadd(Ti, vv, -(b.S * roma)) : a != T(0) ? (Ti * vv - b.S * roma) : T(0);
+            b.S = fmadd(w, vv, b.S);
+            b.Tcur = Ti;
+            const T dq = clamped ? T(0) : dalpha * a;  // -2 dL/dQ = o dL/do
+            if constexpr (NW == 1) {  // constant factors where the row is read
+                const T t1 = dq * dx, t2 = dq * dy;
+                v[C * kGradWords + 0] = dq * pp;
+                v[C * kGradWords + 1] = dq * rr;
+                v[C * kGradWords + 2] = t1 * dx;
+                v[C * kGradWords + 3] = t1 * dy;
+                v[C * kGradWords + 4] = t2 * dy;
+            } else {
+                const T dqi = dq * iq, t1 = T(-0.5) * dq * dx, t2 = T(-0.5) * dq * dy;
+                v[C * kGradWords + 0] = dqi * pp;
+                v[C * kGradWords + 1] = dqi * rr;
+                v[C * kGradWords + 2] = t1 * dx;
+                v[C * kGradWords + 3] = -dq * dx * dy;
+                v[C * kGradWords + 4] = t2 * dy;
+            }
+            v[C * kGradWords + 5] = dq;
+            v[C * kGradWords + 6] = b.gc0 * w;
+            v[C * kGradWords + 7] = b.gc1 * w;
+            v[C * kGradWords + 8] = b.gc2 * w;
+            v[C * kGradWords + 9] = b.gd * w;
+            const int r = __builtin_amdgcn_readfirstlane((int)s_idx[wave][jl]);
+            taken |= 1ull << r;
+            chunk = (lane == C) ? (uint32_t)r : chunk;
+            --jl;
+        };
+        for (;;) {
+            if (!next()) break;
+            take(SlotIdx<0>{});
+            if (!next()) { flush_rows<1>(v, chunk, rows); break; }
+            take(SlotIdx<1>{});
+            if (!next()) { flush_rows<2>(v, chunk, rows); break; }
+            take(SlotIdx<2>{});
+            if (!next()) { flush_rows<3>(v, chunk, rows); break; }
+            take(SlotIdx<3>{});
+            if (!next()) { flush_rows<4>(v, chunk, rows); break; }
+            take(SlotIdx<4>{});
+            if (!next()) { flush_rows<5>(v, chunk, rows); break; }
+            take(SlotIdx<5>{});
+            flush_rows<6>(v, chunk, rows);
+        }
+        if (lane == 0) s_taken[buf][wave] = taken;
+        // (with two buffers the other one's readers are a barrier behind)
+        __syncthreads();
+        uint64_t mine[NW], any = 0ull;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            mine[w] = s_taken[buf][w];
+            any |= mine[w];
+        }
+        for (int k = tid; k < kWave * kGradWords; k += TW * TH) {
+            const int r = (k * 6554) >> 16, word = k - r * kGradWords;  // k / 10 for k < 640
+            if (!((any >> r) & 1ull)) continue;
+            T sum = T(0);
+#pragma unroll
+            for (int w = 0; w < NW; ++w) sum += ((mine[w] >> r) & 1ull) ? s_acc[buf][w][k] : T(0);
+            if constexpr (NW == 1)
+                sum *= (word <= 1) ? iq : (word == 2 || word == 4) ? T(-0.5) : (word == 3) ? T(-1) : T(1);
+            const uint32_t slot = s_slot[buf][r];
+            if (slot < cap) {
+                partials[(size_t)slot * kGradWords + word] = sum;
+                if (word == 0) written[slot] = 1;
+            }
+        }
+        if constexpr (kBufs == 1) __syncthreads();
     }
 }
 
@@ -1296,19 +1396,54 @@ static hipError_t fwd_tile(const Frame<T>& f, const dqo_images& img, hipStream_t
     const StatePtrs& s = f.s;
     constexpr int N = Parts<TW, TH>::kCount;
     const unsigned grid = N == 1 ? (unsigned)blocks : (unsigned)((blocks + 7) / 8 * 8 * N);
-    // Boundary states, last positions and the backward's segment list, for a
-    // backward that can run segmented.
-    const bool seg = segmented_backward(s, blocks), probs = img.probs && f.K > 0;
-    const size_t dyn = probs ? (size_t)f.K * kWave * sizeof(T) : 0;
-    auto kern = probs         ? render_forward_kernel<T, TW, TH, true, true>
-                : img.n_blend ? render_forward_kernel<T, TW, TH, false, true>
-                              : render_forward_kernel<T, TW, TH, false, false>;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kWave), dyn, st, f.views, f.consts, f.K, (const T*)s.splats,
-                       s.pair_vals[0], s.ranges, s.schedule, (T*)img.color, (T*)img.depth, (T*)img.t_final, img.last,
-                       (T*)(probs ? img.probs : nullptr), probs ? img.id_map : nullptr, img.target, (T*)img.p_target,
-                       img.n_blend, (uint32_t)s.capacity, (uint32_t)s.items, (T*)(seg ? s.ckpt : nullptr),
-                       (uint32_t)s.ckpt_cap, s.tile_last, s.seg_base, s.seg_list, (uint32_t)s.seg_cap, (uint32_t)s.seg_len,
-                       s.ctrl);
+    // Boundary states, tile ends and the backward's segment list, for a
+    // backward that can run segmented (no instance channels: their sums behind
+    // a boundary would need every object's prefix).
+    const bool seg = segmented_backward(s, blocks) && !img.probs;
+    if (img.probs && f.K > 0) {
+        const size_t dyn = (size_t)f.K * kWave * sizeof(T);
+        hipLaunchKernelGGL((render_forward_kernel<T, TW, TH, true>), dim3(grid), dim3(kWave), dyn, st, f.views,
+                           f.consts, f.K, (const T*)s.splats, s.pair_vals[0], s.ranges, s.schedule, (T*)img.color,
+                           (T*)img.depth, (T*)img.t_final, img.last, (T*)img.probs, img.id_map, img.target,
+                           (T*)img.p_target, img.n_blend, (uint32_t)s.capacity, (uint32_t)s.items,
+                           (T*)(seg ? s.ckpt : nullptr), (uint32_t)s.ckpt_cap, s.tile_last, s.seg_base, s.seg_list,
+                           (uint32_t)s.seg_cap, s.ctrl);
+    } else {
+        auto kern = img.n_blend ? render_forward_kernel<T, TW, TH, false, true> : render_forward_kernel<T, TW, TH, false, false>;
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(kWave), 0, st, f.views,
+                           f.consts, f.K, (const T*)s.splats, s.pair_vals[0], s.ranges, s.schedule, (T*)img.color,
+                           (T*)img.depth, (T*)img.t_final, img.last, (T*)nullptr, (int32_t*)nullptr, img.target,
+                           (T*)img.p_target, img.n_blend, (uint32_t)s.capacity, (uint32_t)s.items,
+                           (T*)(seg ? s.ckpt : nullptr), (uint32_t)s.ckpt_cap, s.tile_last, s.seg_base, s.seg_list,
+                           (uint32_t)s.seg_cap, s.ctrl);
+    }
+    return hipGetLastError();
+}
+
+template <typename T, int TW, int TH, bool PROBS>
+static hipError_t bwd_parts(const Frame<T>& f, const dqo_images& img, const dqo_image_grads& g, hipStream_t st) {
+    const StatePtrs& s = f.s;
+    const int blocks = f.views.n_views * f.views.tiles_per_view;
+    constexpr int N = Parts<TW, TH>::kCount;
+    const bool suf = suffix_backward(s);
+    if (suf) {
+        const unsigned grid = N == 1 ? (unsigned)blocks : (unsigned)((blocks + 7) / 8 * 8 * N);
+        hipLaunchKernelGGL((suffix_state_kernel<T, TW, TH, PROBS>), dim3(grid), dim3(kWave),
+                           PROBS ? (size_t)f.K * kWave * sizeof(T) : 0, st, f.views, f.consts,
+                           f.K, (const T*)s.splats, s.pair_vals[0], s.ranges, s.schedule, (const T*)img.t_final,
+                           img.last, img.target, (const T*)g.d_color, (const T*)g.d_depth, (const T*)g.d_t_final,
+                           (const T*)g.d_probs, (const T*)g.d_p_target, (uint32_t)s.capacity, (uint32_t)s.items,
+                           s.seg_base, s.suf_list, (uint32_t)s.seg_cap, (T*)s.suffix, (uint32_t)s.suf_cap, s.tile_last);
+    }
+    const int64_t gq = 8 * DQO_BWD_XCD_CHUNK;  // whole XCD chunks
+    const unsigned grid = suf ? (unsigned)((s.seg_cap + gq - 1) / gq * gq) : (unsigned)blocks;
+    auto kern = suf ? render_backward_tile_kernel<T, TW, TH, PROBS, true>
+                    : render_backward_tile_kernel<T, TW, TH, PROBS, false>;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(TW * TH), 0, st, f.views, f.consts, f.K, (const T*)s.splats,
+                       s.pair_vals[0], s.ranges, s.schedule, (const T*)img.t_final, img.last, img.target,
+                       (const T*)g.d_color, (const T*)g.d_depth, (const T*)g.d_t_final, (const T*)g.d_probs,
+                       (const T*)g.d_p_target, (T*)s.partials, s.written, (uint32_t)s.capacity, (uint32_t)s.items,
+                       s.suf_list, (const T*)s.suffix, (uint32_t)s.suf_cap, s.tile_last, s.ctrl);
     return hipGetLastError();
 }
 
@@ -1317,33 +1452,30 @@ static hipError_t bwd_tile(const Frame<T>& f, const dqo_images& img, const dqo_i
     const int blocks = f.views.n_views * f.views.tiles_per_view;
     if (blocks == 0) return hipSuccess;
     const StatePtrs& s = f.s;
-    // Segments of the pair ranges, each restarted from the forward's boundary
-    // states; with instance-channel gradients after a pass that sums every
-    // segment's share of the pixels' suffix sums.
-    const bool seg = segmented_backward(s, blocks) &&
-                     (g.d_probs || (img.color && img.depth && (img.p_target || !g.d_p_target)));
-    // units: the segments, at most tiles + pairs / segment length = seg_cap
-    const int64_t gq = 8 * std::max(1, DQO_BWD_XCD_CHUNK);  // whole XCD chunks
-    const unsigned grid = seg ? (unsigned)((std::max<int64_t>(s.seg_cap, blocks) + gq - 1) / gq * gq)
-                              : (unsigned)blocks;
-    if (seg && g.d_probs)
-        hipLaunchKernelGGL((segment_sums_kernel<T, TW, TH>), dim3(grid * Parts<TW, TH>::kCount), dim3(kWave), 0, st, f.views, f.consts, f.K,
-                           (const T*)s.splats, s.pair_vals[0], s.ranges, img.last, img.target, (const T*)g.d_color,
-                           (const T*)g.d_depth, (const T*)g.d_probs, (const T*)g.d_p_target, (uint32_t)s.capacity,
-                           (uint32_t)s.items, s.seg_list, (const T*)s.ckpt, (uint32_t)s.ckpt_cap, s.tile_last,
-                           (uint32_t)s.seg_len, (T*)s.seg_sums, s.ctrl);
-    auto kern = g.d_probs ? (seg ? render_backward_wave_kernel<T, TW, TH, true, true>
-                                 : render_backward_wave_kernel<T, TW, TH, true, false>)
-                          : (seg ? render_backward_wave_kernel<T, TW, TH, false, true>
-                                 : render_backward_wave_kernel<T, TW, TH, false, false>);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kWave), 0, st, f.views, f.consts, f.K, (const T*)s.splats,
-                       s.pair_vals[0], s.ranges, s.schedule, (const T*)img.t_final, img.last, img.target,
-                       (const T*)g.d_color, (const T*)g.d_depth, (const T*)g.d_t_final, (const T*)g.d_probs,
-                       (const T*)g.d_p_target, (T*)s.partials, s.written, (uint32_t)s.capacity,
-                       (uint32_t)s.items, seg ? s.seg_list : nullptr, (const T*)s.ckpt, (uint32_t)s.ckpt_cap,
-                       (const T*)img.color, (const T*)img.depth, (const T*)img.p_target, (const T*)s.seg_sums,
-                       s.tile_last, (uint32_t)s.seg_len, s.ctrl);
-    return hipGetLastError();
+    if constexpr (TW * TH == kWave) {
+        if (g.d_probs && suffix_backward(s)) return bwd_parts<T, TW, TH, true>(f, img, g, st);
+        // Segments of the pair ranges, each restarted from the forward's
+        // boundary states (stored by a forward without instance channels,
+        // which also built the segment list).
+        const bool seg = segmented_backward(s, blocks) && !img.probs && !g.d_probs && img.color && img.depth &&
+                         (img.p_target || !g.d_p_target);
+        // units = segments up to each tile's end <= tiles + pairs / kSegLen = seg_cap
+        const int64_t gq = 8 * DQO_BWD_XCD_CHUNK;  // whole XCD chunks
+        const unsigned grid = seg ? (unsigned)((std::max<int64_t>(s.seg_cap, blocks) + gq - 1) / gq * gq)
+                                  : (unsigned)blocks;
+        auto kern = g.d_probs ? render_backward_wave_kernel<T, TW, TH, true, false>
+                              : (seg ? render_backward_wave_kernel<T, TW, TH, false, true>
+                                     : render_backward_wave_kernel<T, TW, TH, false, false>);
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(kWave), 0, st, f.views, f.consts, f.K, (const T*)s.splats,
+                           s.pair_vals[0], s.ranges, s.schedule, (const T*)img.t_final, img.last, img.target,
+                           (const T*)g.d_color, (const T*)g.d_depth, (const T*)g.d_t_final, (const T*)g.d_probs,
+                           (const T*)g.d_p_target, (T*)s.partials, s.written, (uint32_t)s.capacity,
+                           (uint32_t)s.items, seg ? s.seg_list : nullptr, (const T*)s.ckpt, (uint32_t)s.ckpt_cap,
+                           (const T*)img.color, (const T*)img.depth, (const T*)img.p_target, s.ctrl);
+        return hipGetLastError();
+    } else {
+        return g.d_probs ? bwd_parts<T, TW, TH, true>(f, img, g, st) : bwd_parts<T, TW, TH, false>(f, img, g, st);
+    }
 }
 
 template <typename T>

@@ -229,7 +229,7 @@ constexpr int kSchedBins = 4096;
 constexpr int kSchedRegs = 8;
 __global__ __launch_bounds__(kSchedThreads) void tile_schedule_kernel(const uint32_t* __restrict__ ranges,
                                                                      int tiles, uint32_t* __restrict__ schedule,
-                                                                     uint32_t seg_len, uint32_t* __restrict__ seg_base,
+                                                                     int seg, uint32_t* __restrict__ seg_base,
                                                                      Ctrl* __restrict__ ctrl) {
     __shared__ uint32_t s_cnt[kSchedBins];  // bin b holds count kSchedBins - 1 - b (descending order)
     // segmented backward: the segments of each bin's tiles, then the bin's
@@ -257,7 +257,7 @@ __global__ __launch_bounds__(kSchedThreads) void tile_schedule_kernel(const uint
     __syncthreads();
     auto count = [&](uint32_t wt) {
         atomicAdd(&s_cnt[bin_of_w(wt)], 1u);
-        if (seg_len) atomicAdd(&s_seg[bin_of_w(wt)], tile_segments(wt, seg_len));
+        if (seg) atomicAdd(&s_seg[bin_of_w(wt)], tile_segments(wt));
     };
     if (regs) {
 #pragma unroll
@@ -276,7 +276,7 @@ __global__ __launch_bounds__(kSchedThreads) void tile_schedule_kernel(const uint
         gsum += g[k];
     }
     uint32_t off = block_exclusive_scan<kSchedThreads>(sum, s_tmp);
-    uint32_t goff = seg_len ? block_exclusive_scan<kSchedThreads>(gsum, s_tmp) : 0u;
+    uint32_t goff = seg ? block_exclusive_scan<kSchedThreads>(gsum, s_tmp) : 0u;
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
         s_cnt[tid * kPer + k] = off;
@@ -284,13 +284,14 @@ __global__ __launch_bounds__(kSchedThreads) void tile_schedule_kernel(const uint
         off += c[k];
         goff += g[k];
     }
-    // The backward's segment list holds every segment of every tile, tiles by bin (heaviest first); the forward fills in each tile's entries
+    // The backward's segment list holds every 64-pair segment of every tile,
+    // tiles by bin (heaviest first); the forward fills in each tile's entries
     // once it knows how far its pixels blend (the rest it marks empty).
-    if (seg_len && tid == kSchedThreads - 1) ctrl->counters[kCounterSegTotal] = goff;
+    if (seg && tid == kSchedThreads - 1) ctrl->counters[kCounterSegTotal] = goff;
     __syncthreads();
     auto place = [&](int t, uint32_t wt) {
         schedule[atomicAdd(&s_cnt[bin_of_w(wt)], 1u)] = (uint32_t)t;
-        if (seg_len) seg_base[t] = atomicAdd(&s_seg[bin_of_w(wt)], tile_segments(wt, seg_len));
+        if (seg) seg_base[t] = atomicAdd(&s_seg[bin_of_w(wt)], tile_segments(wt));
     };
     if (regs) {
 #pragma unroll
@@ -551,7 +552,7 @@ hipError_t launch_pair_sort(const StatePtrs& s, int tiles_total, hipStream_t st)
         hipLaunchKernelGGL(tile_bounds_kernel, dim3(grid), dim3(256), 0, st, s.pair_keys[0], n_dev, cap, s.ranges,
                            (uint32_t*)s.written);
         hipLaunchKernelGGL(tile_schedule_kernel, dim3(1), dim3(kSchedThreads), 0, st, s.ranges, tiles_total,
-                           s.schedule, segmented_backward(s, tiles_total) ? (uint32_t)s.seg_len : 0u, s.seg_base, s.ctrl);
+                           s.schedule, segmented_backward(s, tiles_total) || suffix_backward(s) ? 1 : 0, s.seg_base, s.ctrl);
         if (s.tile_sort)
             hipLaunchKernelGGL(tile_sort_kernel, dim3((unsigned)tiles_total), dim3(kTileSortThreads), 0, st, s.ranges,
                                s.schedule, s.depth_keys[0], (uint32_t)s.items, cap, (uint32_t)s.tile_sort_lds,

@@ -1,9 +1,8 @@
 """GPU: tiles of one to four 64-pixel parts.  Every tile shape renders the
-8x8 images (ragged sizes, windows), and the segmented backward (64-pair
-segments where the tiles are few, longer ones up to 8192 tiles, none above)
-agrees with the whole-tile walk of the same images and with the 8x8 gradients,
-with and without instance-channel gradients.  The walks differ in FP32 summing
-order and restart sums only: the parity tolerance."""
+8x8 images (ragged sizes, windows), and the gradients agree with the 8x8 ones
+with and without instance channels, where the backward runs through the suffix
+pass (up to 8192 parts; ranges of many segments) and where it walks whole
+tiles.  The shapes differ in FP32 summing order only: the parity tolerance."""
 import numpy as np
 import pytest
 import torch
@@ -35,10 +34,11 @@ def _upstream(V, H, W, K, probs):
     return up
 
 
-# 128x96 at 30k Gaussians: ranges of many segments; 2 views of 512x384 and up:
-# more tiles than the fine segments take (8x32 and 16x16 stay below)
+# 128x96 at 30k Gaussians: ranges of many segments; 515x389: 3,185 parts a view,
+# three views are above the suffix pass's limit; windows leave parts empty
 @pytest.mark.parametrize("probs", [False, True])
-@pytest.mark.parametrize("n,W,H,V,windows", [(30000, 125, 91, 1, [(3, 5, 120, 91)]), (20000, 515, 389, 2, None)])
+@pytest.mark.parametrize("n,W,H,V,windows", [(30000, 125, 91, 1, [(3, 5, 120, 91)]), (20000, 515, 389, 2, None),
+                                             (6000, 515, 389, 3, None)])
 def test_tile_shapes_agree(n, W, H, V, windows, probs):
     K = 5
     ref = None
@@ -46,20 +46,25 @@ def test_tile_shapes_agree(n, W, H, V, windows, probs):
     for tile in TILES:
         r, p, ids = _setup(n, W, H, V, K, tile, windows)
         img = r.forward(p, ids, probs=probs)
-        g_seg = r.backward(p, img, up).clone()
-        tiles = r.frame.layout.tiles_x * r.frame.layout.tiles_y * V
-        assert tiles <= 8192
-        # another forward's stamp: the backward of img then walks whole tiles
-        other = r.frame.new_images(probs=probs)
-        r.frame.render_forward(other)
-        g_whole = r.backward(p, img, up)
-        close(g_seg.cpu().numpy(), g_whole.cpu().numpy(), GRAD_RTOL, what=f"{tile} segmented against whole")
+        g = r.backward(p, img, up)
+        assert torch.equal(g, r.backward(p, img, up)), tile   # deterministic, nothing left behind
         if ref is None:
-            ref = img, g_seg
+            ref = img, g
         # (a splat's mean is rounded relative to its tile's corner, so shapes agree to rounding)
         for k in ("color", "depth", "t_final") + (("probs",) if probs else ()):
             close(img[k].cpu().numpy(), ref[0][k].cpu().numpy(), FWD_RTOL, what=f"{tile} {k}")
-        close(g_seg.cpu().numpy(), ref[1].cpu().numpy(), GRAD_RTOL, what=f"{tile} against 8x8")
+        close(g.cpu().numpy(), ref[1].cpu().numpy(), GRAD_RTOL, what=f"{tile} against 8x8")
+
+
+def test_channel_gradients_leave_the_stored_states():
+    """A backward with instance-channel gradients (the suffix pass) between a
+    forward and its plain segmented backward changes nothing of the latter."""
+    r, p, ids = _setup(30000, 128, 96, 1, 5, (8, 8))
+    img = r.forward(p, ids)
+    up, up_p = _upstream(1, 96, 128, 5, False), _upstream(1, 96, 128, 5, True)
+    before = r.backward(p, img, up)
+    r.backward(p, img, up_p)
+    assert torch.equal(before, r.backward(p, img, up))
 
 
 def test_marked_pairs_contribute_nowhere():
