@@ -5,8 +5,8 @@
 // per-crop fallback decision and a masked PSNR.
 //
 // Activations are NHWC BF16 with the channel count padded to a multiple of
-// 16.  A convolution workgroup (4 waves) owns a 16 x 16 pixel tile of one
-// image for every output channel: the 18 x 18 input halo and the layer's
+// 16.  A convolution workgroup (4 waves) computes one 16 x 16 pixel tile after
+// another, every output channel: the 18 x 18 input halo and the layer's
 // weights [cout][9][cin] are staged in LDS (16-byte padded rows), and wave w
 // computes tile rows 4w..4w+3 (four M-blocks of 16 pixels) against all
 // output-channel N-blocks, the K loop running over the 9 taps x cin.
@@ -15,6 +15,9 @@
 // from transposed LDS copies of the activation window and the output
 // gradient (transposed in registers, 8x8 blocks of 16-bit values); a second
 // kernel sums the splits in a fixed order.
+#include <algorithm>
+#include <type_traits>
+
 #include "dqo_device.hpp"
 #include "dqo_learned.h"
 #include "net.hpp"
@@ -37,13 +40,35 @@ __device__ __forceinline__ bool valid_px(const float* rgbdm, int64_t plane, int6
     return rgbdm[base + 4 * plane] > 0.5f && rgbdm[base + 3 * plane] > 0.0f;
 }
 
+// Two floats to BF16 (round to nearest even), the first in the low half.
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t f2bf_pair(float lo, float hi) {
+    const bf16x2_t h = __builtin_convertvector(floatx2{lo, hi}, bf16x2_t);
+    uint32_t u;
+    __builtin_memcpy(&u, &h, 4);
+    return u;
+}
+
 constexpr int kT = 16;       // output tile edge (pixels)
 constexpr int kHalo = kT + 2;
 
 enum { kEpiRelu = 0, kEpiGate = 1, kEpiOut = 2 };
 
+// A workgroup stages the layer's weights once and walks a run of consecutive
+// tiles (neighbours along an image row share their halo in L2): the next
+// tile's input is in flight in registers while the matrix cores work on the
+// current one from LDS.  The weights are the left operand, so a lane ends with
+// consecutive channels of a pixel and stores (and gates) 16 bytes at a time.
+// At 64 to 64 channels the weights and the input take 121 KB of LDS, so one
+// workgroup of four waves has a CU to itself and nothing else hides its loads.
+// For 32 crops of 128x128, one tile per workgroup with the weights staged
+// every time and 2-byte stores took 101 us (gated: 111 us), 0.38 PFLOP/s; now
+// 56 (59) us, 0.69 PFLOP/s, where the traffic of 134 MB (201 MB) takes 27
+// (40) us at the copy rate.  Through LDS to 16-byte stores instead: 58 (85).
 template <int CIN, int COUT, int EPI>
-__global__ __launch_bounds__(256) void conv3x3_kernel(int H, int W, const uint16_t* __restrict__ in,
+__global__ __launch_bounds__(256) void conv3x3_kernel(int H, int W, int n_tiles, int run,
+                                                      const uint16_t* __restrict__ in,
                                                       const uint16_t* __restrict__ wk, const float* __restrict__ bias,
                                                       const uint16_t* __restrict__ gate, uint16_t* __restrict__ out_bf,
                                                       float* __restrict__ out_f, int nout) {
@@ -54,96 +79,141 @@ __global__ __launch_bounds__(256) void conv3x3_kernel(int H, int W, const uint16
     static_assert(CIN % 16 == 0 && COUT % 16 == 0, "channels must be multiples of 16");
     __shared__ __attribute__((aligned(16))) uint16_t s_in[kHalo * kHalo * PIX];
     __shared__ __attribute__((aligned(16))) uint16_t s_w[COUT * WROW];
-    const int tiles_x = W / kT, tiles_y = H / kT;
-    const int img = blockIdx.x / (tiles_x * tiles_y);
-    const int t = blockIdx.x - img * tiles_x * tiles_y;
-    const int ty0 = (t / tiles_x) * kT, tx0 = (t % tiles_x) * kT;
+    const int tiles_x = W / kT, tiles_img = tiles_x * (H / kT);
     const int tid = threadIdx.x;
+    const int t0 = (int)blockIdx.x * run, t1 = min(n_tiles, t0 + run);
+    // this thread's 16-byte pieces of a tile's input: channels c8 of halo pixels
+    // tid / CCH, + 256 / CCH, ...
+    constexpr int CCH = CIN / 8, kPieces = (kHalo * kHalo * CCH + 255) / 256;
+    static_assert(256 % CCH == 0, "a thread keeps its channels");
+    const int c8 = tid % CCH, pix0 = tid / CCH;
+    uint4 pre[kPieces];
+    auto load_tile = [&](int tile) {
+        const int img = tile / tiles_img, t = tile - img * tiles_img;
+        const int ty0 = (t / tiles_x) * kT, tx0 = (t % tiles_x) * kT;
+        const uint16_t* base = in + (size_t)img * H * W * CIN + c8 * 8;
+#pragma unroll
+        for (int k = 0; k < kPieces; ++k) {
+            const int pix = pix0 + k * (256 / CCH);
+            const int hy = pix / kHalo, hx = pix - hy * kHalo;
+            const int y = ty0 + hy - 1, x = tx0 + hx - 1;
+            pre[k] = make_uint4(0u, 0u, 0u, 0u);
+            if (pix < kHalo * kHalo && (uint32_t)y < (uint32_t)H && (uint32_t)x < (uint32_t)W)
+                pre[k] = *reinterpret_cast<const uint4*>(base + ((size_t)y * W + x) * CIN);
+        }
+    };
+    if (t0 < t1) load_tile(t0);
     constexpr int WCH = 9 * CIN / 8;
     for (int c = tid; c < COUT * WCH; c += 256) {
         const int co = c / WCH, k8 = c - co * WCH;
-        *reinterpret_cast<uint4*>(s_w + co * WROW + k8 * 8) =
+        // channel 4 NT g + 4 n + r is row 4 g + r of the n-th product, so a lane
+        // ends with 4 NT consecutive channels (kEpiOut keeps the order)
+        const int row = EPI == kEpiOut ? co : (co / 4 % NT) * 16 + (co / (4 * NT)) * 4 + co % 4;
+        *reinterpret_cast<uint4*>(s_w + row * WROW + k8 * 8) =
             *reinterpret_cast<const uint4*>(wk + (size_t)co * 9 * CIN + k8 * 8);
     }
-    constexpr int CCH = CIN / 8;
-    for (int c = tid; c < kHalo * kHalo * CCH; c += 256) {
-        const int pix = c / CCH, c8 = c - pix * CCH;
-        const int hy = pix / kHalo, hx = pix - hy * kHalo;
-        const int y = ty0 + hy - 1, x = tx0 + hx - 1;
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (y >= 0 && y < H && x >= 0 && x < W)
-            v = *reinterpret_cast<const uint4*>(in + (((size_t)img * H + y) * W + x) * CIN + c8 * 8);
-        *reinterpret_cast<uint4*>(s_in + pix * PIX + c8 * 8) = v;
-    }
-    __syncthreads();
     const int lane = tid & 63, wave = tid >> 6;
     const int lr = lane & 15, lg = lane >> 4;
-    floatx4 acc[4][NT];
+    for (int tile = t0; tile < t1; ++tile) {
+        const int img = tile / tiles_img, t = tile - img * tiles_img;
+        const int ty0 = (t / tiles_x) * kT, tx0 = (t % tiles_x) * kT;
 #pragma unroll
-    for (int m = 0; m < 4; ++m)
-#pragma unroll
-        for (int n = 0; n < NT; ++n) acc[m][n] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-    for (int tap = 0; tap < 9; ++tap) {
-        const int dy = tap / 3, dx = tap - 3 * dy;
-#pragma unroll
-        for (int kc = 0; kc < CIN; kc += KS) {
-            if constexpr (KS == 32) {
-                bf16x8_t a[4], b[NT];
-#pragma unroll
-                for (int m = 0; m < 4; ++m)
-                    a[m] = *reinterpret_cast<const bf16x8_t*>(s_in + ((wave * 4 + m + dy) * kHalo + lr + dx) * PIX +
-                                                              kc + 8 * lg);
-#pragma unroll
-                for (int n = 0; n < NT; ++n)
-                    b[n] = *reinterpret_cast<const bf16x8_t*>(s_w + (n * 16 + lr) * WROW + tap * CIN + kc + 8 * lg);
-#pragma unroll
-                for (int m = 0; m < 4; ++m)
-#pragma unroll
-                    for (int n = 0; n < NT; ++n)
-                        acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], b[n], acc[m][n], 0, 0, 0);
-            } else {
-                short4_t a[4], b[NT];
-#pragma unroll
-                for (int m = 0; m < 4; ++m)
-                    a[m] = *reinterpret_cast<const short4_t*>(s_in + ((wave * 4 + m + dy) * kHalo + lr + dx) * PIX +
-                                                              kc + 4 * lg);
-#pragma unroll
-                for (int n = 0; n < NT; ++n)
-                    b[n] = *reinterpret_cast<const short4_t*>(s_w + (n * 16 + lr) * WROW + tap * CIN + kc + 4 * lg);
-#pragma unroll
-                for (int m = 0; m < 4; ++m)
-#pragma unroll
-                    for (int n = 0; n < NT; ++n)
-                        acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[m], b[n], acc[m][n], 0, 0, 0);
-            }
+        for (int k = 0; k < kPieces; ++k) {
+            const int pix = pix0 + k * (256 / CCH);
+            if (pix < kHalo * kHalo) *reinterpret_cast<uint4*>(s_in + pix * PIX + c8 * 8) = pre[k];
         }
-    }
-    // acc[m][n][r] = output at pixel (row 4 wave + m, column 4 lg + r), channel 16 n + lr
+        __syncthreads();
+        // outputs of a lane: pixel (row 4 wave + m, column lr), channels 4 NT lg + 0 ..
+        const size_t o0 = (((size_t)img * H + ty0 + wave * 4) * W + tx0 + lr) * COUT + 4 * NT * lg;
+        uint4 gt[EPI == kEpiGate ? 4 : 1][EPI == kEpiGate ? NT / 2 : 1];
+        if constexpr (EPI == kEpiGate) {
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
-        const int y = ty0 + wave * 4 + m;
-        const int x0 = tx0 + 4 * lg;
+            for (int m = 0; m < 4; ++m)
 #pragma unroll
-        for (int n = 0; n < NT; ++n) {
-            const int co = n * 16 + lr;
-            if constexpr (EPI == kEpiOut) {
-                if (co < nout) {
-                    const float b0 = bias[co];
-                    float4 v = make_float4(acc[m][n][0] + b0, acc[m][n][1] + b0, acc[m][n][2] + b0, acc[m][n][3] + b0);
-                    *reinterpret_cast<float4*>(out_f + (((size_t)img * nout + co) * H + y) * W + x0) = v;
+                for (int q = 0; q < NT / 2; ++q)
+                    gt[m][q] = *reinterpret_cast<const uint4*>(gate + o0 + (size_t)m * W * COUT + q * 8);
+        }
+        if (tile + 1 < t1) load_tile(tile + 1);
+        floatx4 acc[4][NT];
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+#pragma unroll
+            for (int n = 0; n < NT; ++n) acc[m][n] = floatx4{0.f, 0.f, 0.f, 0.f};
+        // Steps of KS input channels of one tap, in tap order; the operands of
+        // the next step are read from LDS while the matrix cores take this
+        // one's (one wave per SIMD: nothing else would hide the reads).
+        typedef typename std::conditional<KS == 32, bf16x8_t, short4_t>::type frag_t;
+        constexpr int kSteps = 9 * (CIN / KS), kLane = KS / 4;
+        frag_t fa[2][4], fb[2][NT];
+        auto read_step = [&](int st, frag_t(&a)[4], frag_t(&b)[NT]) {
+            const int tap = st / (CIN / KS), kc = (st - tap * (CIN / KS)) * KS, dy = tap / 3, dx = tap - 3 * dy;
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+                a[m] = *reinterpret_cast<const frag_t*>(s_in + ((wave * 4 + m + dy) * kHalo + lr + dx) * PIX + kc +
+                                                        kLane * lg);
+#pragma unroll
+            for (int n = 0; n < NT; ++n)
+                b[n] = *reinterpret_cast<const frag_t*>(s_w + (n * 16 + lr) * WROW + tap * CIN + kc + kLane * lg);
+        };
+        read_step(0, fa[0], fb[0]);
+#pragma unroll
+        for (int st = 0; st < kSteps; ++st) {
+            if (st + 1 < kSteps) read_step(st + 1, fa[(st + 1) & 1], fb[(st + 1) & 1]);
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+#pragma unroll
+                for (int n = 0; n < NT; ++n) {
+                    // (kEpiOut, planar FP32, wants pixels in a lane's registers: the input on the left)
+                    const frag_t l = EPI == kEpiOut ? fa[st & 1][m] : fb[st & 1][n];
+                    const frag_t r = EPI == kEpiOut ? fb[st & 1][n] : fa[st & 1][m];
+                    if constexpr (KS == 32)
+                        acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(l, r, acc[m][n], 0, 0, 0);
+                    else
+                        acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(l, r, acc[m][n], 0, 0, 0);
                 }
-            } else {
+        }
+        __syncthreads();  // the input is read; its LDS takes the next one
+        if constexpr (EPI == kEpiOut) {
+            // acc[m][n][r] = output at pixel (row 4 wave + m, column 4 lg + r), channel 16 n + lr
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const size_t o = (((size_t)img * H + y) * W + x0 + r) * COUT + co;
-                    float v;
-                    if constexpr (EPI == kEpiRelu) {
-                        v = fmaxf(acc[m][n][r] + bias[co], 0.0f);
-                    } else {
-                        v = bf2f(gate[o]) > 0.0f ? acc[m][n][r] : 0.0f;
+            for (int m = 0; m < 4; ++m) {
+                const int y = ty0 + wave * 4 + m;
+                const int x0 = tx0 + 4 * lg;
+#pragma unroll
+                for (int n = 0; n < NT; ++n) {
+                    const int co = n * 16 + lr;
+                    if (co < nout) {
+                        const float b0 = bias[co];
+                        float4 v = make_float4(acc[m][n][0] + b0, acc[m][n][1] + b0, acc[m][n][2] + b0,
+                                               acc[m][n][3] + b0);
+                        *reinterpret_cast<float4*>(out_f + (((size_t)img * nout + co) * H + y) * W + x0) = v;
                     }
-                    out_bf[o] = f2bf(v);
+                }
+            }
+        } else {
+            static_assert(NT % 2 == 0, "16-byte stores");
+#pragma unroll
+            for (int q = 0; q < NT / 2; ++q) {
+                float bv[8];
+                if constexpr (EPI == kEpiRelu)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) bv[e] = bias[4 * NT * lg + q * 8 + e];
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    uint32_t o[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float lo = acc[m][2 * q + e / 2][e % 2 * 2], hi = acc[m][2 * q + e / 2][e % 2 * 2 + 1];
+                        if constexpr (EPI == kEpiRelu) {
+                            o[e] = f2bf_pair(fmaxf(lo + bv[2 * e], 0.0f), fmaxf(hi + bv[2 * e + 1], 0.0f));
+                        } else {  // zero where the gate (a ReLU output) is not positive
+                            const uint32_t gw = e == 0 ? gt[m][q].x : e == 1 ? gt[m][q].y : e == 2 ? gt[m][q].z : gt[m][q].w;
+                            o[e] = f2bf_pair(bf2f((uint16_t)gw) > 0.0f ? lo : 0.0f,
+                                             bf2f((uint16_t)(gw >> 16)) > 0.0f ? hi : 0.0f);
+                        }
+                    }
+                    *reinterpret_cast<uint4*>(out_bf + o0 + (size_t)m * W * COUT + q * 8) =
+                        make_uint4(o[0], o[1], o[2], o[3]);
                 }
             }
         }
@@ -568,9 +638,13 @@ __global__ __launch_bounds__(kCropThreads) void psnr_kernel(int HW, const float*
 template <int CIN, int COUT, int EPI>
 static void conv(int B, int H, int W, const uint16_t* in, const uint16_t* wk, const float* bias, const uint16_t* gate,
                  uint16_t* out_bf, float* out_f, int nout, hipStream_t st) {
-    const int blocks = B * (H / kT) * (W / kT);
-    hipLaunchKernelGGL((conv3x3_kernel<CIN, COUT, EPI>), dim3(blocks), dim3(256), 0, st, H, W, in, wk, bias, gate,
-                       out_bf, out_f, nout);
+    const int n_tiles = B * (H / kT) * (W / kT);
+    // as many workgroups as the device holds at once, the tiles dealt to them
+    // in equal runs (one tile each while there are fewer tiles)
+    const int resident = std::max(256, resident_blocks<conv3x3_kernel<CIN, COUT, EPI>, 256>());
+    const int run = (n_tiles + resident - 1) / resident;
+    hipLaunchKernelGGL((conv3x3_kernel<CIN, COUT, EPI>), dim3((unsigned)((n_tiles + run - 1) / run)), dim3(256), 0, st,
+                       H, W, n_tiles, run, in, wk, bias, gate, out_bf, out_f, nout);
 }
 
 template <int CIN, int COUT>
