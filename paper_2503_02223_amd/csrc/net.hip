@@ -10,11 +10,10 @@
 // weights [cout][9][cin] are staged in LDS (16-byte padded rows), and wave w
 // computes tile rows 4w..4w+3 (four M-blocks of 16 pixels) against all
 // output-channel N-blocks, the K loop running over the 9 taps x cin.
-// Weight gradients are GEMMs over pixels: one workgroup per (pixel split,
-// tap column) accumulates the three taps' dW_tap[cout][cin] over its tiles
-// from transposed LDS copies of the activation window and the output
-// gradient (transposed in registers, 8x8 blocks of 16-bit values); a second
-// kernel sums the splits in a fixed order.
+// Weight gradients are GEMMs over pixels: one workgroup per (pixel split, block
+// of channels) accumulates the nine taps' dW_tap[cout][cin] over its tiles from
+// LDS copies of the activation window and the output gradient, transposed by
+// the LDS reads; a second kernel sums the splits in a fixed order.
 #include <algorithm>
 #include <type_traits>
 
@@ -220,120 +219,209 @@ __global__ __launch_bounds__(256) void conv3x3_kernel(int H, int W, int n_tiles,
     }
 }
 
-// Stages C channels of ROWS x 16 pixels (row-major; image rows y0..,
-// columns x0..x0+15) into LDS transposed, channel-major rows of KP elements,
-// from NHWC BF16 (zero outside the image).  Each thread takes a block of 8
-// consecutive pixels (half a row) x 8 channels: 8 16-byte loads, an 8x8
-// transpose of the 16-bit values in registers (v_perm_b32), and 8 16-byte
-// stores, one per channel.  Consecutive lanes take consecutive pixel groups,
-// so 16 lanes' stores cover the 64 LDS banks once.
-template <int C, int KP, int ROWS>
-__device__ __forceinline__ void stage_transposed(uint16_t* __restrict__ s, const uint16_t* __restrict__ src, int img,
-                                                 int H, int W, int y0, int x0, int tid) {
-    constexpr int PG = ROWS * kT / 8;  // pixel groups
-    constexpr int NB = PG * (C / 8);
-    for (int b = tid; b < NB; b += 256) {
-        const int pg = b % PG, cg = b / PG;
-        const int px0 = pg * 8;
-        const int y = y0 + px0 / kT, xb = x0 + px0 % kT;
-        uint4 r[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int x = xb + k;
-            r[k] = make_uint4(0u, 0u, 0u, 0u);
-            if (y >= 0 && y < H && x >= 0 && x < W)
-                r[k] = *reinterpret_cast<const uint4*>(src + (((size_t)img * H + y) * W + x) * C + cg * 8);
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            // channel cg*8 + j: dword d of pixel k holds channels 2d (low half) and 2d+1
-            const uint32_t sel = (j & 1) ? 0x07060302u : 0x05040100u;
-            uint32_t o[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const uint4 lo = r[2 * e], hi = r[2 * e + 1];
-                const uint32_t a = (j >> 1) == 0 ? lo.x : (j >> 1) == 1 ? lo.y : (j >> 1) == 2 ? lo.z : lo.w;
-                const uint32_t c = (j >> 1) == 0 ? hi.x : (j >> 1) == 1 ? hi.y : (j >> 1) == 2 ? hi.z : hi.w;
-                o[e] = __builtin_amdgcn_perm(c, a, sel);  // pixels 2e (low half) and 2e+1
-            }
-            *reinterpret_cast<uint4*>(s + (cg * 8 + j) * KP + px0) = make_uint4(o[0], o[1], o[2], o[3]);
-        }
-    }
+// Partial weight gradients over one pixel split, of output channels
+// co0 .. co0 + CO_B and input channels ci0 .. ci0 + CI_B (blockIdx.y), all taps:
+// part[split][co][tap][ci] = sum over the split's pixels p of g[p][co] * act[p + (dy, dx)][ci],
+// part_b[split][co] = sum_p g[p][co].
+// Both operands are wanted with pixels along a lane's registers, but lie with
+// channels first.  A tile's output gradient and activations (18 x 18, with the
+// halo) are staged as they lie, in planes of 16 channels, and ds_read_tr16_b64
+// transposes them on the way to the matrix cores, so that one staged copy
+// serves the nine taps (a column shift is a pixel's address, where a
+// transposed copy would need one copy for each).  Within a row, pixels 8 and
+// on lie 4 places further: the 8 pixels that half a wavefront reads, x .. x + 3
+// and x + 8 .. x + 11, then cover the 64 banks once.  A wave takes one block
+// of 16 input channels, MW blocks of 16 output channels and DXW columns of
+// taps; activation rows stay in registers for the next step, two rows on.  The
+// last wave sums the output gradient, pixel by pixel in order.  The next
+// tile is in flight in registers meanwhile.
+// Bound by the loads of one workgroup per CU (43 of the 62 us at 64 to 64
+// channels are left without the products and sums, 237 MB at 5.5 TB/s; the
+// activations are read for each half of the output channels), then by the
+// serial sum (7 to 12 us).  For 32 crops of 128x128, three workgroups per
+// split (one for each column of taps) that staged transposed copies took 109
+// us at 64 to 64 channels (32 to 64: 85, 64 to 16: 89, 16 to 32: 71); now 62
+// (46, 39, 32).
+template <int CIN, int COUT>
+struct WgradCfg;
+template <>
+struct WgradCfg<64, 64> { static constexpr int CI_B = 64, CO_B = 32, MW = 2, DXW = 3; };
+template <>
+struct WgradCfg<32, 64> { static constexpr int CI_B = 32, CO_B = 32, MW = 1, DXW = 3; };
+template <>
+struct WgradCfg<64, 16> { static constexpr int CI_B = 32, CO_B = 16, MW = 1, DXW = 1; };
+template <>
+struct WgradCfg<16, 32> { static constexpr int CI_B = 16, CO_B = 16, MW = 1, DXW = 1; };
+
+template <int CIN, int COUT>
+constexpr int wgrad_waves() {
+    using C = WgradCfg<CIN, COUT>;
+    return (C::CI_B / 16) * (C::CO_B / 16 / C::MW) * (3 / C::DXW);
 }
 
-// Partial weight gradients of the three taps (dy, dx), dy = -1, 0, 1, of one
-// column dx = blockIdx.y - 1, over one pixel split:
-// part[split][co][tap][ci] = sum over the split's pixels p of g[p][co] * act[p + (dy, dx)][ci],
-// part_b[split][co] = sum_p g[p][co] (written by the centre-column workgroups).
-// Per tile the output gradient is staged once and the activations once, as
-// 18 rows (the tile's rows -1..16 shifted by dx), so a tap's operand is that
-// copy offset by dy rows; a wave's A operand serves its three taps.
+typedef __attribute__((address_space(3))) short4_t lds_short4_t;
+
+// 8 consecutive pixels of one channel per lane, from two transposing reads.
+__device__ __forceinline__ bf16x8_t read_tr(const uint16_t* lo, const uint16_t* hi) {
+    const short4_t a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_t*)lo);
+    const short4_t b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_t*)hi);
+    bf16x8_t v;
+    __builtin_memcpy(&v, &a, 8);
+    __builtin_memcpy(reinterpret_cast<char*>(&v) + 8, &b, 8);
+    return v;
+}
+
 template <int CIN, int COUT>
-__global__ __launch_bounds__(256) void conv3x3_wgrad_kernel(int H, int W, int n_tiles, int tiles_per_split,
-                                                            const uint16_t* __restrict__ act,
-                                                            const uint16_t* __restrict__ g, float* __restrict__ part,
-                                                            float* __restrict__ part_b) {
-    constexpr int KP = kT * kT + 8;        // LDS row of the output gradient (pixels of a tile) + 16-byte pad
-    constexpr int KA = (kT + 2) * kT + 8;  // LDS row of the activations (18 x 16 pixels) + pad
-    constexpr int MT = COUT / 16, NTL = CIN / 16, PAIRS = MT * NTL, PER_WAVE = (PAIRS + 3) / 4;
-    __shared__ __attribute__((aligned(16))) uint16_t s_g[COUT * KP];
-    __shared__ __attribute__((aligned(16))) uint16_t s_a[CIN * KA];
-    const int split = blockIdx.x, dxi = blockIdx.y, dx = dxi - 1;
+__global__ __launch_bounds__((wgrad_waves<CIN, COUT>() + 1) * 64) void conv3x3_wgrad_kernel(
+    int H, int W, int n_tiles, int tiles_per_split, const uint16_t* __restrict__ act, const uint16_t* __restrict__ g,
+    float* __restrict__ part, float* __restrict__ part_b) {
+    using C = WgradCfg<CIN, COUT>;
+    constexpr int CI_B = C::CI_B, CO_B = C::CO_B, MW = C::MW, DXW = C::DXW;
+    constexpr int WAVES = wgrad_waves<CIN, COUT>(), NTHR = (WAVES + 1) * 64;
+    constexpr int NTB = CI_B / 16, MTB = CO_B / 16, MG = MTB / MW;
+    constexpr int AROW = 26 * 16, APLANE = kHalo * AROW;  // activations: 18 rows of 18 pixels
+    constexpr int GROW = 20 * 16, GPLANE = kT * GROW;     // output gradient: 16 rows of 16 pixels
+    __shared__ __attribute__((aligned(16))) uint16_t s_a[NTB * APLANE];
+    __shared__ __attribute__((aligned(16))) uint16_t s_g[MTB * GPLANE];
+    const int split = blockIdx.x;
+    const int co0 = ((int)blockIdx.y % (COUT / CO_B)) * CO_B, ci0 = ((int)blockIdx.y / (COUT / CO_B)) * CI_B;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int lr = lane & 15, lg = lane >> 4;
     const int tiles_x = W / kT, tiles_img = tiles_x * (H / kT);
-    floatx4 acc[PER_WAVE][3];
+    // this thread's 16-byte pieces (8 channels of a pixel) of a tile
+    constexpr int ACH = CI_B / 8, kA = (kHalo * kHalo * ACH + NTHR - 1) / NTHR;
+    constexpr int GCH = CO_B / 8, kG = (kT * kT * GCH + NTHR - 1) / NTHR;
+    static_assert(NTHR % ACH == 0 && NTHR % GCH == 0, "a thread keeps its channels");
+    const int ac = tid % ACH, apix0 = tid / ACH, gc = tid % GCH, gpix0 = tid / GCH;
+    uint4 pa[kA], pg[kG];
+    auto load_tile = [&](int tile) {
+        const int img = tile / tiles_img, t = tile - img * tiles_img;
+        const int ty0 = (t / tiles_x) * kT, tx0 = (t % tiles_x) * kT;
+        const uint16_t* ba = act + (size_t)img * H * W * CIN + ci0 + ac * 8;
+        const uint16_t* bg = g + (((size_t)img * H + ty0) * W + tx0) * COUT + co0 + gc * 8;
 #pragma unroll
-    for (int i = 0; i < PER_WAVE; ++i)
+        for (int k = 0; k < kA; ++k) {
+            const int pix = apix0 + k * (NTHR / ACH), hy = pix / kHalo, hx = pix - hy * kHalo;
+            const int y = ty0 + hy - 1, x = tx0 + hx - 1;
+            pa[k] = make_uint4(0u, 0u, 0u, 0u);
+            if (pix < kHalo * kHalo && (uint32_t)y < (uint32_t)H && (uint32_t)x < (uint32_t)W)
+                pa[k] = *reinterpret_cast<const uint4*>(ba + ((size_t)y * W + x) * CIN);
+        }
 #pragma unroll
-        for (int d = 0; d < 3; ++d) acc[i][d] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int k = 0; k < kG; ++k) {
+            const int pix = gpix0 + k * (NTHR / GCH);
+            pg[k] = make_uint4(0u, 0u, 0u, 0u);
+            if (pix < kT * kT)
+                pg[k] = *reinterpret_cast<const uint4*>(bg + ((size_t)(pix / kT) * W + pix % kT) * COUT);
+        }
+    };
+    // the wave's part, and where its lanes read: a transposing read of 16 lanes
+    // takes 4 pixels x 16 channels, lane i giving pixel i / 4, channels 4 (i % 4) ..
+    const int nt = wave % NTB, mg = wave / NTB % MG, dx0 = wave / (NTB * MG) * DXW;
+    const int cx = 8 * (lg & 1) + (lr >> 2), cc = 4 * (lr & 3);
+    const uint16_t* ra[DXW][2];
+#pragma unroll
+    for (int x = 0; x < DXW; ++x)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int hx = cx + 4 * h + dx0 + x;
+            ra[x][h] = s_a + nt * APLANE + (lg >> 1) * AROW + (hx + 4 * (hx >> 3)) * 16 + cc;
+        }
+    const uint16_t* rg = s_g + mg * MW * GPLANE + (lg >> 1) * GROW + (cx + 4 * (cx >> 3)) * 16 + cc;
+    floatx4 acc[MW][DXW][3];
+#pragma unroll
+    for (int m = 0; m < MW; ++m)
+#pragma unroll
+        for (int x = 0; x < DXW; ++x)
+#pragma unroll
+            for (int d = 0; d < 3; ++d) acc[m][x][d] = floatx4{0.f, 0.f, 0.f, 0.f};
     float bsum = 0.0f;
     const int t_begin = split * tiles_per_split;
     const int t_end = min(n_tiles, t_begin + tiles_per_split);
+    if (t_begin < t_end) load_tile(t_begin);
     for (int t = t_begin; t < t_end; ++t) {
-        const int img = t / tiles_img, tt = t - img * tiles_img;
-        const int ty0 = (tt / tiles_x) * kT, tx0 = (tt % tiles_x) * kT;
-        __syncthreads();
-        stage_transposed<COUT, KP, kT>(s_g, g, img, H, W, ty0, tx0, tid);
-        stage_transposed<CIN, KA, kT + 2>(s_a, act, img, H, W, ty0 - 1, tx0 + dx, tid);
-        __syncthreads();
-#pragma unroll 2
-        for (int k0 = 0; k0 < kT * kT; k0 += 32) {
+        if (t != t_begin) __syncthreads();  // the previous tile is read
 #pragma unroll
-            for (int i = 0; i < PER_WAVE; ++i) {
-                const int pr = wave + 4 * i;
-                if (pr < PAIRS) {
-                    const int mt = pr / NTL, nt = pr - mt * NTL;
-                    const bf16x8_t a = *reinterpret_cast<const bf16x8_t*>(s_g + (mt * 16 + lr) * KP + k0 + 8 * lg);
+        for (int k = 0; k < kA; ++k) {
+            const int pix = apix0 + k * (NTHR / ACH), hy = pix / kHalo, hx = pix - hy * kHalo;
+            if (pix < kHalo * kHalo)
+                *reinterpret_cast<uint4*>(s_a + (ac >> 1) * APLANE + hy * AROW + (hx + 4 * (hx >> 3)) * 16 +
+                                          (ac & 1) * 8) = pa[k];
+        }
 #pragma unroll
-                    for (int d = 0; d < 3; ++d) {
-                        // output pixel k reads activation row (k / 16) + d of the staged copy
-                        const bf16x8_t b =
-                            *reinterpret_cast<const bf16x8_t*>(s_a + (nt * 16 + lr) * KA + k0 + 8 * lg + d * kT);
-                        acc[i][d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[i][d], 0, 0, 0);
+        for (int k = 0; k < kG; ++k) {
+            const int pix = gpix0 + k * (NTHR / GCH), x = pix % kT;
+            if (pix < kT * kT)
+                *reinterpret_cast<uint4*>(s_g + (gc >> 1) * GPLANE + (pix / kT) * GROW + (x + 4 * (x >> 3)) * 16 +
+                                          (gc & 1) * 8) = pg[k];
+        }
+        __syncthreads();
+        if (t + 1 < t_end) load_tile(t + 1);
+        if (wave < WAVES) {
+            // step s: pixel rows 2 s and 2 s + 1; tap row d reads activation rows 2 s + d and + 1
+            constexpr int kSteps = kT / 2;
+            bf16x8_t fg[2][MW], fa[2 * kSteps + 1][DXW];
+#pragma unroll
+            for (int m = 0; m < MW; ++m) fg[0][m] = read_tr(rg + m * GPLANE, rg + m * GPLANE + 4 * 16);
+#pragma unroll
+            for (int r = 0; r < 3; ++r)
+#pragma unroll
+                for (int x = 0; x < DXW; ++x) fa[r][x] = read_tr(ra[x][0] + r * AROW, ra[x][1] + r * AROW);
+#pragma unroll
+            for (int s = 0; s < kSteps; ++s) {
+                if (s + 1 < kSteps) {
+#pragma unroll
+                    for (int m = 0; m < MW; ++m) {
+                        const uint16_t* p = rg + m * GPLANE + 2 * (s + 1) * GROW;
+                        fg[(s + 1) & 1][m] = read_tr(p, p + 4 * 16);
                     }
+#pragma unroll
+                    for (int r = 2 * s + 3; r < 2 * s + 5; ++r)
+#pragma unroll
+                        for (int x = 0; x < DXW; ++x) fa[r][x] = read_tr(ra[x][0] + r * AROW, ra[x][1] + r * AROW);
                 }
+#pragma unroll
+                for (int m = 0; m < MW; ++m)
+#pragma unroll
+                    for (int x = 0; x < DXW; ++x)
+#pragma unroll
+                        for (int d = 0; d < 3; ++d)
+                            acc[m][x][d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fg[s & 1][m], fa[2 * s + d][x],
+                                                                                   acc[m][x][d], 0, 0, 0);
+            }
+        } else if (ci0 == 0) {
+            // lane: channel lr of plane lg % MTB, 4 pixels at a time
+            const uint16_t* p = s_g + (lg % MTB) * GPLANE + (lr >> 2) * 16 + cc;
+#pragma unroll 2
+            for (int row = 0; row < kT; ++row) {
+                short4_t v[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    v[q] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                        (lds_short4_t*)(p + row * GROW + (4 * q + 4 * (q >> 1)) * 16));
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) bsum += bf2f((uint16_t)v[q][j]);
             }
         }
-        if (dxi == 1 && tid < COUT)
-            for (int px = 0; px < kT * kT; ++px) bsum += bf2f(s_g[tid * KP + px]);
     }
-    // acc[i][d][r] = dW[co = 16 mt + 4 lg + r][tap = 3 d + dxi][ci = 16 nt + lr]
+    if (wave < WAVES) {
+        // acc[m][x][d][r] = dW[co = 16 mt + 4 lg + r][tap = 3 d + dx][ci = 16 nt + lr]
 #pragma unroll
-    for (int i = 0; i < PER_WAVE; ++i) {
-        const int pr = wave + 4 * i;
-        if (pr < PAIRS) {
-            const int mt = pr / NTL, nt = pr - mt * NTL;
+        for (int m = 0; m < MW; ++m)
 #pragma unroll
-            for (int d = 0; d < 3; ++d)
+            for (int x = 0; x < DXW; ++x)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int co = mt * 16 + 4 * lg + r, ci = nt * 16 + lr;
-                    part[((size_t)split * COUT + co) * 9 * CIN + (3 * d + dxi) * CIN + ci] = acc[i][d][r];
-                }
-        }
+                for (int d = 0; d < 3; ++d)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int co = co0 + (mg * MW + m) * 16 + 4 * lg + r, ci = ci0 + nt * 16 + lr;
+                        part[((size_t)split * COUT + co) * 9 * CIN + (3 * d + dx0 + x) * CIN + ci] = acc[m][x][d][r];
+                    }
+    } else if (ci0 == 0 && lg < MTB) {
+        part_b[split * COUT + co0 + lane] = bsum;
     }
-    if (dxi == 1 && tid < COUT) part_b[split * COUT + tid] = bsum;
 }
 
 // Sums the splits' partial weight gradients: a workgroup takes 64 entries,
@@ -653,8 +741,9 @@ static void wgrad(const Work& w, int B, int H, int W, const uint16_t* act, const
     const int n_tiles = B * (H / kT) * (W / kT);
     const int S = w.splits;
     const int per = (n_tiles + S - 1) / S;
-    hipLaunchKernelGGL((conv3x3_wgrad_kernel<CIN, COUT>), dim3(S, 3), dim3(256), 0, st, H, W, n_tiles, per, act, g,
-                       w.part, w.part_b);
+    using C = WgradCfg<CIN, COUT>;
+    hipLaunchKernelGGL((conv3x3_wgrad_kernel<CIN, COUT>), dim3(S, (CIN / C::CI_B) * (COUT / C::CO_B)),
+                       dim3((wgrad_waves<CIN, COUT>() + 1) * 64), 0, st, H, W, n_tiles, per, act, g, w.part, w.part_b);
     const int64_t E = (int64_t)COUT * 9 * CIN;
     hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((unsigned)((E + COUT + 63) / 64)), dim3(256), 0, st, S, E, COUT, w.part,
                        w.part_b, gw, gb);
