@@ -35,7 +35,7 @@ struct Geo {
     int64_t lb_words;
     // scratch sub-offsets (relative to DQO_BUF_SCRATCH)
     int64_t off_dk1, off_dv1, off_dk2, off_dv2, off_pk1, off_pv1, off_sched, off_sums, off_pose, off_written, off_sbase, off_seg,
-        off_sgbase, off_tlast, off_ckpt, off_suf, off_suflist, off_lbd, off_lbs, off_lbp;
+        off_sgbase, off_tlast, off_ckpt, off_suf, off_suflist, off_dcnt, off_lbd, off_lbs, off_lbp;
     int64_t seg_cap, ckpt_cap, suf_cap;
     bool tile_sort;     // per-tile depth order (dqo_depth_order TILE)
     int tile_sort_lds;  // pairs of a tile sorted in LDS
@@ -110,9 +110,8 @@ Geo geometry(const dqo_ctx* ctx, const dqo_frame_desc* d, const dqo_camera* cams
     g.depth_blocks = depth_blocks(g.listed);
     g.scan_blocks = (int)((g.listed + kScanTile - 1) / kScanTile);
     // the most blocks any listing of at most M items takes: blocks get longer
-    // at 2^18 and 2^19 items, so fewer items can need more of them
-    const int depth_blocks_max = std::max(depth_blocks(M), std::max(depth_blocks(std::min<int64_t>(M, (1 << 18) - 1)),
-                                                                    depth_blocks(std::min<int64_t>(M, (1 << 19) - 1))));
+    // at 2^18 items, so fewer items can need more of them
+    const int depth_blocks_max = std::max(depth_blocks(M), depth_blocks(std::min<int64_t>(M, (1 << 18) - 1)));
     const int scan_blocks_max = (int)((M + kScanTile - 1) / kScanTile);
     g.pair_blocks = (int)((cap + kPairTileMin - 1) / kPairTileMin);
     int64_t sz[DQO_BUF_COUNT];
@@ -151,6 +150,7 @@ Geo geometry(const dqo_ctx* ctx, const dqo_frame_desc* d, const dqo_camera* cams
     g.off_ckpt = so; so = align256(so + g.ckpt_cap * 6 * kWave * ts);
     g.off_suf = so; so = align256(so + g.suf_cap * 2 * tw * th * ts);
     g.off_suflist = so; so = align256(so + (g.suf_cap ? g.seg_cap * 8 : 0));
+    g.off_dcnt = so; so = align256(so + split_count_words(std::max(M, cap)) * 4);
     // look-back words: every block's, then every group's (grouped look-back)
     g.off_lbd = so; so = align256(so + (int64_t)kMaxDepthPasses * lb_blocks(depth_blocks_max) * kRadixBins * 8);
     g.off_lbs = so; so = align256(so + (int64_t)lb_blocks(scan_blocks_max) * (kRadixBins + 1) * 8);
@@ -202,6 +202,7 @@ StatePtrs state_ptrs(const Geo& g, void* state) {
     s.seg_cap = g.seg_cap;
     s.ckpt_cap = g.ckpt_cap;
     s.ctrl = (Ctrl*)(b + g.L.offset[DQO_BUF_CONTROL]);
+    s.digit_counts = (uint32_t*)(sc + g.off_dcnt);
     s.lb_depth = (uint64_t*)(sc + g.off_lbd);
     s.lb_scan = (uint64_t*)(sc + g.off_lbs);
     s.lb_pair = (uint64_t*)(sc + g.off_lbp);

@@ -22,38 +22,27 @@ constexpr int kGradWords = 10;    // dmx,dmy,dA,dB,dC, o*do, dr,dg,db,dz
 constexpr int kRadixBits = 8;
 constexpr int kRadixBins = 1 << kRadixBits;
 constexpr int kSortThreads = 256;
-// Items per thread of a radix pass.  The decoupled look-back costs one memory
-// latency per window of preceding blocks, so longer blocks shorten the chain
-// but lengthen each block's own ranking and scatter.  Measured on one MI355X:
-// the pair passes take short blocks (then 4096 items; 4608 now, below) while
-// that grid fits on the device at once (1.5M pairs of the 640x480 view: 1761 -> 1788 it/s against 8192) and
-// 8192-item blocks beyond (49M pairs of eight keyframes: 163 -> 175 it/s); the
-// depth passes are fastest with 2048-item blocks at 200k items (4096: 1700 ->
-// 1672 it/s, 8192 slower still) and with 8192-item blocks from about a
-// million (175 -> 180 it/s at 9.6M); 4096 in between.
-// Workgroup sizes of the depth and pair passes (256 or 1024 threads).
-#ifndef DQO_DEPTH_NT
-#define DQO_DEPTH_NT 256
-#endif
-#ifndef DQO_PAIR_NT
-#define DQO_PAIR_NT 512
-#endif
-#ifndef DQO_PAIR_IPT_SHORT
-#define DQO_PAIR_IPT_SHORT (DQO_PAIR_NT == 512 ? 9 : DQO_PAIR_NT == 256 ? 16 : 8)
-#endif
-#ifndef DQO_DEPTH_IPT_SMALL
-#define DQO_DEPTH_IPT_SMALL (DQO_DEPTH_NT == 256 ? 8 : 4)
-#endif
-// Pair passes whose grid fits on the device at once: 512 threads x 9 pairs
-// (4608-pair blocks, two per CU; 22.7 -> 21.3 us per pass at 1.5M pairs
-// against 256 x 16); longer grids: 256 x 32.
-constexpr int kDepthNt = DQO_DEPTH_NT, kPairNt = DQO_PAIR_NT, kPairNtLong = 256;
-constexpr int kPairIptShort = DQO_PAIR_IPT_SHORT, kPairIptLong = 32;
-constexpr int kPairTileMin = kPairNt * kPairIptShort < kPairNtLong * kPairIptLong ? kPairNt * kPairIptShort
-                                                                                   : kPairNtLong * kPairIptLong;  // sizes the pair look-back arrays
-inline int depth_ipt(int64_t items) {
-    constexpr int s = DQO_DEPTH_IPT_SMALL;
-    return items < (int64_t(1) << 18) ? s : items < (int64_t(1) << 19) ? 2 * s : 4 * s;
+// Blocks of a radix pass whose grid fits on the device at once (threads x
+// items per thread).  The decoupled look-back costs one memory latency per
+// group of preceding blocks, so longer blocks shorten it but lengthen each
+// block's own ranking and scatter, and more wavefronts hide more of the loads.
+// Depth passes: 2048 items below 2^18 of them, else 4096 (per pass, 4096-item
+// blocks against 2048: 300k items 12.3 / 11.4 us, 700k 15.7 / 22.9, 1M 21.0 /
+// 32.1; against 8192: 700k 17.5, 1M 23.6; 256 threads x 16 and x 32 instead
+// of 1024: 300k 14.4, 700k 24.0, 1M 31.4).  Pair passes: 4608-pair blocks, two
+// per CU, while that grid is resident (21.3 us at 1.5M pairs against 22.7 with
+// 256 x 16), else 8192-pair blocks (2.3M pairs: 34.9 us; split 38.6).
+constexpr int kDepthNt = 1024;
+constexpr int kPairNt = 512, kPairIptShort = 9, kPairNtLong = 256, kPairIptLong = 32;
+constexpr int kPairTileMin = kPairNt * kPairIptShort;  // sizes the pair look-back arrays
+static_assert(kPairTileMin <= kPairNtLong * kPairIptLong, "the look-back arrays hold the shorter blocks");
+inline int depth_ipt(int64_t items) { return items < (int64_t(1) << 18) ? 2 : 4; }
+// Split radix passes (a grid too large to be resident): items per block, and
+// blocks whose digit counts are prefixed together.
+constexpr int kSplitTile = 8192, kSplitGroup = 128;
+inline int64_t split_count_words(int64_t items) {  // counts per block and digit, then per group and digit
+    const int64_t nb = (items + kSplitTile - 1) / kSplitTile;
+    return (nb + (nb + kSplitGroup - 1) / kSplitGroup) * 256;
 }
 // Scan + emission: one record per thread, 512 per block, so that each of the
 // 8 wavefronts emits the pairs of its own 64 records (with the first pair
@@ -400,6 +389,7 @@ struct StatePtrs {
     uint64_t* lb_depth;   // [kMaxDepthPasses][blocks][256]
     uint64_t* lb_scan;    // [blocks][257]: 256 digits of the fused first pair pass, then the pair count
     uint64_t* lb_pair;    // [kMaxPairPasses][blocks][256]
+    uint32_t* digit_counts;  // split_count_words: a split radix pass, depth or pairs
     int64_t items;        // V * n
     int64_t listed;       // items inside their view's segment (== items without segments): sorted and emitted
     int64_t capacity;

@@ -608,26 +608,23 @@ hipError_t launch_project_bin(const Frame<T>& f, const T* params, const int32_t*
                        f.n, (uint32_t)N, s.tile_sort ? 1 : 0, params, ids, (T*)s.splats, s.rects, s.counts, s.depth_keys[0], s.depth_vals[0],
                        s.ranges, range_words, s.hist_copies_depth, s.ctrl,
                        s.fused_emit ? &s.ctrl->hist_pair[0][0][0] : nullptr, s.hist_copies_pair);
-    // Below 2^18 items the 2048-item blocks run as 1024 threads x 2 items
-    // (4 wavefronts per SIMD instead of 1 hide more of the load latency:
-    // 12.6 -> 12.0 us per pass at 200k items); the block length is the same.
-#ifndef DQO_DEPTH_SMALL_NT
-#define DQO_DEPTH_SMALL_NT 1024
-#endif
     if (N == 0) return hipGetLastError();
-    const int dnt = N < (int64_t(1) << 18) ? DQO_DEPTH_SMALL_NT : kDepthNt;
-    const int dipt = kDepthNt * depth_ipt(N) / dnt;
+    const int dipt = depth_ipt(N);
+    const bool split = !radix_resident(kDepthNt, dipt, N);
     // Buffers of the four passes: 0 -> 1 -> 2 -> 1 -> 0, or 0 -> 1 -> 2 -> 0
     // when three passes suffice (decided on the device from the key range).
     static const int kIn[kMaxDepthPasses] = {0, 1, 2, 1}, kOut[kMaxDepthPasses] = {1, 2, 1, 0};
     for (int p = 0; p < (s.tile_sort ? 0 : kMaxDepthPasses); ++p) {
         const DepthRel rel{p, p == 2 ? s.depth_keys[0] : nullptr, p == 2 ? s.depth_vals[0] : nullptr,
                            p + 1 < kMaxDepthPasses ? &s.ctrl->hist_depth[0][p + 1][0] : nullptr};
-        hipError_t e = launch_radix_pass(s.depth_keys[kIn[p]], s.depth_vals[kIn[p]], s.depth_keys[kOut[p]],
+        hipError_t e = split
+            ? launch_split_pass(s.depth_keys[kIn[p]], s.depth_vals[kIn[p]], s.depth_keys[kOut[p]], s.depth_vals[kOut[p]],
+                                nullptr, (uint32_t)N, p * kRadixBits, s.digit_counts, s.ctrl, st, &rel)
+            : launch_radix_pass(s.depth_keys[kIn[p]], s.depth_vals[kIn[p]], s.depth_keys[kOut[p]],
                                          s.depth_vals[kOut[p]], nullptr, (uint32_t)N, p * kRadixBits,
                                          &s.ctrl->hist_depth[0][p][0], kMaxDepthPasses * kRadixBins, s.hist_copies_depth,
                                          s.lb_depth + (size_t)p * lb_blocks(s.depth_blocks) * kRadixBins,
-                                         &s.ctrl->counters[kCounterDepth + p], s.ctrl, st, dnt, dipt, &rel);
+                                         &s.ctrl->counters[kCounterDepth + p], s.ctrl, st, kDepthNt, dipt, &rel);
         if (e != hipSuccess) return e;
     }
     // the fused emission writes the first pair pass's output buffer

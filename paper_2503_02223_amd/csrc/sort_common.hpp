@@ -49,6 +49,11 @@ hipError_t launch_radix_pass(const uint32_t* kin, const uint32_t* vin, uint32_t*
                              const uint32_t* n_dev, uint32_t n_host, int shift, const uint32_t* ghist,
                              int hist_stride, int hist_copies, uint64_t* lb, uint32_t* counter, Ctrl* ctrl,
                              hipStream_t st, int nt, int ipt, const DepthRel* rel = nullptr);
+// The same pass as three kernels without a look-back, for a grid that does not
+// fit on the device at once.  cnt: split_count_words(n_host).  The inputs must be 16-byte aligned.
+hipError_t launch_split_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout,
+                             const uint32_t* n_dev, uint32_t n_host, int shift, uint32_t* cnt, const Ctrl* ctrl,
+                             hipStream_t st, const DepthRel* rel = nullptr);
 // Whether a radix pass of nt threads x ipt items per block over `items` keys
 // fits on the device at once (resident-grid block order).
 bool radix_resident(int nt, int ipt, int64_t items);
