@@ -166,6 +166,12 @@ struct Consts {
 // only add work (measured: 1M Gaussians at 1200x680, 12750 tiles, backward
 // 11% slower segmented).
 constexpr int kSegTilesMax = 8192;
+// The suffix pass pays up to this many 64-pixel parts, 16 wavefronts per CU
+// (forward, suffix pass and backward of 60k Gaussians against the same without
+// it: 1200 parts 169 / 254 us, 2700 159 / 196 and 168 / 209, 4800 170 / 165
+// and 177 / 174, 7680 198 / 158; with instance channels, 8x8 tiles: 1200 210 /
+// 272, 4800 198 / 179, 16x16 tiles: 4800 224 / 235, 16x8: 7680 245 / 208).
+constexpr int kSuffixPartsMax = 4096;
 // The boundary state at pair position b (a multiple of kSegLen past its
 // tile's first position rs) is record rs / kSegLen + (b - rs) / kSegLen: the
 // records of different tiles never meet (a tile of n pairs has fewer than

@@ -1157,9 +1157,12 @@ __global__ __launch_bounds__(kWave) void suffix_state_kernel(
 // SUF: a workgroup per listed segment, starting from the suffix pass's states;
 // else per tile.  Waves per SIMD: three without spills for the segments, whose
 // frames leave the machine half empty (of four, 14% slower), four with 60
-// bytes of spills for the frames that fill it (of three, 6% slower).
+// bytes of spills for the frames that fill it (of three, 6% slower).  With
+// instance channels, whose gradients are gathered for each record, three
+// (640x480 in 16x16 tiles 178 -> 152 us, 762x637 in 16x8 tiles 159 -> 135,
+// 1000x700 226 -> 228).
 template <typename T, int TW, int TH, bool PROBS, bool SUF>
-__global__ __launch_bounds__(TW* TH, sizeof(T) == 8 ? 1 : SUF ? 3 : 4) void render_backward_tile_kernel(
+__global__ __launch_bounds__(TW* TH, sizeof(T) == 8 ? 1 : SUF || PROBS ? 3 : 4) void render_backward_tile_kernel(
     Views<T> V, Consts<T> cs, int K, const T* __restrict__ splats,
     const uint32_t* __restrict__ pvals, const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ schedule,
     const T* __restrict__ tfinal, const int32_t* __restrict__ last, const int32_t* __restrict__ target,
@@ -1388,6 +1391,173 @@ __global__ __launch_bounds__(TW* TH, sizeof(T) == 8 ? 1 : SUF ? 3 : 4) void rend
     }
 }
 
+// Tiles of several wavefronts with instance-channel gradients where the tiles
+// fill the machine: the workgroup walks its range in chunks of six records,
+// each wave's sums meeting in LDS after every chunk.  Its 7 KB of LDS and few
+// registers keep more wavefronts in flight than the strips' kernel, which
+// hides the gathers of the channels' gradients: 500k Gaussians at 1200x680 in
+// 16x8 tiles 295 us against 339 (100k at 1000x700 195 / 222, in 16x16 tiles
+// 214 / 228); with fewer tiles the strips' kernel, which skips what a strip
+// does not touch, is ahead (762x637 135 / 135, 640x480 147 / 139, in 16x16
+// tiles 188 / 152), and without channel gradients it is at least level (257 /
+// 261 and 171 / 170; eight keyframes over 1.2M Gaussians 1376 / 1260).
+template <typename T, int TW, int TH>
+__global__ __launch_bounds__(TW* TH) void render_backward_kernel(
+    Views<T> V, Consts<T> cs, int K, const T* __restrict__ splats,
+    const uint32_t* __restrict__ pvals, const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ schedule,
+    const T* __restrict__ tfinal, const int32_t* __restrict__ last, const int32_t* __restrict__ target,
+    const T* __restrict__ dC, const T* __restrict__ dD, const T* __restrict__ dT, const T* __restrict__ dP,
+    const T* __restrict__ dPt, T* __restrict__ partials, uint8_t* __restrict__ written, uint32_t cap, uint32_t M) {
+    constexpr int BLOCK = TW * TH;
+    constexpr int NW = BLOCK / kWave;
+    __shared__ __align__(16) T s_sp[BLOCK * kWalkWords];
+    __shared__ uint32_t s_slot[BLOCK];
+    __shared__ T s_red[2][NW][kWave];
+    __shared__ int s_maxlast;
+    __shared__ int s_wc[NW];
+
+    const int tid = threadIdx.x;
+    const int lane = tid & (kWave - 1);
+    const int wave = tid >> 6;
+    const int tile = (int)min(schedule[blockIdx.x], (uint32_t)(gridDim.x - 1));
+    const int view = tile / V.tiles_per_view;
+    const int t = tile - view * V.tiles_per_view;
+    const int ty = t / V.tiles_x, tx = t - ty * V.tiles_x;
+    const int px = tx * TW + (tid % TW), py = ty * TH + (tid / TW);
+    const bool inside = px < V.W && py < V.H && in_window(V.cam[view], px, py);
+    const int64_t HW = (int64_t)V.W * V.H;
+    const int64_t pix = (int64_t)py * V.W + px;
+    const int64_t o = view * HW + pix;
+    // the pixel centre relative to the tile's corner
+    const T u = T(tid % TW) + T(0.5), v_px = T(tid / TW) + T(0.5);
+    const T ox = T(tx * TW), oy = T(ty * TH);
+    const uint32_t re = min(ranges[2 * tile + 1], cap), rs = min(ranges[2 * tile], re);
+
+    int lastp = -1;
+    T Tcur = T(1), gc0 = T(0), gc1 = T(0), gc2 = T(0), gd = T(0), gt = T(0), gpt = T(0);
+    int tgt = -2;
+    if (inside) {
+        lastp = last[o];
+        if (lastp < (int)rs || lastp >= (int)re) lastp = -1;  // not from this frame's forward: no work
+        Tcur = tfinal[o];
+        gc0 = dC[(view * 3 + 0) * HW + pix];
+        gc1 = dC[(view * 3 + 1) * HW + pix];
+        gc2 = dC[(view * 3 + 2) * HW + pix];
+        gd = dD ? dD[o] : T(0);
+        gt = dT ? dT[o] : T(0);
+        if (dPt && target) {
+            tgt = job_target(V.cam[view].job, target[o]);
+            gpt = dPt[o];
+            if (tgt == -1) gt += gpt;
+        }
+    }
+    if (tid == 0) s_maxlast = -1;
+    __syncthreads();
+    if (lastp >= 0) atomicMax(&s_maxlast, lastp);
+    __syncthreads();
+    const int maxlast = __builtin_amdgcn_readfirstlane(s_maxlast);  // uniform: scalar walk bounds
+    // Pairs behind every pixel's last blended Gaussian are not written and
+    // stay unmarked (their partials count as zero).
+    const uint32_t hi = (maxlast >= (int)rs) ? (uint32_t)(maxlast + 1) : rs;
+    T S = Tcur * (gc0 * cs.bg[0] + gc1 * cs.bg[1] + gc2 * cs.bg[2] + gt);
+    int buf = 0;
+    for (uint32_t bend = hi; bend > rs;) {
+        const uint32_t bstart = (bend - rs > (uint32_t)BLOCK) ? bend - BLOCK : rs;
+        const int nbr = (int)(bend - bstart);
+        __syncthreads();
+        // the batch's records that may contribute in the tile (those the
+        // forward did not mark), compacted in order
+        T r[kRecWords];
+        uint32_t slot = 0u;
+        bool cand = false;
+        if (tid < nbr) {
+            const uint32_t pv = pvals[bstart + tid];
+            if (!(pv & kPairSkip)) {
+                slot = load_splat_slot<T>(r, splats + (size_t)min(pv, M - 1) * kSplatWords, tx, ty);
+                cand = true;
+            }
+        }
+        const uint64_t bal = __ballot(cand);
+        if (lane == 0) s_wc[wave] = __popcll(bal);
+        __syncthreads();
+        int nb = 0, off = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            off += (w < wave) ? s_wc[w] : 0;
+            nb += s_wc[w];
+        }
+        if (cand) {
+            const int q = off + rank_below(bal);
+            store_walk_record<T>(s_sp + q * kWalkWords, r, ox, oy, (int)(bstart + tid), cs);
+            s_slot[q] = slot;
+        }
+        __syncthreads();
+        for (int c0 = nb - 1; c0 >= 0; c0 -= kChunk) {
+            T v[64];
+#pragma unroll
+            for (int k = 0; k < 64; ++k) v[k] = T(0);
+            bool any = false;
+#pragma unroll
+            for (int c = 0; c < kChunk; ++c) {
+                const int jl = c0 - c;
+                if (jl < 0) break;
+                const T* sp = s_sp + jl * kWalkWords;
+                T dx, dy, pp, rr;
+                const T E = walk_exponent(sp, u, v_px, dx, dy, pp, rr);
+                const bool contrib = (E >= sp[kWThr]) && (word_to_id<T>(sp[kWPos]) <= lastp);
+                if (!wave_any(contrib)) continue;
+                const T araw = exp2_of<T>(E);
+                const bool clamped = !(araw < cs.alpha_max);
+                const T a0 = clamped ? cs.alpha_max : araw;
+                any = true;
+                const T a = contrib ? a0 : T(0);
+                const T roma = fast_rcp<T>(T(1) - a);
+                const T Ti = Tcur * roma;
+                const T w = a * Ti;
+                const int id = word_to_id<T>(sp[kWId]);
+                T vv = fmadd(gc0, sp[kWR], fmadd(gc1, sp[kWG], fmadd(gc2, sp[kWB], gd * sp[kWZ])));
+                vv += (tgt >= 0 && id == tgt) ? gpt : T(0);
+                if (dP && contrib && id >= 0 && id < K) vv += dP[((int64_t)view * K + id) * HW + pix];
+                const T dalpha = contrib ? (Ti * vv - S * roma) : T(0);
+                S = fmadd(w, vv, S);
+                Tcur = Ti;
+                v[c * kGradWords + 6] = gc0 * w;
+                v[c * kGradWords + 7] = gc1 * w;
+                v[c * kGradWords + 8] = gc2 * w;
+                v[c * kGradWords + 9] = gd * w;
+                // dq = -2 dL/dQ; the conic rows from the exponent's (p, r)
+                const T dq = clamped ? T(0) : dalpha * a;
+                const T iq = T(1) / neg_half_log2e<T>();
+                v[c * kGradWords + 5] = dq;  // o dL/do (the opacity's sum is divided by o)
+                v[c * kGradWords + 0] = dq * iq * pp;
+                v[c * kGradWords + 1] = dq * iq * rr;
+                v[c * kGradWords + 2] = T(-0.5) * dq * dx * dx;
+                v[c * kGradWords + 3] = -dq * dx * dy;
+                v[c * kGradWords + 4] = T(-0.5) * dq * dy * dy;
+            }
+            if (wave_any(any)) wave_transpose_sum<T>(v, lane);
+            s_red[buf][wave][lane] = v[0];
+            __syncthreads();
+            if (tid < kChunk * kGradWords) {
+                const int c = tid / kGradWords;
+                const int jl = c0 - c;
+                if (jl >= 0) {
+                    T sum = T(0);
+#pragma unroll
+                    for (int w2 = 0; w2 < NW; ++w2) sum += s_red[buf][w2][tid];
+                    const uint32_t slot = s_slot[jl];
+                    if (slot < cap) {
+                        partials[(size_t)slot * kGradWords + (tid - c * kGradWords)] = sum;
+                        if (tid == c * kGradWords) written[slot] = 1;
+                    }
+                }
+            }
+            buf ^= 1;
+        }
+        bend = bstart;
+    }
+}
+
 // ---------------------------------------------------------------- launchers
 template <typename T, int TW, int TH>
 static hipError_t fwd_tile(const Frame<T>& f, const dqo_images& img, hipStream_t st) {
@@ -1434,6 +1604,16 @@ static hipError_t bwd_parts(const Frame<T>& f, const dqo_images& img, const dqo_
                            img.last, img.target, (const T*)g.d_color, (const T*)g.d_depth, (const T*)g.d_t_final,
                            (const T*)g.d_probs, (const T*)g.d_p_target, (uint32_t)s.capacity, (uint32_t)s.items,
                            s.seg_base, s.suf_list, (uint32_t)s.seg_cap, (T*)s.suffix, (uint32_t)s.suf_cap, s.tile_last);
+    }
+    if constexpr (PROBS && N > 1) {
+        if (!suf && (int64_t)blocks * N > kSegTilesMax) {
+            hipLaunchKernelGGL((render_backward_kernel<T, TW, TH>), dim3(blocks), dim3(TW * TH), 0, st, f.views,
+                               f.consts, f.K, (const T*)s.splats, s.pair_vals[0], s.ranges, s.schedule,
+                               (const T*)img.t_final, img.last, img.target, (const T*)g.d_color, (const T*)g.d_depth,
+                               (const T*)g.d_t_final, (const T*)g.d_probs, (const T*)g.d_p_target, (T*)s.partials,
+                               s.written, (uint32_t)s.capacity, (uint32_t)s.items);
+            return hipGetLastError();
+        }
     }
     const int64_t gq = 8 * DQO_BWD_XCD_CHUNK;  // whole XCD chunks
     const unsigned grid = suf ? (unsigned)((s.seg_cap + gq - 1) / gq * gq) : (unsigned)blocks;
