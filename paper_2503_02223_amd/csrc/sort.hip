@@ -509,7 +509,7 @@ hipError_t launch_split_pass(const uint32_t* kin, const uint32_t* vin, uint32_t*
 // took 66 us for 27.8M pairs, now 28).
 __global__ __launch_bounds__(256) void tile_bounds_kernel(const uint32_t* __restrict__ keys,
                                                           const uint32_t* __restrict__ n_dev, uint32_t n_host,
-                                                          uint32_t* __restrict__ ranges,
+                                                          uint32_t tiles, uint32_t* __restrict__ ranges,
                                                           uint32_t* __restrict__ written_words) {
     const uint32_t n = min(*n_dev, n_host), nw = (n + 3u) / 4u;
     const int lane = threadIdx.x & (kWave - 1);
@@ -535,11 +535,12 @@ __global__ __launch_bounds__(256) void tile_bounds_kernel(const uint32_t* __rest
             const uint32_t p = i + j;
             if (p >= n) break;
             const uint32_t t = k[1 + j];
+            // (a list that overflowed may hold slots that no pair was written to)
             if (p == 0u || k[j] != t) {
-                ranges[2 * t] = p;
-                if (p > 0u) ranges[2 * k[j] + 1] = p;
+                if (t < tiles) ranges[2 * t] = p;
+                if (p > 0u && k[j] < tiles) ranges[2 * k[j] + 1] = p;
             }
-            if (p + 1u == n) ranges[2 * t + 1] = n;
+            if (p + 1u == n && t < tiles) ranges[2 * t + 1] = n;
         }
         if (w < nw) written_words[w] = 0u;
     }
@@ -736,12 +737,14 @@ __global__ __launch_bounds__(kTileSortThreads) void tile_sort_kernel(const uint3
                                                                     const uint32_t* __restrict__ schedule,
                                                                     const uint32_t* __restrict__ dkeys, uint32_t M,
                                                                     uint32_t cap, uint32_t lds_max, int tiles,
+                                                                    const uint32_t* __restrict__ n_dev,
                                                                     uint32_t* __restrict__ pvals,
                                                                     uint32_t* __restrict__ tmp) {
     __shared__ uint64_t s_k[kTileSortLds];
     __shared__ uint32_t s_off[kRadixBins];
     __shared__ uint32_t s_wcnt[kTileSortThreads / kWave][kRadixBins];
     __shared__ uint32_t s_scan[kTileSortThreads / kWave];
+    if (*n_dev > cap) return;  // the list overflowed: its ranges mean nothing
     const int tid = threadIdx.x;
     const uint32_t tile = min(schedule[blockIdx.x], (uint32_t)(tiles - 1));
     const uint32_t re = min(ranges[2 * tile + 1], cap), rs = min(ranges[2 * tile], re);
@@ -859,14 +862,15 @@ hipError_t launch_pair_sort(const StatePtrs& s, int tiles_total, hipStream_t st)
     if (tiles_total > 0) {
         // four pairs per thread, every key load in flight at once
         const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(1 << 20, ((int64_t)cap + 1023) / 1024));
-        hipLaunchKernelGGL(tile_bounds_kernel, dim3(grid), dim3(256), 0, st, s.pair_keys[0], n_dev, cap, s.ranges,
+        hipLaunchKernelGGL(tile_bounds_kernel, dim3(grid), dim3(256), 0, st, s.pair_keys[0], n_dev, cap,
+                           (uint32_t)tiles_total, s.ranges,
                            (uint32_t*)s.written);
         hipLaunchKernelGGL(tile_schedule_kernel, dim3(1), dim3(kSchedThreads), 0, st, s.ranges, tiles_total,
                            s.schedule, segmented_backward(s, tiles_total) || suffix_backward(s) ? 1 : 0, s.seg_base, s.ctrl);
         if (s.tile_sort)
             hipLaunchKernelGGL(tile_sort_kernel, dim3((unsigned)tiles_total), dim3(kTileSortThreads), 0, st, s.ranges,
                                s.schedule, s.depth_keys[0], (uint32_t)s.items, cap, (uint32_t)s.tile_sort_lds,
-                               tiles_total, s.pair_vals[0], s.pair_vals[1]);
+                               tiles_total, n_dev, s.pair_vals[0], s.pair_vals[1]);
         return hipGetLastError();
     }
     return launch_clear_written(s, st);
