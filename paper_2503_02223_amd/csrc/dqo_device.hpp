@@ -426,6 +426,9 @@ struct Frame {
 template <typename T>
 hipError_t launch_project_bin(const Frame<T>& f, const T* params, const int32_t* ids, hipStream_t st);
 hipError_t launch_pair_sort(const StatePtrs& s, int tiles_total, hipStream_t st);
+// Whether the pair sort counts its digits itself (split passes); else the
+// emission counts them.
+bool pair_sort_split(int64_t capacity);
 // Workgroups of the scan + emission (fused with the first pair pass or not)
 // that the device holds at once.
 int scan_emit_resident(bool fused);

@@ -316,7 +316,7 @@ template <typename T, bool FUSED>
 __global__ __launch_bounds__(kScanThreads) void scan_emit_kernel(
     const uint32_t* __restrict__ order, const uint32_t* __restrict__ counts, const short4* __restrict__ rects,
     uint32_t* __restrict__ offsets, T* __restrict__ splats, uint32_t* __restrict__ pkeys, uint32_t* __restrict__ pvals, uint32_t listed,
-    uint32_t M, uint32_t cap, int64_t n, int tiles_x, int tiles_per_view, int pair_passes, int copies, uint64_t* lb, Ctrl* ctrl,
+    uint32_t M, uint32_t cap, int64_t n, int tiles_x, int tiles_per_view, int hist_passes, int copies, uint64_t* lb, Ctrl* ctrl,
     const uint32_t* __restrict__ block_base) {
     __shared__ uint32_t s_incl[kScanTile];
     __shared__ uint32_t s_rec[kScanTile];
@@ -565,7 +565,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_emit_kernel(
                 pvals[gpos] = item;
             }
             if (valid)
-                for (int p = FUSED ? 1 : 0; p < pair_passes; ++p) atomicAdd(&s_hist[p][(tile >> (8 * p)) & 255u], 1u);
+                for (int p = FUSED ? 1 : 0; p < hist_passes; ++p) atomicAdd(&s_hist[p][(tile >> (8 * p)) & 255u], 1u);
         }
     }
     __syncthreads();
@@ -580,7 +580,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_emit_kernel(
         }
     }
     if (tid < kRadixBins)
-        for (int p = FUSED ? 1 : 0; p < pair_passes; ++p) {
+        for (int p = FUSED ? 1 : 0; p < hist_passes; ++p) {
             const uint32_t h = s_hist[p][tid];
             if (h) atomicAdd(&ctrl->hist_pair[blockIdx.x % copies][p][tid], h);
         }
@@ -639,7 +639,8 @@ hipError_t launch_project_bin(const Frame<T>& f, const T* params, const int32_t*
     auto emit = s.fused_emit ? scan_emit_kernel<T, true> : scan_emit_kernel<T, false>;
     hipLaunchKernelGGL(emit, dim3((unsigned)s.scan_blocks), dim3(kScanThreads), 0, st, item_order(s),
                        s.counts, s.rects, s.offsets, (T*)s.splats, s.pair_keys[pf], s.pair_vals[pf], (uint32_t)N,
-                       (uint32_t)M, (uint32_t)s.capacity, f.n, f.views.tiles_x, f.views.tiles_per_view, s.pair_passes,
+                       (uint32_t)M, (uint32_t)s.capacity, f.n, f.views.tiles_x, f.views.tiles_per_view,
+                       pair_sort_split(s.capacity) ? 0 : s.pair_passes,
                        s.hist_copies_pair, s.lb_scan, s.ctrl, two_level ? (const uint32_t*)s.scan_base : nullptr);
     return hipGetLastError();
 }
@@ -745,6 +746,10 @@ __global__ __launch_bounds__(kSlotWaves * kWave) void slot_sum_kernel(const uint
             const uint32_t s = b0 + q * kWave + (uint32_t)lane;
             mk[q] = s < S1 && written[s] != 0;
         }
+        bool any = false;
+#pragma unroll
+        for (int q = 0; q < kSlotBatch; ++q) any = any || mk[q];
+        if (__ballot(any) == 0ull) continue;  // nothing written: sums of zeros
 #pragma unroll
         for (int q = 0; q < kSlotBatch; ++q) {
             const uint32_t s = b0 + q * kWave + (uint32_t)lane;
@@ -755,6 +760,7 @@ __global__ __launch_bounds__(kSlotWaves * kWave) void slot_sum_kernel(const uint
         for (int q = 0; q < kSlotBatch; ++q) {
             const uint32_t r0 = b0 + q * kWave;
             if (r0 >= S1) break;  // wave-uniform
+            if (__ballot(mk[q]) == 0ull) continue;
             s_start[wave][lane] = 0;
             if (has && off >= r0 && off < r0 + kWave) s_start[wave][off - r0] = 1;
             __builtin_amdgcn_wave_barrier();

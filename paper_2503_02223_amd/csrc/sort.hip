@@ -838,12 +838,16 @@ __global__ __launch_bounds__(kTileSortThreads) void tile_sort_kernel(const uint3
     // four passes: the result is back in pvals
 }
 
+bool pair_sort_split(int64_t capacity) {
+    return !radix_resident(kPairNt, kPairIptShort, capacity) && !radix_resident(kPairNtLong, kPairIptLong, capacity);
+}
+
 hipError_t launch_pair_sort(const StatePtrs& s, int tiles_total, hipStream_t st) {
     const uint32_t cap = (uint32_t)s.capacity;
     const uint32_t* n_dev = &s.ctrl->num_pairs;
     // short blocks while that grid is resident, else long ones, else the split pass
     const bool short_ok = radix_resident(kPairNt, kPairIptShort, cap);
-    const bool split = !short_ok && !radix_resident(kPairNtLong, kPairIptLong, cap);
+    const bool split = pair_sort_split(cap);
     const int nt = short_ok ? kPairNt : kPairNtLong, ipt = short_ok ? kPairIptShort : kPairIptLong;
     // the fused emission has done pass 0 (its output is in the other buffer)
     const int p0 = s.fused_emit ? 1 : 0;
