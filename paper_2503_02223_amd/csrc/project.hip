@@ -314,8 +314,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_block_base_kernel(uint32_t*
 // running count per digit).  Needs the whole grid on the device at once.
 template <typename T, bool FUSED>
 __global__ __launch_bounds__(kScanThreads) void scan_emit_kernel(
-    const uint32_t* __restrict__ order, const uint32_t* __restrict__ counts, const short4* __restrict__ rects,
-    uint32_t* __restrict__ offsets, T* __restrict__ splats, uint32_t* __restrict__ pkeys, uint32_t* __restrict__ pvals, uint32_t listed,
+    const uint32_t* __restrict__ order, const short4* __restrict__ rects, uint32_t* __restrict__ offsets, T* __restrict__ splats, uint32_t* __restrict__ pkeys, uint32_t* __restrict__ pvals, uint32_t listed,
     uint32_t M, uint32_t cap, int64_t n, int tiles_x, int tiles_per_view, int hist_passes, int copies, uint64_t* lb, Ctrl* ctrl,
     const uint32_t* __restrict__ block_base) {
     __shared__ uint32_t s_incl[kScanTile];
@@ -378,14 +377,15 @@ __global__ __launch_bounds__(kScanThreads) void scan_emit_kernel(
     const uint32_t base = bid * (uint32_t)kScanTile;
     if (base >= listed) return;
     if (bid != blockIdx.x) load_recs(bid);
-    // The block's records with their counts and tile rectangles, gathered
-    // with every load in flight at once and kept in LDS for the emission.
+    // The block's records with their tile rectangles, whose areas are the pair
+    // counts (0 by 0 where there are none), gathered with every load in flight
+    // at once and kept in LDS for the emission.
     short4 rc[kScanIpt];
 #pragma unroll
     for (int k = 0; k < kScanIpt; ++k) {
         const bool ok = rec[k] != 0xffffffffu;
-        c[k] = ok ? counts[rec[k]] : 0u;
         rc[k] = ok ? rects[rec[k]] : make_short4(0, 0, -1, -1);
+        c[k] = (uint32_t)(rc[k].z - rc[k].x + 1) * (uint32_t)(rc[k].w - rc[k].y + 1);
     }
 #pragma unroll
     for (int k = 0; k < kScanIpt; ++k) {
@@ -637,8 +637,7 @@ hipError_t launch_project_bin(const Frame<T>& f, const T* params, const int32_t*
                            (uint32_t)s.capacity, s.ctrl);
     }
     auto emit = s.fused_emit ? scan_emit_kernel<T, true> : scan_emit_kernel<T, false>;
-    hipLaunchKernelGGL(emit, dim3((unsigned)s.scan_blocks), dim3(kScanThreads), 0, st, item_order(s),
-                       s.counts, s.rects, s.offsets, (T*)s.splats, s.pair_keys[pf], s.pair_vals[pf], (uint32_t)N,
+    hipLaunchKernelGGL(emit, dim3((unsigned)s.scan_blocks), dim3(kScanThreads), 0, st, item_order(s), s.rects, s.offsets, (T*)s.splats, s.pair_keys[pf], s.pair_vals[pf], (uint32_t)N,
                        (uint32_t)M, (uint32_t)s.capacity, f.n, f.views.tiles_x, f.views.tiles_per_view,
                        pair_sort_split(s.capacity) ? 0 : s.pair_passes,
                        s.hist_copies_pair, s.lb_scan, s.ctrl, two_level ? (const uint32_t*)s.scan_base : nullptr);
@@ -708,7 +707,7 @@ __device__ __forceinline__ T segmented_scan(T v, int lane, int seg_lo) {
 
 template <typename T>
 __global__ __launch_bounds__(kSlotWaves * kWave) void slot_sum_kernel(const uint32_t* __restrict__ order,
-                                                                      const uint32_t* __restrict__ counts,
+                                                                      const uint32_t* __restrict__ n_pairs,
                                                                       const uint32_t* __restrict__ offsets,
                                                                       const T* __restrict__ partials,
                                                                       const uint8_t* __restrict__ written, uint32_t listed,
@@ -719,12 +718,18 @@ __global__ __launch_bounds__(kSlotWaves * kWave) void slot_sum_kernel(const uint
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
     const uint64_t lt = lane ? (~0ull >> (kWave - lane)) : 0ull;
     const uint32_t q = ((uint32_t)blockIdx.x * kSlotWaves + wave) * kWave + lane;
-    uint32_t rec = 0, c = 0, off = 0;
+    uint32_t rec = 0, off = 0, end = 0;
+    const uint32_t pairs = *n_pairs;
     if (q < listed) {
         rec = order ? min(order[q], M - 1) : q;  // emission order: depth order, or item order
-        c = counts[rec];
         off = offsets[rec];
+        // an item's slots end where the next one's begin
+        end = pairs;
+        if (lane == kWave - 1 && q + 1u < listed) end = offsets[order ? min(order[q + 1u], M - 1) : q + 1u];
     }
+    const uint32_t next_off = __shfl_down(off, 1);
+    if (lane < kWave - 1 && q + 1u < listed) end = next_off;
+    const uint32_t c = q < listed ? end - off : 0u;
 #pragma unroll
     for (int k = 0; k < kGradWords; ++k) s_acc[wave][lane][k] = T(0);
     const bool has = c > 0;
@@ -796,7 +801,7 @@ static void launch_slot_sums(const Frame<T>& f, hipStream_t st) {
     constexpr int kItems = kSlotWaves * kWave;
     if (s.listed == 0) return;
     hipLaunchKernelGGL(slot_sum_kernel<T>, dim3((unsigned)((s.listed + kItems - 1) / kItems)), dim3(kItems), 0, st,
-                       item_order(s), s.counts, s.offsets, (const T*)s.partials, s.written, (uint32_t)s.listed,
+                       item_order(s), &s.ctrl->num_pairs, s.offsets, (const T*)s.partials, s.written, (uint32_t)s.listed,
                        (uint32_t)s.items, (uint32_t)s.capacity, (T*)s.sums);
 }
 
