@@ -288,6 +288,7 @@ class Frame:
         ctx.check(lib().dqo_state_layout(ctx.h, ctypes.byref(self.desc), self.cams, ctypes.byref(self.layout)))
         self.state = torch.empty(int(self.layout.total), dtype=torch.uint8, device=self.device)
         ctx.check(lib().dqo_state_init(ctx.h, ctypes.byref(self.desc), self.cams, _ptr(self.state), _stream()))
+        self.control_words = self.buf("control", torch.int32, 3)   # status, epoch, pair count
         self.W, self.H = int(cams[0]["width"]), int(cams[0]["height"])
         self.V = len(cams)
         self.n, self.K, self.capacity = int(n), int(K), int(capacity)
@@ -593,10 +594,11 @@ class Rasterizer:
     def _post_status(self, stream):
         """Enqueues a copy of the frame's status word and pair count to pinned
         host words, for _wait_status."""
-        s = stream if stream is not None else torch.cuda.current_stream()
-        with torch.cuda.stream(s):
-            self._words.copy_(self.frame.buf("control", torch.int32, 3), non_blocking=True)
-            self._words_event.record(s)
+        if stream is not None and stream != torch.cuda.current_stream():
+            with torch.cuda.stream(stream):
+                return self._post_status(None)
+        self._words.copy_(self.frame.control_words, non_blocking=True)
+        self._words_event.record()
 
     def _wait_status(self):
         """(status word, pair count) as of _post_status; waits for that copy
