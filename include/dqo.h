@@ -340,7 +340,9 @@ int dqo_object_loss_noalloc(const dqo_ctx* ctx, const dqo_frame_desc* desc, cons
  * the state the forward stored at the segment's end.  Those states belong
  * to the last such forward; the device checks that it is this binning and
  * these images (img->last and img->target), and otherwise walks every tile
- * whole, which gives the same gradients up to rounding order. */
+ * whole, which gives the same gradients up to rounding order.  Larger
+ * tiles, and 8x8 tiles with instance-channel gradients, go through states
+ * of this call's own where the tiles hold at most 4096 parts of 64 pixels. */
 int dqo_render_backward(const dqo_ctx* ctx, const dqo_frame_desc* desc, const dqo_camera* cams,
                         void* state, const dqo_images* img, const dqo_image_grads* g, void* stream);
 
