@@ -593,12 +593,17 @@ class Rasterizer:
 
     def _post_status(self, stream):
         """Enqueues a copy of the frame's status word and pair count to pinned
-        host words, for _wait_status."""
+        host words, for _wait_status.  (A frame on another device than the
+        current one, whose copy would run on another stream than its kernels:
+        reads them at once and returns them.)"""
+        if self.frame.state.device.index != torch.cuda.current_device():
+            return self.frame.read_status(stream)[1:]
         if stream is not None and stream != torch.cuda.current_stream():
             with torch.cuda.stream(stream):
                 return self._post_status(None)
         self._words.copy_(self.frame.control_words, non_blocking=True)
         self._words_event.record()
+        return None
 
     def _wait_status(self):
         """(status word, pair count) as of _post_status; waits for that copy
@@ -623,11 +628,11 @@ class Rasterizer:
             if not grow:
                 f.sort(stream)
                 return
-            self._post_status(stream)
+            read = self._post_status(stream)
             try:
                 f.sort(stream)
             finally:
-                st, npairs = self._wait_status()
+                st, npairs = read or self._wait_status()
             if grown or not st & STATUS_OVERFLOW:
                 break
             # the sort is done with the short list before its memory is given

@@ -1,8 +1,8 @@
 """GPU: tiles of one to four 64-pixel parts.  Every tile shape renders the
 8x8 images (ragged sizes, windows), and the gradients agree with the 8x8 ones
 with and without instance channels, where the backward runs through the suffix
-pass (up to 8192 parts; ranges of many segments) and where it walks whole
-tiles.  The shapes differ in FP32 summing order only: the parity tolerance."""
+pass (up to 4096 parts; ranges of many segments) and where it walks whole
+tiles, by strips or, with channels and more than 8192 parts, in chunks.  The shapes differ in FP32 summing order only: the parity tolerance."""
 import numpy as np
 import pytest
 import torch
@@ -34,10 +34,11 @@ def _upstream(V, H, W, K, probs):
     return up
 
 
-# 128x96 at 30k Gaussians: ranges of many segments; 515x389: 3,185 parts a view,
-# three views are above the suffix pass's limit; windows leave parts empty
+# 125x91 at 30k Gaussians: ranges of many segments, windows leave parts empty;
+# 515x389: 3,185 parts a view, so one view goes through the suffix pass, two
+# are above its limit, and three take the chunked walk with channels
 @pytest.mark.parametrize("probs", [False, True])
-@pytest.mark.parametrize("n,W,H,V,windows", [(30000, 125, 91, 1, [(3, 5, 120, 91)]), (20000, 515, 389, 2, None),
+@pytest.mark.parametrize("n,W,H,V,windows", [(30000, 125, 91, 1, [(3, 5, 120, 91)]), (20000, 515, 389, 1, None), (20000, 515, 389, 2, None),
                                              (6000, 515, 389, 3, None)])
 def test_tile_shapes_agree(n, W, H, V, windows, probs):
     K = 5
