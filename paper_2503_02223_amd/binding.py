@@ -9,6 +9,7 @@ from __future__ import annotations
 import ctypes
 import math
 import os
+import weakref
 from typing import Dict, List, Optional, Sequence
 
 import numpy as np
@@ -572,6 +573,24 @@ def default_lrs(scene_extent: float = 1.0):
     return [1.6e-4 * scene_extent] * 3 + [5e-3] * 3 + [1e-3] * 4 + [5e-2] + [2.5e-3] * 3
 
 
+# Pinned words for the status copies.  Allocating pinned memory takes some 300
+# us, so 256 Rasterizers share a block of 16 KB, 64 bytes each, which come back
+# when a Rasterizer goes; there are as many blocks as the most Rasterizers
+# alive at once needed.
+_status_words: list = []
+
+
+def _take_status_words(owner):
+    while True:
+        try:
+            words = _status_words.pop()
+            break
+        except IndexError:   # (two threads may both allocate: harmless)
+            _status_words.extend(torch.empty(256, 16, dtype=torch.int32, pin_memory=True)[:, :3].unbind(0))
+    weakref.finalize(owner, _status_words.append, words).atexit = False
+    return words
+
+
 class Rasterizer:
     """Frame + image buffers for a fixed camera set, with capacity management."""
 
@@ -584,7 +603,7 @@ class Rasterizer:
         cap = capacity if capacity is not None else max(1024, 4 * n * (len(cams) if segments is None else 1))
         self.frame = self._new_frame(min(cap, 1 << 30))
         self.generation = 0   # bumped by every bin(): identifies the pair list in the state
-        self._words = torch.empty(3, dtype=torch.int32, pin_memory=True)  # of _post_status
+        self._words = _take_status_words(self)   # of _post_status
         self._words_event = torch.cuda.Event()
 
     def _new_frame(self, capacity):
