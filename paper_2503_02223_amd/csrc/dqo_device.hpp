@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "dqo.h"
+#include "segments.hpp"
 
 namespace dqo {
 
@@ -48,9 +49,6 @@ inline int64_t split_count_words(int64_t items) {  // counts per block and digit
 // 8 wavefronts emits the pairs of its own 64 records (with the first pair
 // pass fused, two blocks share a CU: 35.8 -> 34.4 us at the 200k view against
 // 1024; 256 per block: 46.5 us).
-constexpr int kSegLen = 64;        // pairs per backward segment of a 64-pixel tile
-constexpr int kSegMax = 255;       // segments per tile (the last one takes the rest of the range)
-constexpr uint32_t kNoBoundary = 0xFFFFFFFFu;  // segment-list entry of a tile's last segment: no restart
 // Pair values are item indices; the render forward sets this bit on the pairs
 // whose Gaussian cannot contribute at any pixel of their tile, and the render
 // backward skips those pairs without loading their records.
@@ -157,9 +155,6 @@ struct Consts {
     T bg[3];
 };
 
-// Segments of a tile's pair range for the segmented backward (0 for an empty
-// tile); the last one takes the rest of the range when a tile has more than
-// kSegMax.
 // Segmenting the backward pays where there are few tiles for the machine (the
 // longest ranges then finish last); with more tiles than this the grid is
 // balanced by tiles alone and the boundary states, the list and the restarts
@@ -172,15 +167,6 @@ constexpr int kSegTilesMax = 8192;
 // and 177 / 174, 7680 198 / 158; with instance channels, 8x8 tiles: 1200 210 /
 // 272, 4800 198 / 179, 16x16 tiles: 4800 224 / 235, 16x8: 7680 245 / 208).
 constexpr int kSuffixPartsMax = 4096;
-// The boundary state at pair position b (a multiple of kSegLen past its
-// tile's first position rs) is record rs / kSegLen + (b - rs) / kSegLen: the
-// records of different tiles never meet (a tile of n pairs has fewer than
-// n / kSegLen boundaries and the next starts n positions later), and they
-// stay below capacity / kSegLen + 1.
-__host__ __device__ constexpr uint32_t boundary_record(uint32_t rs, uint32_t k) { return rs / kSegLen + k; }
-__device__ __forceinline__ uint32_t tile_segments(uint32_t range) {
-    return min((range + kSegLen - 1) / (uint32_t)kSegLen, (uint32_t)kSegMax);
-}
 
 // Look-back words: [flag:2 | epoch:30 | value:32].
 constexpr uint64_t kFlagAggregate = 1ull;

@@ -261,7 +261,8 @@ __global__ __launch_bounds__(kWave) void render_forward_kernel(
     // the pixel centre relative to the tile's corner
     const T u = T(lx) + T(0.5), v = T(ly) + T(0.5);
     const T ox = T(tx * TW), oy = T(ty * TH);
-    const uint32_t re = min(ranges[2 * tile + 1], cap), rs = min(ranges[2 * tile], re);
+    const PairRange range = tile_range(ranges[2 * tile], ranges[2 * tile + 1], cap);
+    const uint32_t rs = range.rs, re = range.re;
     const uint32_t sbase = (kSeg && ckpt) ? seg_base[tile] : 0u;  // used at the end
     int tgt = -2;
     if (target && in_img) tgt = job_target(V.cam[view].job, target[view * HW + pix]);
@@ -891,8 +892,9 @@ __global__ __launch_bounds__(kWave, 4) void render_backward_wave_kernel(
     const T* __restrict__ tfinal, const int32_t* __restrict__ last, const int32_t* __restrict__ target,
     const T* __restrict__ dC, const T* __restrict__ dD, const T* __restrict__ dT, const T* __restrict__ dP,
     const T* __restrict__ dPt, T* __restrict__ partials, uint8_t* __restrict__ written, uint32_t cap, uint32_t M,
-    const uint4* __restrict__ seg_list, const T* __restrict__ ckpt, uint32_t ckpt_cap, const T* __restrict__ color,
-    const T* __restrict__ depth, const T* __restrict__ ptarget, const Ctrl* __restrict__ ctrl) {
+    const uint4* __restrict__ seg_list, uint32_t seg_cap, const T* __restrict__ ckpt, uint32_t ckpt_cap,
+    const T* __restrict__ color, const T* __restrict__ depth, const T* __restrict__ ptarget,
+    const Ctrl* __restrict__ ctrl) {
     static_assert(TW * TH == kWave, "one wavefront per tile");
     __shared__ __align__(16) T s_sp[kWave * kWalkWords];
     __shared__ uint32_t s_slot[kWave];
@@ -912,7 +914,7 @@ __global__ __launch_bounds__(kWave, 4) void render_backward_wave_kernel(
     if (seg_list && (ctrl->seg_stamp[0] != (uint64_t)ctrl->epoch || ctrl->seg_stamp[1] != (uint64_t)(uintptr_t)last ||
                      ctrl->seg_stamp[2] != (uint64_t)(uintptr_t)target))
         seg_list = nullptr;
-    const uint32_t n_units = seg_list ? ctrl->counters[kCounterSegTotal] : n_tiles;
+    const uint32_t n_units = seg_list ? listed_segments(ctrl->counters[kCounterSegTotal], seg_cap) : n_tiles;
     uint32_t unit = blockIdx.x;
     if (SEG && seg_list) unit = seg_unit(blockIdx.x);
     if (unit >= n_units) return;
@@ -1037,7 +1039,8 @@ __global__ __launch_bounds__(kWave) void suffix_state_kernel(
     const T u = T(lx) + T(0.5), vp = T(ly) + T(0.5);
     const T ox = T(tx * TW), oy = T(ty * TH);
     const int64_t HW = (int64_t)V.W * V.H, pix = (int64_t)py * V.W + px;
-    const uint32_t re = min(ranges[2 * tile + 1], cap), rs = min(ranges[2 * tile], re);
+    const PairRange range = tile_range(ranges[2 * tile], ranges[2 * tile + 1], cap);
+    const uint32_t rs = range.rs, re = range.re;
     if (part == 0) {
         const uint32_t nseg = tile_segments(re - rs), base = seg_base[tile];
         for (uint32_t j = (uint32_t)lane; j < nseg; j += kWave)
@@ -1168,7 +1171,7 @@ __global__ __launch_bounds__(TW* TH, sizeof(T) == 8 ? 1 : SUF || PROBS ? 3 : 4) 
     const T* __restrict__ tfinal, const int32_t* __restrict__ last, const int32_t* __restrict__ target,
     const T* __restrict__ dC, const T* __restrict__ dD, const T* __restrict__ dT, const T* __restrict__ dP,
     const T* __restrict__ dPt, T* __restrict__ partials, uint8_t* __restrict__ written, uint32_t cap, uint32_t M,
-    const uint2* __restrict__ suf_list, const T* __restrict__ suffix, uint32_t suf_cap,
+    const uint2* __restrict__ suf_list, uint32_t seg_cap, const T* __restrict__ suffix, uint32_t suf_cap,
     const int32_t* __restrict__ tile_last, const Ctrl* __restrict__ ctrl) {
     constexpr int NW = TW * TH / kWave, kRows = kWave / TW;
     static_assert(NW >= 1 && NW <= 4 && kWave % TW == 0, "strips of whole rows");
@@ -1188,14 +1191,15 @@ __global__ __launch_bounds__(TW* TH, sizeof(T) == 8 ? 1 : SUF || PROBS ? 3 : 4) 
     uint32_t seg = 0u;
     if constexpr (SUF) {
         const uint32_t unit = seg_unit(blockIdx.x);
-        if (unit >= ctrl->counters[kCounterSegTotal]) return;
+        if (unit >= listed_segments(ctrl->counters[kCounterSegTotal], seg_cap)) return;
         const uint2 en = suf_list[unit];
         tile = (int)min(en.x, n_tiles - 1u);
         seg = en.y;
     } else {
         tile = (int)min(schedule[blockIdx.x], n_tiles - 1u);
     }
-    const uint32_t re = min(ranges[2 * tile + 1], cap), rs = min(ranges[2 * tile], re);
+    const PairRange range = tile_range(ranges[2 * tile], ranges[2 * tile + 1], cap);
+    const uint32_t rs = range.rs, re = range.re;
     // the pairs walked here: [s0, hi), up to the tile's last blended position;
     // pixels that blend past s1 start from the state stored behind it
     uint32_t s0 = rs, s1 = re, hi = rs;
@@ -1204,12 +1208,12 @@ __global__ __launch_bounds__(TW* TH, sizeof(T) == 8 ? 1 : SUF || PROBS ? 3 : 4) 
         int tl = -1;
 #pragma unroll
         for (int w = 0; w < NW; ++w) tl = max(tl, tile_last[tile * NW + w]);
-        s0 = rs + seg * (uint32_t)kSegLen;
-        const bool tail = seg + 1u >= tile_segments(re - rs);  // takes the rest of the range
-        s1 = tail ? re : s0 + (uint32_t)kSegLen;
-        if (tl < (int)s0) return;  // behind every pixel's last blended position (uniform)
-        hi = min((uint32_t)tl + 1u, s1);
-        past = tl >= (int)s1;
+        const SegmentWalk sw = segment_walk(range, seg, tl);
+        if (sw.hi == sw.s0) return;  // behind every pixel's last blended position (uniform)
+        s0 = sw.s0;
+        s1 = sw.s1;
+        hi = sw.hi;
+        past = sw.past;
     }
     const int view = tile / V.tiles_per_view;
     const int t = tile - view * V.tiles_per_view;
@@ -1431,7 +1435,8 @@ __global__ __launch_bounds__(TW* TH) void render_backward_kernel(
     // the pixel centre relative to the tile's corner
     const T u = T(tid % TW) + T(0.5), v_px = T(tid / TW) + T(0.5);
     const T ox = T(tx * TW), oy = T(ty * TH);
-    const uint32_t re = min(ranges[2 * tile + 1], cap), rs = min(ranges[2 * tile], re);
+    const PairRange range = tile_range(ranges[2 * tile], ranges[2 * tile + 1], cap);
+    const uint32_t rs = range.rs, re = range.re;
 
     int lastp = -1;
     T Tcur = T(1), gc0 = T(0), gc1 = T(0), gc2 = T(0), gd = T(0), gt = T(0), gpt = T(0);
@@ -1623,7 +1628,7 @@ static hipError_t bwd_parts(const Frame<T>& f, const dqo_images& img, const dqo_
                        s.pair_vals[0], s.ranges, s.schedule, (const T*)img.t_final, img.last, img.target,
                        (const T*)g.d_color, (const T*)g.d_depth, (const T*)g.d_t_final, (const T*)g.d_probs,
                        (const T*)g.d_p_target, (T*)s.partials, s.written, (uint32_t)s.capacity, (uint32_t)s.items,
-                       s.suf_list, (const T*)s.suffix, (uint32_t)s.suf_cap, s.tile_last, s.ctrl);
+                       s.suf_list, (uint32_t)s.seg_cap, (const T*)s.suffix, (uint32_t)s.suf_cap, s.tile_last, s.ctrl);
     return hipGetLastError();
 }
 
@@ -1650,8 +1655,8 @@ static hipError_t bwd_tile(const Frame<T>& f, const dqo_images& img, const dqo_i
                            s.pair_vals[0], s.ranges, s.schedule, (const T*)img.t_final, img.last, img.target,
                            (const T*)g.d_color, (const T*)g.d_depth, (const T*)g.d_t_final, (const T*)g.d_probs,
                            (const T*)g.d_p_target, (T*)s.partials, s.written, (uint32_t)s.capacity,
-                           (uint32_t)s.items, seg ? s.seg_list : nullptr, (const T*)s.ckpt, (uint32_t)s.ckpt_cap,
-                           (const T*)img.color, (const T*)img.depth, (const T*)img.p_target, s.ctrl);
+                           (uint32_t)s.items, seg ? s.seg_list : nullptr, (uint32_t)s.seg_cap, (const T*)s.ckpt,
+                           (uint32_t)s.ckpt_cap, (const T*)img.color, (const T*)img.depth, (const T*)img.p_target, s.ctrl);
         return hipGetLastError();
     } else {
         return g.d_probs ? bwd_parts<T, TW, TH, true>(f, img, g, st) : bwd_parts<T, TW, TH, false>(f, img, g, st);

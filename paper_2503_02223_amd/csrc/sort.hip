@@ -566,7 +566,8 @@ constexpr int kSchedBins = 4096;
 constexpr int kSchedRegs = 8;
 __global__ __launch_bounds__(kSchedThreads) void tile_schedule_kernel(const uint32_t* __restrict__ ranges,
                                                                      int tiles, uint32_t* __restrict__ schedule,
-                                                                     int seg, uint32_t* __restrict__ seg_base,
+                                                                     uint32_t cap, int seg,
+                                                                     uint32_t* __restrict__ seg_base,
                                                                      Ctrl* __restrict__ ctrl) {
     __shared__ uint32_t s_cnt[kSchedBins];  // bin b holds count kSchedBins - 1 - b (descending order)
     // segmented backward: the segments of each bin's tiles, then the bin's
@@ -577,8 +578,9 @@ __global__ __launch_bounds__(kSchedThreads) void tile_schedule_kernel(const uint
     const int tid = threadIdx.x;
     auto bin_of_w = [](uint32_t w) { return kSchedBins - 1 - (int)min(w, (uint32_t)(kSchedBins - 1)); };
     auto width = [&](int t) {
-        const uint2 r = reinterpret_cast<const uint2*>(ranges)[t];
-        return r.y - r.x;
+        const uint2 b = reinterpret_cast<const uint2*>(ranges)[t];
+        const PairRange r = tile_range(b.x, b.y, cap);  // as the render kernels see it
+        return r.re - r.rs;
     };
     // thread tid holds tiles tid + k * kSchedThreads (coalesced loads)
     const bool regs = tiles <= kSchedRegs * kSchedThreads;
@@ -747,7 +749,8 @@ __global__ __launch_bounds__(kTileSortThreads) void tile_sort_kernel(const uint3
     if (*n_dev > cap) return;  // the list overflowed: its ranges mean nothing
     const int tid = threadIdx.x;
     const uint32_t tile = min(schedule[blockIdx.x], (uint32_t)(tiles - 1));
-    const uint32_t re = min(ranges[2 * tile + 1], cap), rs = min(ranges[2 * tile], re);
+    const PairRange range = tile_range(ranges[2 * tile], ranges[2 * tile + 1], cap);
+    const uint32_t rs = range.rs, re = range.re;
     const uint32_t n = re - rs;
     if (n <= 1u) return;
     if (n <= min(lds_max, (uint32_t)kTileSortLds)) {
@@ -870,7 +873,8 @@ hipError_t launch_pair_sort(const StatePtrs& s, int tiles_total, hipStream_t st)
                            (uint32_t)tiles_total, s.ranges,
                            (uint32_t*)s.written);
         hipLaunchKernelGGL(tile_schedule_kernel, dim3(1), dim3(kSchedThreads), 0, st, s.ranges, tiles_total,
-                           s.schedule, segmented_backward(s, tiles_total) || suffix_backward(s) ? 1 : 0, s.seg_base, s.ctrl);
+                           s.schedule, cap, segmented_backward(s, tiles_total) || suffix_backward(s) ? 1 : 0, s.seg_base,
+                           s.ctrl);
         if (s.tile_sort)
             hipLaunchKernelGGL(tile_sort_kernel, dim3((unsigned)tiles_total), dim3(kTileSortThreads), 0, st, s.ranges,
                                s.schedule, s.depth_keys[0], (uint32_t)s.items, cap, (uint32_t)s.tile_sort_lds,
