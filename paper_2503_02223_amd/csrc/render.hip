@@ -1126,9 +1126,11 @@ __global__ __launch_bounds__(kWave) void suffix_state_kernel(
 #pragma unroll
             for (int q = 0; q < G; ++q) {
                 const int id = word_to_id<T>(bl[q][kWId - kWZ]);
+                // only where the record blends, as in the gradient walk: the
+                // gradient of a probability that is zero may be infinite or NaN
                 dp[q] = T(0);
                 if constexpr (PROBS) {
-                    if ((uint32_t)id < (uint32_t)K) dp[q] = s_dP[id * kWave + lane];
+                    if (a[q] != T(0) && (uint32_t)id < (uint32_t)K) dp[q] = s_dP[id * kWave + lane];
                 }
             }
 #pragma unroll
