@@ -574,21 +574,28 @@ def default_lrs(scene_extent: float = 1.0):
 
 
 # Pinned words for the status copies.  Allocating pinned memory takes some 300
-# us, so 256 Rasterizers share a block of 16 KB, 64 bytes each, which come back
-# when a Rasterizer goes; there are as many blocks as the most Rasterizers
-# alive at once needed.
+# us, so 256 of them share a block of 16 KB, 64 bytes each, which come back
+# when their holder goes; there are as many blocks as the most holders alive at
+# once needed.
 _status_words: list = []
 
 
-def _take_status_words(owner):
-    while True:
-        try:
-            words = _status_words.pop()
-            break
-        except IndexError:   # (two threads may both allocate: harmless)
-            _status_words.extend(torch.empty(256, 16, dtype=torch.int32, pin_memory=True)[:, :3].unbind(0))
-    weakref.finalize(owner, _status_words.append, words).atexit = False
-    return words
+class _StatusWords:
+    """Pinned words that one Rasterizer at a time holds (a copy of it holds them
+    with it).  The block is a plain host tensor whatever device or inference
+    mode its first user runs under, since later users share it."""
+
+    def __init__(self):
+        while True:
+            try:
+                self.words = _status_words.pop()
+                break
+            except IndexError:   # (two threads may both allocate: harmless)
+                with torch.inference_mode(False), torch.no_grad():
+                    block = torch.empty(256, 16, dtype=torch.int32, device="cpu", pin_memory=True)
+                    _status_words.extend(block[:, :3].unbind(0))
+        weakref.finalize(self, _status_words.append, self.words).atexit = False
+        self.event = torch.cuda.Event()
 
 
 class Rasterizer:
@@ -603,8 +610,7 @@ class Rasterizer:
         cap = capacity if capacity is not None else max(1024, 4 * n * (len(cams) if segments is None else 1))
         self.frame = self._new_frame(min(cap, 1 << 30))
         self.generation = 0   # bumped by every bin(): identifies the pair list in the state
-        self._words = _take_status_words(self)   # of _post_status
-        self._words_event = torch.cuda.Event()
+        self._status = None   # of _post_status
 
     def _new_frame(self, capacity):
         return Frame(self.ctx, self.cams, self.n, self.K, capacity, self.dtype, self.device, segments=self.segments,
@@ -620,15 +626,17 @@ class Rasterizer:
         if stream is not None and stream != torch.cuda.current_stream():
             with torch.cuda.stream(stream):
                 return self._post_status(None)
-        self._words.copy_(self.frame.control_words, non_blocking=True)
-        self._words_event.record()
+        if self._status is None:
+            self._status = _StatusWords()
+        self._status.words.copy_(self.frame.control_words, non_blocking=True)
+        self._status.event.record()
         return None
 
     def _wait_status(self):
         """(status word, pair count) as of _post_status; waits for that copy
         only, not for what was enqueued after it."""
-        self._words_event.synchronize()
-        st, _, npairs = self._words.tolist()
+        self._status.event.synchronize()
+        st, _, npairs = self._status.words.tolist()
         return st & 0xFFFFFFFF, npairs & 0xFFFFFFFF
 
     def bin(self, params, ids, grow=True, stream=None):
