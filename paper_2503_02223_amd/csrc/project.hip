@@ -707,7 +707,7 @@ __device__ __forceinline__ T segmented_scan(T v, int lane, int seg_lo) {
 
 template <typename T>
 __global__ __launch_bounds__(kSlotWaves * kWave) void slot_sum_kernel(const uint32_t* __restrict__ order,
-                                                                      const uint32_t* __restrict__ n_pairs,
+                                                                      const uint32_t* __restrict__ counts,
                                                                       const uint32_t* __restrict__ offsets,
                                                                       const T* __restrict__ partials,
                                                                       const uint8_t* __restrict__ written, uint32_t listed,
@@ -718,18 +718,18 @@ __global__ __launch_bounds__(kSlotWaves * kWave) void slot_sum_kernel(const uint
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
     const uint64_t lt = lane ? (~0ull >> (kWave - lane)) : 0ull;
     const uint32_t q = ((uint32_t)blockIdx.x * kSlotWaves + wave) * kWave + lane;
-    uint32_t rec = 0, off = 0, end = 0;
-    const uint32_t pairs = *n_pairs;
+    // An item's slots end where the next one's begin, which the lane above
+    // holds; the wave's last item takes its tile count (not the next wave's
+    // offset: the scan may have given up a wait in between, and its slots
+    // would then reach to the list's end).
+    uint32_t rec = 0, off = 0, c = 0;
     if (q < listed) {
         rec = order ? min(order[q], M - 1) : q;  // emission order: depth order, or item order
         off = offsets[rec];
-        // an item's slots end where the next one's begin
-        end = pairs;
-        if (lane == kWave - 1 && q + 1u < listed) end = offsets[order ? min(order[q + 1u], M - 1) : q + 1u];
+        if (lane == kWave - 1 || q + 1u == listed) c = counts[rec];
     }
     const uint32_t next_off = __shfl_down(off, 1);
-    if (lane < kWave - 1 && q + 1u < listed) end = next_off;
-    const uint32_t c = q < listed ? end - off : 0u;
+    if (lane < kWave - 1 && q + 1u < listed) c = next_off - off;
 #pragma unroll
     for (int k = 0; k < kGradWords; ++k) s_acc[wave][lane][k] = T(0);
     const bool has = c > 0;
@@ -801,7 +801,7 @@ static void launch_slot_sums(const Frame<T>& f, hipStream_t st) {
     constexpr int kItems = kSlotWaves * kWave;
     if (s.listed == 0) return;
     hipLaunchKernelGGL(slot_sum_kernel<T>, dim3((unsigned)((s.listed + kItems - 1) / kItems)), dim3(kItems), 0, st,
-                       item_order(s), &s.ctrl->num_pairs, s.offsets, (const T*)s.partials, s.written, (uint32_t)s.listed,
+                       item_order(s), s.counts, s.offsets, (const T*)s.partials, s.written, (uint32_t)s.listed,
                        (uint32_t)s.items, (uint32_t)s.capacity, (T*)s.sums);
 }
 
