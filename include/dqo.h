@@ -149,14 +149,14 @@ typedef struct dqo_frame_desc {
 enum dqo_buf {
     DQO_BUF_SPLATS = 0,  /* [V*n] records of 16 values: mx,my,A,B,C,opacity,z,id,r,g,b,0, first pair slot,
                             tile rectangle x0 | y0 << 16, rectangle width, 0 (integers as FP32 bit patterns,
-                            FP64 values); written for the listed items */
+                            FP64 values); all zero for unlisted items */
     DQO_BUF_RECTS,       /* [V*n] int16x4 tile rectangle x0,y0,x1,y1 (inclusive), empty = x1<x0 */
     DQO_BUF_COUNTS,      /* [V*n] uint32 tiles covered */
-    DQO_BUF_OFFSETS,     /* [V*n] uint32 first slot of the item's pairs in emission order (listed items) */
-    DQO_BUF_DEPTH_KEYS,  /* [V*n] uint32 sorted depth keys (float bits of z; culled = 0xffffffff), one per
-                            listed item */
+    DQO_BUF_OFFSETS,     /* [V*n] uint32 first slot of the item's pairs in emission order */
+    DQO_BUF_DEPTH_KEYS,  /* [V*n] uint32 sorted depth keys (float bits of z; culled and unlisted =
+                            0xffffffff); at their item index under the TILE depth order */
     DQO_BUF_DEPTH_ORDER, /* [V*n] uint32 item index (view*n + g) in depth order (GLOBAL depth order only),
-                            one per listed item */
+                            the unlisted items last */
     DQO_BUF_PAIR_KEYS,   /* [cap] uint32 sorted global tile id (view*tiles + tile) */
     DQO_BUF_PAIR_VALS,   /* [cap] uint32 item index, in (tile, depth, index) order; after a render
                             forward, bit 31 is set on the pairs whose Gaussian cannot contribute at

@@ -75,6 +75,7 @@ constexpr int kCounterScan = 4;    // scan + emission blocks (ticket order after
 constexpr int kCounterPair = 5;    // + pass
 constexpr int kCounterAdam = 12;   // workgroups done in the fused project-backward + Adam
 constexpr int kCounterSegTotal = 13;  // entries in the backward's segment list
+constexpr int kCounterUnlisted = 14;  // workgroups done with the unlisted items
 constexpr int kNumCounters = 16;
 constexpr int kHistCopies = 16;
 constexpr int kProjItems = 4;      // items per thread of the projection kernel
@@ -101,6 +102,10 @@ struct Ctrl {
     // workgroup w adds to copy w mod kHistCopies): max of ~key (so that the
     // cleared word is neutral) and max of key.
     uint32_t dkey_range[kHistCopies][2];
+    // The segments (first << 32 | end) whose unlisted items the state's buffers
+    // hold, and the number of views with the depth order's bit (0: none).
+    uint64_t listing[DQO_MAX_VIEWS];
+    uint32_t listing_of;
 };
 
 template <typename T>

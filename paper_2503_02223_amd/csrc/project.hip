@@ -23,9 +23,10 @@ namespace dqo {
 
 // Starts a frame: new look-back epoch, counters and the histogram copies in
 // use cleared (workgroup c clears copy c of each).
-__global__ __launch_bounds__(256) void prep_kernel(Ctrl* ctrl, int copies_depth, int copies_pair) {
+__global__ __launch_bounds__(256) void prep_kernel(Ctrl* ctrl, int copies_depth, int copies_pair, int all_listed) {
     const int t = threadIdx.x, c = blockIdx.x;
     if (c == 0) {
+        if (t == 0 && all_listed) ctrl->listing_of = 0u;
         if (t == 0) ctrl->epoch = ctrl->epoch + 1u;
         if (t < kNumCounters) ctrl->counters[t] = 0u;
         if (t == 0) ctrl->num_pairs = 0u;
@@ -222,16 +223,6 @@ __global__ __launch_bounds__(256) void project_kernel(Views<T> V, Consts<T> cs, 
             }
         }
     }
-    // Items outside their view's segment cover no tile.
-    if (listed != (uint32_t)(V.n_views * n))
-        for (int v = 0; v < V.n_views; ++v) {
-            const int64_t lo = V.cam[v].seg_lo, cnt = V.cam[v].seg_hi - lo;
-            for (int64_t k = (int64_t)blockIdx.x * 256 + tid; k < n - cnt; k += (int64_t)gridDim.x * 256) {
-                const int64_t i = (int64_t)v * n + (k < lo ? k : k + cnt);
-                counts[i] = 0u;
-                rects[i] = make_short4(0, 0, -1, -1);
-            }
-        }
 #pragma unroll
     for (int d = 1; d < kWave; d <<= 1) {
         kmin_inv = max(kmin_inv, (uint32_t)__shfl_xor(kmin_inv, d));
@@ -252,6 +243,76 @@ __global__ __launch_bounds__(256) void project_kernel(Views<T> V, Consts<T> cs, 
         const uint32_t c = block_exclusive_scan<256>(d, s_tmp) + d + s_pall;
         if (c) atomicAdd(&pair_hist0[(size_t)(blockIdx.x % copies_pair) * kMaxPairPasses * kRadixBins + tid], c);
     }
+}
+
+// Items outside their view's segment, in every buffer that holds one entry per
+// item: no tiles, an empty record, the depth key of a culled item, a place
+// behind the listed items in the depth order, and as first slot that of the
+// next item in emission order.  All but the first slots depend on the segments
+// alone, so they are written when the segments differ from the frame's before
+// (a stamp in the state, written by the last workgroup): 88 bytes per item
+// then, 4 otherwise.
+template <typename T>
+__global__ __launch_bounds__(256) void unlisted_items_kernel(Views<T> V, int64_t n, uint32_t listed, int item_order,
+                                                             T* __restrict__ splats, short4* __restrict__ rects,
+                                                             uint32_t* __restrict__ counts,
+                                                             uint32_t* __restrict__ dkeys,
+                                                             uint32_t* __restrict__ dvals, uint32_t* offsets,
+                                                             Ctrl* ctrl) {
+    __shared__ uint32_t s_same, s_slot[2];
+    const int v = blockIdx.y, tid = threadIdx.x;
+    const int64_t lo = V.cam[v].seg_lo, hi = V.cam[v].seg_hi, first = (int64_t)v * n, cnt = n - (hi - lo);
+    const uint32_t listing_of = (uint32_t)V.n_views | (item_order ? 0x100u : 0u);
+    auto segment = [&](int k) { return (uint64_t)V.cam[k].seg_lo << 32 | (uint64_t)V.cam[k].seg_hi; };
+    if (tid == 0) {
+        bool same = ctrl->listing_of == listing_of;
+        for (int k = 0; k < V.n_views; ++k) same = same && ctrl->listing[k] == segment(k);
+        s_same = same ? 1u : 0u;
+    }
+    if (tid < 2) {  // in depth order they follow every pair
+        const uint32_t q = V.list_off[v + tid];
+        uint32_t slot = ctrl->num_pairs;
+        if (item_order && q < listed) {
+            const int u = listed_view(V, q);
+            slot = offsets[(int64_t)u * n + V.cam[u].seg_lo + (q - V.list_off[u])];
+        }
+        s_slot[tid] = slot;
+    }
+    __syncthreads();
+    const bool same = s_same != 0u;
+    const int64_t step = (int64_t)gridDim.x * 256, t0 = (int64_t)blockIdx.x * 256 + tid;
+    const int64_t place = (int64_t)listed + first - V.list_off[v];
+    for (int64_t k = t0; k < cnt; k += step) {
+        const int64_t i = first + (k < lo ? k : k + (hi - lo));
+        offsets[i] = s_slot[k < lo ? 0 : 1];
+        if (same) continue;
+        counts[i] = 0u;
+        rects[i] = make_short4(0, 0, -1, -1);
+        dkeys[item_order ? i : place + k] = 0xffffffffu;
+        dvals[place + k] = (uint32_t)i;
+    }
+    if (same) return;  // uniform
+    constexpr int64_t kPieces = kSplatWords * sizeof(T) / sizeof(float4);
+    float4* sp = reinterpret_cast<float4*>(splats);
+    const float4 zero = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    for (int64_t k = t0; k < lo * kPieces; k += step) sp[first * kPieces + k] = zero;
+    for (int64_t k = t0; k < (n - hi) * kPieces; k += step) sp[(first + hi) * kPieces + k] = zero;
+    if (tid == 0 && atomicAdd(&ctrl->counters[kCounterUnlisted], 1u) == gridDim.x * gridDim.y - 1u) {
+        // every workgroup has read the stamp
+        for (int k = 0; k < V.n_views; ++k) ctrl->listing[k] = segment(k);
+        ctrl->listing_of = listing_of;
+    }
+}
+
+template <typename T>
+static hipError_t launch_unlisted_items(const Frame<T>& f, hipStream_t st) {
+    const StatePtrs& s = f.s;
+    if (s.listed == s.items) return hipGetLastError();
+    const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>(512, (f.n + 255) / 256)), (unsigned)f.views.n_views);
+    hipLaunchKernelGGL(unlisted_items_kernel<T>, grid, dim3(256), 0, st, f.views, f.n, (uint32_t)s.listed,
+                       s.tile_sort ? 1 : 0, (T*)s.splats, s.rects, s.counts, s.depth_keys[0], s.depth_vals[0],
+                       s.offsets, s.ctrl);
+    return hipGetLastError();
 }
 
 // Scan of the tile counts in depth order and emission of (tile, item) pairs.
@@ -597,18 +658,18 @@ template <typename T>
 hipError_t launch_project_bin(const Frame<T>& f, const T* params, const int32_t* ids, hipStream_t st) {
     const StatePtrs& s = f.s;
     hipLaunchKernelGGL(prep_kernel, dim3((unsigned)std::max(1, std::max(s.hist_copies_depth, s.hist_copies_pair))),
-                       dim3(256), 0, st, s.ctrl, s.hist_copies_depth, s.hist_copies_pair);
+                       dim3(256), 0, st, s.ctrl, s.hist_copies_depth, s.hist_copies_pair, s.listed == s.items ? 1 : 0);
     const int64_t M = s.items, N = s.listed;
     const int64_t range_words = 2 * (int64_t)f.views.tiles_per_view * f.views.n_views;
     if (M == 0) return launch_zero_words(s.ranges, range_words, st);
-    // (a frame whose segments are all empty still clears its ranges and counts)
+    // (a frame whose segments are all empty still clears its ranges)
     hipLaunchKernelGGL(project_kernel<T>,
                        dim3((unsigned)std::max<int64_t>(1, (N + 256 * kProjItems - 1) / (256 * kProjItems))), dim3(256),
                        0, st, f.views, f.consts,
                        f.n, (uint32_t)N, s.tile_sort ? 1 : 0, params, ids, (T*)s.splats, s.rects, s.counts, s.depth_keys[0], s.depth_vals[0],
                        s.ranges, range_words, s.hist_copies_depth, s.ctrl,
                        s.fused_emit ? &s.ctrl->hist_pair[0][0][0] : nullptr, s.hist_copies_pair);
-    if (N == 0) return hipGetLastError();
+    if (N == 0) return launch_unlisted_items(f, st);
     const int dipt = depth_ipt(N);
     const bool split = !radix_resident(kDepthNt, dipt, N);
     // Buffers of the four passes: 0 -> 1 -> 2 -> 1 -> 0, or 0 -> 1 -> 2 -> 0
@@ -641,7 +702,7 @@ hipError_t launch_project_bin(const Frame<T>& f, const T* params, const int32_t*
                        (uint32_t)M, (uint32_t)s.capacity, f.n, f.views.tiles_x, f.views.tiles_per_view,
                        pair_sort_split(s.capacity) ? 0 : s.pair_passes,
                        s.hist_copies_pair, s.lb_scan, s.ctrl, two_level ? (const uint32_t*)s.scan_base : nullptr);
-    return hipGetLastError();
+    return launch_unlisted_items(f, st);
 }
 
 // ---------------------------------------------------------------- backward
