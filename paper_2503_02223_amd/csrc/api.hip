@@ -143,6 +143,8 @@ Geo geometry(const dqo_ctx* ctx, const dqo_frame_desc* d, const dqo_camera* cams
     g.ckpt_cap = (tw * th == kWave && tiles_total <= kSegTilesMax) ? cap / kSegLen + 1 : 0;
     const int parts = tw * th / kWave;
     g.suf_cap = tiles_total * parts <= kSuffixPartsMax && (parts > 1 || d->K > 0) ? cap / kSegLen + 1 : 0;
+    // (a launch holds fewer than 2^32 work items: 256-pixel tiles at the largest capacities go without)
+    if ((tiles_total + g.suf_cap + 8 * kXcdChunk) * tw * th >= (int64_t(1) << 32)) g.suf_cap = 0;
     g.seg_cap = tiles_total + std::max(g.ckpt_cap, g.suf_cap);
     g.off_seg = so; so = align256(so + g.seg_cap * 16);
     g.off_sgbase = so; so = align256(so + tiles_total * 4);

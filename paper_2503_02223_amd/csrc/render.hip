@@ -570,11 +570,8 @@ __device__ __forceinline__ void flush_slots(T (&v)[64], uint32_t chunk, T* __res
 // head of the list still spread over the device.  Each XCD has its own L2; at
 // the 200k view this cut the backward's HBM reads from 148 to 103 MB (chunks
 // of 4: 116 MB, of 64: 99 MB but slower).
-#ifndef DQO_BWD_XCD_CHUNK
-#define DQO_BWD_XCD_CHUNK 16
-#endif
 __device__ __forceinline__ uint32_t seg_unit(uint32_t b) {
-    constexpr uint32_t c = DQO_BWD_XCD_CHUNK;
+    constexpr uint32_t c = kXcdChunk;
     const uint32_t x = b % 8u, r = b / 8u;
     return ((r / c) * 8u + x) * c + r % c;
 }
@@ -1622,7 +1619,7 @@ static hipError_t bwd_parts(const Frame<T>& f, const dqo_images& img, const dqo_
             return hipGetLastError();
         }
     }
-    const int64_t gq = 8 * DQO_BWD_XCD_CHUNK;  // whole XCD chunks
+    const int64_t gq = 8 * kXcdChunk;  // whole XCD chunks
     const unsigned grid = suf ? (unsigned)((s.seg_cap + gq - 1) / gq * gq) : (unsigned)blocks;
     auto kern = suf ? render_backward_tile_kernel<T, TW, TH, PROBS, true>
                     : render_backward_tile_kernel<T, TW, TH, PROBS, false>;
@@ -1647,7 +1644,7 @@ static hipError_t bwd_tile(const Frame<T>& f, const dqo_images& img, const dqo_i
         const bool seg = segmented_backward(s, blocks) && !img.probs && !g.d_probs && img.color && img.depth &&
                          (img.p_target || !g.d_p_target);
         // units = segments up to each tile's end <= tiles + pairs / kSegLen = seg_cap
-        const int64_t gq = 8 * DQO_BWD_XCD_CHUNK;  // whole XCD chunks
+        const int64_t gq = 8 * kXcdChunk;  // whole XCD chunks
         const unsigned grid = seg ? (unsigned)((std::max<int64_t>(s.seg_cap, blocks) + gq - 1) / gq * gq)
                                   : (unsigned)blocks;
         auto kern = g.d_probs ? render_backward_wave_kernel<T, TW, TH, true, false>
