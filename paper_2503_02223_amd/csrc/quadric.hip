@@ -7,6 +7,8 @@
 // Jacobi SVD rotates column pairs with three wave-wide dot products per pair,
 // and lanes 0-9 carry the rows of the accumulated right rotation V.  The
 // solution is the column of V whose rotated column of A has the least norm.
+#include <algorithm>
+
 #include "dqo_device.hpp"
 #include "wave_f64.hpp"
 
@@ -287,7 +289,7 @@ __global__ __launch_bounds__(kBoxThreads) void id_boxes_clear_kernel(int n, int 
 __global__ __launch_bounds__(kBoxThreads) void id_boxes_kernel(const int32_t* __restrict__ id_map, int W, int H, int K,
                                                                int* __restrict__ boxes) {
     __shared__ __align__(16) int s_box[DQO_MAX_K][4];
-    const int v = blockIdx.y, y0 = blockIdx.x * kBoxRows, y1 = min(H, y0 + kBoxRows);
+    const int v = blockIdx.y;
     for (int k = threadIdx.x; k < K; k += kBoxThreads) {
         s_box[k][0] = W;
         s_box[k][1] = H;
@@ -296,20 +298,23 @@ __global__ __launch_bounds__(kBoxThreads) void id_boxes_kernel(const int32_t* __
     }
     __syncthreads();
     const int32_t* im = id_map + (int64_t)v * W * H;
-    for (int x0 = 0; x0 < W; x0 += kBoxThreads) {
-        const int u = x0 + (int)threadIdx.x;
-        int id[kBoxRows];  // a column of the strip: its loads are in flight together
+    for (int64_t y0 = (int64_t)blockIdx.x * kBoxRows; y0 < H; y0 += (int64_t)gridDim.x * kBoxRows) {
+        const int y1 = (int)min((int64_t)H, y0 + kBoxRows);
+        for (uint32_t x0 = 0; x0 < (uint32_t)W; x0 += kBoxThreads) {
+            const uint32_t u = x0 + threadIdx.x;
+            int id[kBoxRows];  // a column of the strip: its loads are in flight together
 #pragma unroll
-        for (int r = 0; r < kBoxRows; ++r) id[r] = (u < W && y0 + r < y1) ? im[(int64_t)(y0 + r) * W + u] : -1;
+            for (int r = 0; r < kBoxRows; ++r) id[r] = (u < (uint32_t)W && y0 + r < y1) ? im[(y0 + r) * W + u] : -1;
 #pragma unroll
-        for (int r = 0; r < kBoxRows; ++r) {
-            const int k = id[r], y = y0 + r;
-            if (k < 0 || k >= K) continue;
-            const int4 c = *reinterpret_cast<const int4*>(s_box[k]);
-            if (u < c.x) atomicMin(&s_box[k][0], u);
-            if (y < c.y) atomicMin(&s_box[k][1], y);
-            if (u > c.z) atomicMax(&s_box[k][2], u);
-            if (y > c.w) atomicMax(&s_box[k][3], y);
+            for (int r = 0; r < kBoxRows; ++r) {
+                const int k = id[r], x = (int)u, y = (int)(y0 + r);
+                if (k < 0 || k >= K) continue;
+                const int4 c = *reinterpret_cast<const int4*>(s_box[k]);
+                if (x < c.x) atomicMin(&s_box[k][0], x);
+                if (y < c.y) atomicMin(&s_box[k][1], y);
+                if (x > c.z) atomicMax(&s_box[k][2], x);
+                if (y > c.w) atomicMax(&s_box[k][3], y);
+            }
         }
     }
     __syncthreads();
@@ -346,7 +351,9 @@ hipError_t launch_id_boxes(const int32_t* id_map, int n_views, int W, int H, int
     const int n = n_views * K;
     const dim3 per_box((unsigned)((n + kBoxThreads - 1) / kBoxThreads));
     hipLaunchKernelGGL(id_boxes_clear_kernel, per_box, dim3(kBoxThreads), 0, st, n, W, H, (int*)boxes);
-    hipLaunchKernelGGL(id_boxes_kernel, dim3((unsigned)((H + kBoxRows - 1) / kBoxRows), (unsigned)n_views),
+    // a strip per workgroup up to 2^16 of them (a launch holds fewer than 2^32 threads)
+    const int64_t strips = std::min<int64_t>(1 << 16, ((int64_t)H + kBoxRows - 1) / kBoxRows);
+    hipLaunchKernelGGL(id_boxes_kernel, dim3((unsigned)strips, (unsigned)n_views),
                        dim3(kBoxThreads), 0, st, id_map, W, H, K, (int*)boxes);
     hipLaunchKernelGGL(id_boxes_finish_kernel, per_box, dim3(kBoxThreads), 0, st, n, K, (int*)boxes, box_obj,
                        box_view);
