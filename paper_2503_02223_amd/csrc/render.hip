@@ -1127,7 +1127,8 @@ __global__ __launch_bounds__(kWave) void suffix_state_kernel(
                 // gradient of a probability that is zero may be infinite or NaN
                 dp[q] = T(0);
                 if constexpr (PROBS) {
-                    if (a[q] != T(0) && (uint32_t)id < (uint32_t)K) dp[q] = s_dP[id * kWave + lane];
+                    const T g = s_dP[min((uint32_t)id, (uint32_t)K - 1u) * kWave + lane];
+                    dp[q] = (a[q] != T(0)) & ((uint32_t)id < (uint32_t)K) ? g : T(0);
                 }
             }
 #pragma unroll
