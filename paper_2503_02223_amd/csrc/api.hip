@@ -36,7 +36,7 @@ struct Geo {
     // scratch sub-offsets (relative to DQO_BUF_SCRATCH)
     int64_t off_dk1, off_dv1, off_dk2, off_dv2, off_pk1, off_pv1, off_sched, off_sums, off_pose, off_written, off_sbase, off_seg,
         off_sgbase, off_tlast, off_ckpt, off_suf, off_suflist, off_dcnt, off_lbd, off_lbs, off_lbp;
-    int64_t seg_cap, ckpt_cap, suf_cap;
+    int64_t seg_cap, ckpt_cap, suf_cap, suf_list_cap;
     bool tile_sort;     // per-tile depth order (dqo_depth_order TILE)
     int tile_sort_lds;  // pairs of a tile sorted in LDS
 };
@@ -127,31 +127,37 @@ Geo geometry(const dqo_ctx* ctx, const dqo_frame_desc* d, const dqo_camera* cams
     sz[DQO_BUF_PARTIALS] = cap * kGradWords * ts;
     sz[DQO_BUF_CONTROL] = (int64_t)sizeof(Ctrl);
     int64_t so = 0;
-    g.off_dk1 = so; so = align256(so + M * 4);
-    g.off_dv1 = so; so = align256(so + M * 4);
-    g.off_dk2 = so; so = align256(so + M * 4);
-    g.off_dv2 = so; so = align256(so + M * 4);
-    g.off_pk1 = so; so = align256(so + cap * 4);
-    g.off_pv1 = so; so = align256(so + cap * 4);
-    g.off_sched = so; so = align256(so + tiles_total * 4);
-    g.off_sums = so; so = align256(so + M * kGradWords * ts);
-    g.off_pose = so; so = align256(so + (int64_t)d->n_views * ((d->n + 255) / 256) * 6 * 8);
-    g.off_written = so; so = align256(so + cap);
-    g.off_sbase = so; so = align256(so + (int64_t)scan_blocks_max * 4);
     // segment boundaries (64-pixel tiles, frames the backward segments):
     // sum over tiles of ceil(range / L) - 1 <= cap / L
     g.ckpt_cap = (tw * th == kWave && tiles_total <= kSegTilesMax) ? cap / kSegLen + 1 : 0;
+    g.seg_cap = g.ckpt_cap ? tiles_total + g.ckpt_cap : 0;
     const int parts = tw * th / kWave;
     g.suf_cap = tiles_total * parts <= kSuffixPartsMax && (parts > 1 || d->K > 0) ? cap / kSegLen + 1 : 0;
     // (a launch holds fewer than 2^32 work items: 256-pixel tiles at the largest capacities go without)
     if ((tiles_total + g.suf_cap + 8 * kXcdChunk) * tw * th >= (int64_t(1) << 32)) g.suf_cap = 0;
-    g.seg_cap = tiles_total + std::max(g.ckpt_cap, g.suf_cap);
+    g.suf_list_cap = g.suf_cap ? tiles_total + g.suf_cap : 0;
+    // The suffix states (2 T per pixel and 64 pairs of capacity: 8 to 32 bytes
+    // a pair in FP32) live from a render backward's suffix pass to its end.
+    // They share memory with what holds nothing then: the depth passes'
+    // buffers and the per-item sums, 56 bytes an item in FP32.
+    g.off_suf = so;
+    g.off_dk1 = so; so = align256(so + M * 4);
+    g.off_dv1 = so; so = align256(so + M * 4);
+    g.off_dk2 = so; so = align256(so + M * 4);
+    g.off_dv2 = so; so = align256(so + M * 4);
+    g.off_sums = so; so = align256(so + M * kGradWords * ts);
+    so = std::max(so, align256(g.off_suf + g.suf_cap * 2 * tw * th * ts));
+    g.off_pk1 = so; so = align256(so + cap * 4);
+    g.off_pv1 = so; so = align256(so + cap * 4);
+    g.off_sched = so; so = align256(so + tiles_total * 4);
+    g.off_pose = so; so = align256(so + (int64_t)d->n_views * ((d->n + 255) / 256) * 6 * 8);
+    g.off_written = so; so = align256(so + cap);
+    g.off_sbase = so; so = align256(so + (int64_t)scan_blocks_max * 4);
     g.off_seg = so; so = align256(so + g.seg_cap * 16);
     g.off_sgbase = so; so = align256(so + tiles_total * 4);
-    g.off_tlast = so; so = align256(so + tiles_total * parts * 4);
+    g.off_tlast = so; so = align256(so + (g.suf_cap ? tiles_total * parts * 4 : 0));
     g.off_ckpt = so; so = align256(so + g.ckpt_cap * 6 * kWave * ts);
-    g.off_suf = so; so = align256(so + g.suf_cap * 2 * tw * th * ts);
-    g.off_suflist = so; so = align256(so + (g.suf_cap ? g.seg_cap * 8 : 0));
+    g.off_suflist = so; so = align256(so + g.suf_list_cap * 8);
     g.off_dcnt = so; so = align256(so + split_count_words(std::max(M, cap)) * 4);
     // look-back words: every block's, then every group's (grouped look-back)
     g.off_lbd = so; so = align256(so + (int64_t)kMaxDepthPasses * lb_blocks(depth_blocks_max) * kRadixBins * 8);
@@ -201,6 +207,7 @@ StatePtrs state_ptrs(const Geo& g, void* state) {
     s.suffix = sc + g.off_suf;
     s.suf_list = (uint2*)(sc + g.off_suflist);
     s.suf_cap = g.suf_cap;
+    s.suf_list_cap = g.suf_list_cap;
     s.seg_cap = g.seg_cap;
     s.ckpt_cap = g.ckpt_cap;
     s.ctrl = (Ctrl*)(b + g.L.offset[DQO_BUF_CONTROL]);

@@ -368,16 +368,17 @@ struct StatePtrs {
     // per-pixel states the forward stores at the segment boundaries.
     uint4* seg_list;      // [seg_cap] (tile, first position, walk end, boundary record) in launch order (after the forward)
     uint32_t* seg_base;   // [V*tiles] first entry of each tile's segments in the backward's list
-    int32_t* tile_last;   // [V*tiles][parts] last blended position in each 64-pixel part of a tile
+    int32_t* tile_last;   // [V*tiles][parts] last blended position in each 64-pixel part of a tile (suffix pass)
     void* ckpt;           // [ckpt_cap][6][64] T, colour (3), depth, target probability before each boundary
     int64_t seg_cap, ckpt_cap;
     // Tiles of several 64-pixel parts, and instance-channel gradients: a pass
     // runs the backward's transmittance and suffix recurrence alone and stores
     // them at every kSegLen-th pair, and the gradients of the pairs between
     // are then taken side by side.
-    uint2* suf_list;      // [seg_cap] (tile, segment) in launch order
-    void* suffix;         // [suf_cap][2][pixels of a tile] T and suffix sum behind each boundary
-    int64_t suf_cap;
+    uint2* suf_list;      // [suf_list_cap] (tile, segment) in launch order
+    void* suffix;         // [suf_cap][2][pixels of a tile] T and suffix sum behind each boundary (shared memory:
+                          // holds nothing after the backward that wrote it)
+    int64_t suf_cap, suf_list_cap;
     void* partials;
     void* sums;           // [V*n][kGradWords] per-item totals of the pair partials
     double* pose_partials;  // [V][ceil(n/256)][6] per-block camera-pose gradient sums

@@ -228,8 +228,7 @@ __global__ __launch_bounds__(kWave) void render_forward_kernel(
     int32_t* __restrict__ last, T* __restrict__ probs, int32_t* __restrict__ idmap,
     const int32_t* __restrict__ target, T* __restrict__ ptarget, int32_t* __restrict__ nblend, uint32_t cap,
     uint32_t M, T* __restrict__ ckpt, uint32_t ckpt_cap,
-    int32_t* __restrict__ tile_last, const uint32_t* __restrict__ seg_base, uint4* __restrict__ seg_list,
-    uint32_t seg_cap, Ctrl* __restrict__ ctrl) {
+    const uint32_t* __restrict__ seg_base, uint4* __restrict__ seg_list, uint32_t seg_cap, Ctrl* __restrict__ ctrl) {
     using P = Parts<TW, TH>;
     constexpr int BLOCK = kWave;
     constexpr bool kSeg = P::kCount == 1;  // 64-pixel tiles can store the segmented backward's states
@@ -399,11 +398,10 @@ __global__ __launch_bounds__(kWave) void render_forward_kernel(
     }
     if constexpr (kSeg) {
         if (ckpt) {
-            // The tile's last blended position: how far its backward has work.
+            // the tile's last blended position: how far its backward has work
             int m = lastpos;
 #pragma unroll
             for (int d = 32; d >= 1; d >>= 1) m = max(m, __shfl_xor(m, d));
-            if (tid == 0) tile_last[tile] = m;
             // The tile's entries of the backward's segment list, at the place
             // the sort reserved for its segments: every 64-pair segment up to
             // the last blended position, with the end of its walk (one past
@@ -1011,7 +1009,7 @@ __global__ __launch_bounds__(kWave) void suffix_state_kernel(
     const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ schedule, const T* __restrict__ tfinal,
     const int32_t* __restrict__ last, const int32_t* __restrict__ target, const T* __restrict__ dC,
     const T* __restrict__ dD, const T* __restrict__ dT, const T* __restrict__ dP, const T* __restrict__ dPt,
-    uint32_t cap, uint32_t M, const uint32_t* __restrict__ seg_base, uint2* __restrict__ suf_list, uint32_t seg_cap,
+    uint32_t cap, uint32_t M, const uint32_t* __restrict__ seg_base, uint2* __restrict__ suf_list, uint32_t list_cap,
     T* __restrict__ suffix, uint32_t suf_cap, int32_t* __restrict__ tile_last) {
     using P = Parts<TW, TH>;
     __shared__ __align__(16) T s_sp[kWave * kWalkWords];
@@ -1041,7 +1039,7 @@ __global__ __launch_bounds__(kWave) void suffix_state_kernel(
     if (part == 0) {
         const uint32_t nseg = tile_segments(re - rs), base = seg_base[tile];
         for (uint32_t j = (uint32_t)lane; j < nseg; j += kWave)
-            if (base + j < seg_cap) suf_list[base + j] = make_uint2((uint32_t)tile, j);
+            if (base + j < list_cap) suf_list[base + j] = make_uint2((uint32_t)tile, j);
     }
     BwdPixel<T> b = load_bwd_pixel<T>(V, cs, view, px, py, rs, re, tfinal, last, target, dC, dD, dT, dPt);
     int m = b.lastp;
@@ -1171,7 +1169,7 @@ __global__ __launch_bounds__(TW* TH, sizeof(T) == 8 ? 1 : SUF || PROBS ? 3 : 4) 
     const T* __restrict__ tfinal, const int32_t* __restrict__ last, const int32_t* __restrict__ target,
     const T* __restrict__ dC, const T* __restrict__ dD, const T* __restrict__ dT, const T* __restrict__ dP,
     const T* __restrict__ dPt, T* __restrict__ partials, uint8_t* __restrict__ written, uint32_t cap, uint32_t M,
-    const uint2* __restrict__ suf_list, uint32_t seg_cap, const T* __restrict__ suffix, uint32_t suf_cap,
+    const uint2* __restrict__ suf_list, uint32_t list_cap, const T* __restrict__ suffix, uint32_t suf_cap,
     const int32_t* __restrict__ tile_last, const Ctrl* __restrict__ ctrl) {
     constexpr int NW = TW * TH / kWave, kRows = kWave / TW;
     static_assert(NW >= 1 && NW <= 4 && kWave % TW == 0, "strips of whole rows");
@@ -1191,7 +1189,7 @@ __global__ __launch_bounds__(TW* TH, sizeof(T) == 8 ? 1 : SUF || PROBS ? 3 : 4) 
     uint32_t seg = 0u;
     if constexpr (SUF) {
         const uint32_t unit = seg_unit(blockIdx.x);
-        if (unit >= listed_segments(ctrl->counters[kCounterSegTotal], seg_cap)) return;
+        if (unit >= listed_segments(ctrl->counters[kCounterSegTotal], list_cap)) return;
         const uint2 en = suf_list[unit];
         tile = (int)min(en.x, n_tiles - 1u);
         seg = en.y;
@@ -1581,7 +1579,7 @@ static hipError_t fwd_tile(const Frame<T>& f, const dqo_images& img, hipStream_t
                            f.consts, f.K, (const T*)s.splats, s.pair_vals[0], s.ranges, s.schedule, (T*)img.color,
                            (T*)img.depth, (T*)img.t_final, img.last, (T*)img.probs, img.id_map, img.target,
                            (T*)img.p_target, img.n_blend, (uint32_t)s.capacity, (uint32_t)s.items,
-                           (T*)(seg ? s.ckpt : nullptr), (uint32_t)s.ckpt_cap, s.tile_last, s.seg_base, s.seg_list,
+                           (T*)(seg ? s.ckpt : nullptr), (uint32_t)s.ckpt_cap, s.seg_base, s.seg_list,
                            (uint32_t)s.seg_cap, s.ctrl);
     } else {
         auto kern = img.n_blend ? render_forward_kernel<T, TW, TH, false, true> : render_forward_kernel<T, TW, TH, false, false>;
@@ -1589,7 +1587,7 @@ static hipError_t fwd_tile(const Frame<T>& f, const dqo_images& img, hipStream_t
                            f.consts, f.K, (const T*)s.splats, s.pair_vals[0], s.ranges, s.schedule, (T*)img.color,
                            (T*)img.depth, (T*)img.t_final, img.last, (T*)nullptr, (int32_t*)nullptr, img.target,
                            (T*)img.p_target, img.n_blend, (uint32_t)s.capacity, (uint32_t)s.items,
-                           (T*)(seg ? s.ckpt : nullptr), (uint32_t)s.ckpt_cap, s.tile_last, s.seg_base, s.seg_list,
+                           (T*)(seg ? s.ckpt : nullptr), (uint32_t)s.ckpt_cap, s.seg_base, s.seg_list,
                            (uint32_t)s.seg_cap, s.ctrl);
     }
     return hipGetLastError();
@@ -1608,7 +1606,7 @@ static hipError_t bwd_parts(const Frame<T>& f, const dqo_images& img, const dqo_
                            f.K, (const T*)s.splats, s.pair_vals[0], s.ranges, s.schedule, (const T*)img.t_final,
                            img.last, img.target, (const T*)g.d_color, (const T*)g.d_depth, (const T*)g.d_t_final,
                            (const T*)g.d_probs, (const T*)g.d_p_target, (uint32_t)s.capacity, (uint32_t)s.items,
-                           s.seg_base, s.suf_list, (uint32_t)s.seg_cap, (T*)s.suffix, (uint32_t)s.suf_cap, s.tile_last);
+                           s.seg_base, s.suf_list, (uint32_t)s.suf_list_cap, (T*)s.suffix, (uint32_t)s.suf_cap, s.tile_last);
     }
     if constexpr (PROBS && N > 1) {
         if (!suf && (int64_t)blocks * N > kSegTilesMax) {
@@ -1621,14 +1619,14 @@ static hipError_t bwd_parts(const Frame<T>& f, const dqo_images& img, const dqo_
         }
     }
     const int64_t gq = 8 * kXcdChunk;  // whole XCD chunks
-    const unsigned grid = suf ? (unsigned)((s.seg_cap + gq - 1) / gq * gq) : (unsigned)blocks;
+    const unsigned grid = suf ? (unsigned)((s.suf_list_cap + gq - 1) / gq * gq) : (unsigned)blocks;
     auto kern = suf ? render_backward_tile_kernel<T, TW, TH, PROBS, true>
                     : render_backward_tile_kernel<T, TW, TH, PROBS, false>;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(TW * TH), 0, st, f.views, f.consts, f.K, (const T*)s.splats,
                        s.pair_vals[0], s.ranges, s.schedule, (const T*)img.t_final, img.last, img.target,
                        (const T*)g.d_color, (const T*)g.d_depth, (const T*)g.d_t_final, (const T*)g.d_probs,
                        (const T*)g.d_p_target, (T*)s.partials, s.written, (uint32_t)s.capacity, (uint32_t)s.items,
-                       s.suf_list, (uint32_t)s.seg_cap, (const T*)s.suffix, (uint32_t)s.suf_cap, s.tile_last, s.ctrl);
+                       s.suf_list, (uint32_t)s.suf_list_cap, (const T*)s.suffix, (uint32_t)s.suf_cap, s.tile_last, s.ctrl);
     return hipGetLastError();
 }
 
