@@ -610,7 +610,8 @@ class Rasterizer:
         cap = capacity if capacity is not None else max(1024, 4 * n * (len(cams) if segments is None else 1))
         self.frame = self._new_frame(min(cap, 1 << 30))
         self.generation = 0   # bumped by every bin(): identifies the pair list in the state
-        self._status = None   # of _post_status
+        # of _post_status (pinned memory is not allocated during a capture, where bin cannot wait anyway)
+        self._status = None if torch.cuda.is_current_stream_capturing() else _StatusWords()
 
     def _new_frame(self, capacity):
         return Frame(self.ctx, self.cams, self.n, self.K, capacity, self.dtype, self.device, segments=self.segments,

@@ -46,11 +46,12 @@ def test_made_under_a_default_device(scene):
 
 
 def test_made_inside_a_capture(scene):
-    """Without growth a Rasterizer needs no status words, so one can be made
-    (and its state cleared) while a graph is being captured."""
+    """A Rasterizer made while a graph is being captured (its state cleared in
+    the graph) allocates no status words: it cannot wait for them there."""
     make, p, ids, want = scene
     make().forward(p, ids, grow=False)   # kernels loaded
     torch.cuda.synchronize()
+    B._status_words = []
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g):
         r = make()
