@@ -172,6 +172,9 @@ constexpr int kSegTilesMax = 8192;
 // and 177 / 174, 7680 198 / 158; with instance channels, 8x8 tiles: 1200 210 /
 // 272, 4800 198 / 179, 16x16 tiles: 4800 224 / 235, 16x8: 7680 245 / 208).
 constexpr int kSuffixPartsMax = 4096;
+// With channel gradients and more 64-pixel parts than this, larger tiles are
+// walked in chunks (measured at the kernel).
+constexpr int kStripPartsMax = 8192;
 constexpr int kXcdChunk = 16;      // consecutive backward segments that go to one XCD
 
 // Look-back words: [flag:2 | epoch:30 | value:32].

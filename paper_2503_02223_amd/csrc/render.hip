@@ -1609,7 +1609,7 @@ static hipError_t bwd_parts(const Frame<T>& f, const dqo_images& img, const dqo_
                            s.seg_base, s.suf_list, (uint32_t)s.suf_list_cap, (T*)s.suffix, (uint32_t)s.suf_cap, s.tile_last);
     }
     if constexpr (PROBS && N > 1) {
-        if (!suf && (int64_t)blocks * N > kSegTilesMax) {
+        if (!suf && (int64_t)blocks * N > kStripPartsMax) {
             hipLaunchKernelGGL((render_backward_kernel<T, TW, TH>), dim3(blocks), dim3(TW * TH), 0, st, f.views,
                                f.consts, f.K, (const T*)s.splats, s.pair_vals[0], s.ranges, s.schedule,
                                (const T*)img.t_final, img.last, img.target, (const T*)g.d_color, (const T*)g.d_depth,
@@ -1620,8 +1620,10 @@ static hipError_t bwd_parts(const Frame<T>& f, const dqo_images& img, const dqo_
     }
     const int64_t gq = 8 * kXcdChunk;  // whole XCD chunks
     const unsigned grid = suf ? (unsigned)((s.suf_list_cap + gq - 1) / gq * gq) : (unsigned)blocks;
-    auto kern = suf ? render_backward_tile_kernel<T, TW, TH, PROBS, true>
-                    : render_backward_tile_kernel<T, TW, TH, PROBS, false>;
+    auto kern = render_backward_tile_kernel<T, TW, TH, PROBS, true>;
+    if constexpr (N > 1) {  // (8x8 tiles come here for the suffix pass only)
+        if (!suf) kern = render_backward_tile_kernel<T, TW, TH, PROBS, false>;
+    }
     hipLaunchKernelGGL(kern, dim3(grid), dim3(TW * TH), 0, st, f.views, f.consts, f.K, (const T*)s.splats,
                        s.pair_vals[0], s.ranges, s.schedule, (const T*)img.t_final, img.last, img.target,
                        (const T*)g.d_color, (const T*)g.d_depth, (const T*)g.d_t_final, (const T*)g.d_probs,
