@@ -251,7 +251,8 @@ __global__ __launch_bounds__(256) void project_kernel(Views<T> V, Consts<T> cs, 
 // next item in emission order.  All but the first slots depend on the segments
 // alone, so they are written when the segments differ from the frame's before
 // (a stamp in the state, written by the last workgroup): 88 bytes per item
-// then, 4 otherwise.
+// then, 4 otherwise.  16 crops of 128x128, 983k unlisted items: 5 us, most of
+// it the launch, against 20 with all of it written every frame.
 template <typename T>
 __global__ __launch_bounds__(256) void unlisted_items_kernel(Views<T> V, int64_t n, uint32_t listed, int item_order,
                                                              T* __restrict__ splats, short4* __restrict__ rects,
@@ -308,7 +309,9 @@ template <typename T>
 static hipError_t launch_unlisted_items(const Frame<T>& f, hipStream_t st) {
     const StatePtrs& s = f.s;
     if (s.listed == s.items) return hipGetLastError();
-    const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>(512, (f.n + 255) / 256)), (unsigned)f.views.n_views);
+    // (four workgroups per CU: more of them wait for the counter of those that are done)
+    const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(1024 / f.views.n_views, (f.n + 255) / 256));
+    const dim3 grid((unsigned)blocks, (unsigned)f.views.n_views);
     hipLaunchKernelGGL(unlisted_items_kernel<T>, grid, dim3(256), 0, st, f.views, f.n, (uint32_t)s.listed,
                        s.tile_sort ? 1 : 0, (T*)s.splats, s.rects, s.counts, s.depth_keys[0], s.depth_vals[0],
                        s.offsets, s.ctrl);
@@ -323,8 +326,9 @@ static hipError_t launch_unlisted_items(const Frame<T>& f, hipStream_t st) {
 // emission then reads its block's offset and waits on nothing (eight
 // keyframes, 9.6M items: 206 -> 211 training steps/s).
 __global__ __launch_bounds__(kScanThreads) void scan_block_sums_kernel(const uint32_t* __restrict__ order,
-                                                                      const uint32_t* __restrict__ counts, uint32_t listed,
-                                                                      uint32_t M, uint32_t* __restrict__ sums) {
+                                                                      const uint32_t* __restrict__ counts,
+                                                                      uint32_t listed, uint32_t M,
+                                                                      uint32_t* __restrict__ sums) {
     __shared__ uint32_t s_tmp[kScanThreads / kWave];
     const int tid = threadIdx.x;
     const uint32_t base = blockIdx.x * (uint32_t)kScanTile;
@@ -375,8 +379,9 @@ __global__ __launch_bounds__(kScanThreads) void scan_block_base_kernel(uint32_t*
 // running count per digit).  Needs the whole grid on the device at once.
 template <typename T, bool FUSED>
 __global__ __launch_bounds__(kScanThreads) void scan_emit_kernel(
-    const uint32_t* __restrict__ order, const short4* __restrict__ rects, uint32_t* __restrict__ offsets, T* __restrict__ splats, uint32_t* __restrict__ pkeys, uint32_t* __restrict__ pvals, uint32_t listed,
-    uint32_t M, uint32_t cap, int64_t n, int tiles_x, int tiles_per_view, int hist_passes, int copies, uint64_t* lb, Ctrl* ctrl,
+    const uint32_t* __restrict__ order, const short4* __restrict__ rects, uint32_t* __restrict__ offsets,
+    T* __restrict__ splats, uint32_t* __restrict__ pkeys, uint32_t* __restrict__ pvals, uint32_t listed, uint32_t M,
+    uint32_t cap, int64_t n, int tiles_x, int tiles_per_view, int hist_passes, int copies, uint64_t* lb, Ctrl* ctrl,
     const uint32_t* __restrict__ block_base) {
     __shared__ uint32_t s_incl[kScanTile];
     __shared__ uint32_t s_rec[kScanTile];
@@ -665,10 +670,9 @@ hipError_t launch_project_bin(const Frame<T>& f, const T* params, const int32_t*
     // (a frame whose segments are all empty still clears its ranges)
     hipLaunchKernelGGL(project_kernel<T>,
                        dim3((unsigned)std::max<int64_t>(1, (N + 256 * kProjItems - 1) / (256 * kProjItems))), dim3(256),
-                       0, st, f.views, f.consts,
-                       f.n, (uint32_t)N, s.tile_sort ? 1 : 0, params, ids, (T*)s.splats, s.rects, s.counts, s.depth_keys[0], s.depth_vals[0],
-                       s.ranges, range_words, s.hist_copies_depth, s.ctrl,
-                       s.fused_emit ? &s.ctrl->hist_pair[0][0][0] : nullptr, s.hist_copies_pair);
+                       0, st, f.views, f.consts, f.n, (uint32_t)N, s.tile_sort ? 1 : 0, params, ids, (T*)s.splats,
+                       s.rects, s.counts, s.depth_keys[0], s.depth_vals[0], s.ranges, range_words, s.hist_copies_depth,
+                       s.ctrl, s.fused_emit ? &s.ctrl->hist_pair[0][0][0] : nullptr, s.hist_copies_pair);
     if (N == 0) return launch_unlisted_items(f, st);
     const int dipt = depth_ipt(N);
     const bool split = !radix_resident(kDepthNt, dipt, N);
@@ -678,14 +682,15 @@ hipError_t launch_project_bin(const Frame<T>& f, const T* params, const int32_t*
     for (int p = 0; p < (s.tile_sort ? 0 : kMaxDepthPasses); ++p) {
         const DepthRel rel{p, p == 2 ? s.depth_keys[0] : nullptr, p == 2 ? s.depth_vals[0] : nullptr,
                            p + 1 < kMaxDepthPasses ? &s.ctrl->hist_depth[0][p + 1][0] : nullptr};
-        hipError_t e = split
-            ? launch_split_pass(s.depth_keys[kIn[p]], s.depth_vals[kIn[p]], s.depth_keys[kOut[p]], s.depth_vals[kOut[p]],
-                                nullptr, (uint32_t)N, p * kRadixBits, s.digit_counts, s.ctrl, st, &rel)
-            : launch_radix_pass(s.depth_keys[kIn[p]], s.depth_vals[kIn[p]], s.depth_keys[kOut[p]],
-                                         s.depth_vals[kOut[p]], nullptr, (uint32_t)N, p * kRadixBits,
-                                         &s.ctrl->hist_depth[0][p][0], kMaxDepthPasses * kRadixBins, s.hist_copies_depth,
-                                         s.lb_depth + (size_t)p * lb_blocks(s.depth_blocks) * kRadixBins,
-                                         &s.ctrl->counters[kCounterDepth + p], s.ctrl, st, kDepthNt, dipt, &rel);
+        uint32_t *ki = s.depth_keys[kIn[p]], *vi = s.depth_vals[kIn[p]], *ko = s.depth_keys[kOut[p]],
+                 *vo = s.depth_vals[kOut[p]];
+        hipError_t e =
+            split ? launch_split_pass(ki, vi, ko, vo, nullptr, (uint32_t)N, p * kRadixBits, s.digit_counts, s.ctrl, st,
+                                      &rel)
+                  : launch_radix_pass(ki, vi, ko, vo, nullptr, (uint32_t)N, p * kRadixBits,
+                                      &s.ctrl->hist_depth[0][p][0], kMaxDepthPasses * kRadixBins, s.hist_copies_depth,
+                                      s.lb_depth + (size_t)p * lb_blocks(s.depth_blocks) * kRadixBins,
+                                      &s.ctrl->counters[kCounterDepth + p], s.ctrl, st, kDepthNt, dipt, &rel);
         if (e != hipSuccess) return e;
     }
     // the fused emission writes the first pair pass's output buffer
@@ -698,9 +703,9 @@ hipError_t launch_project_bin(const Frame<T>& f, const T* params, const int32_t*
                            (uint32_t)s.capacity, s.ctrl);
     }
     auto emit = s.fused_emit ? scan_emit_kernel<T, true> : scan_emit_kernel<T, false>;
-    hipLaunchKernelGGL(emit, dim3((unsigned)s.scan_blocks), dim3(kScanThreads), 0, st, item_order(s), s.rects, s.offsets, (T*)s.splats, s.pair_keys[pf], s.pair_vals[pf], (uint32_t)N,
-                       (uint32_t)M, (uint32_t)s.capacity, f.n, f.views.tiles_x, f.views.tiles_per_view,
-                       pair_sort_split(s.capacity) ? 0 : s.pair_passes,
+    hipLaunchKernelGGL(emit, dim3((unsigned)s.scan_blocks), dim3(kScanThreads), 0, st, item_order(s), s.rects, s.offsets,
+                       (T*)s.splats, s.pair_keys[pf], s.pair_vals[pf], (uint32_t)N, (uint32_t)M, (uint32_t)s.capacity,
+                       f.n, f.views.tiles_x, f.views.tiles_per_view, pair_sort_split(s.capacity) ? 0 : s.pair_passes,
                        s.hist_copies_pair, s.lb_scan, s.ctrl, two_level ? (const uint32_t*)s.scan_base : nullptr);
     return launch_unlisted_items(f, st);
 }
@@ -771,8 +776,9 @@ __global__ __launch_bounds__(kSlotWaves * kWave) void slot_sum_kernel(const uint
                                                                       const uint32_t* __restrict__ counts,
                                                                       const uint32_t* __restrict__ offsets,
                                                                       const T* __restrict__ partials,
-                                                                      const uint8_t* __restrict__ written, uint32_t listed,
-                                                                      uint32_t M, uint32_t cap, T* __restrict__ sums) {
+                                                                      const uint8_t* __restrict__ written,
+                                                                      uint32_t listed, uint32_t M, uint32_t cap,
+                                                                      T* __restrict__ sums) {
     __shared__ T s_acc[kSlotWaves][kWave][kGradWords + 1];
     __shared__ uint16_t s_nz[kSlotWaves][kWave];
     __shared__ uint8_t s_start[kSlotWaves][kWave];
