@@ -34,8 +34,8 @@ struct Geo {
     int depth_blocks, scan_blocks, pair_blocks, pair_passes, pair_first_buf;
     int64_t lb_words;
     // scratch sub-offsets (relative to DQO_BUF_SCRATCH)
-    int64_t off_dk1, off_dv1, off_dk2, off_dv2, off_pk1, off_pv1, off_sched, off_sums, off_pose, off_written, off_sbase, off_seg,
-        off_sgbase, off_tlast, off_ckpt, off_suf, off_suflist, off_dcnt, off_lbd, off_lbs, off_lbp;
+    int64_t off_dk1, off_dv1, off_dk2, off_dv2, off_pk1, off_pv1, off_sched, off_sums, off_pose, off_written, off_sbase,
+        off_seg, off_sgbase, off_tlast, off_ckpt, off_suf, off_suflist, off_dcnt, off_lbd, off_lbs, off_lbp;
     int64_t seg_cap, ckpt_cap, suf_cap, suf_list_cap;
     bool tile_sort;     // per-tile depth order (dqo_depth_order TILE)
     int tile_sort_lds;  // pairs of a tile sorted in LDS

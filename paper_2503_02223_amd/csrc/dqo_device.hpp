@@ -171,6 +171,8 @@ constexpr int kSegTilesMax = 8192;
 // it: 1200 parts 169 / 254 us, 2700 159 / 196 and 168 / 209, 4800 170 / 165
 // and 177 / 174, 7680 198 / 158; with instance channels, 8x8 tiles: 1200 210 /
 // 272, 4800 198 / 179, 16x16 tiles: 4800 224 / 235, 16x8: 7680 245 / 208).
+// One line for every shape: 16x16 tiles with channels would still gain 5 % at
+// 4800 parts, and every other shape lose there.
 constexpr int kSuffixPartsMax = 4096;
 // With channel gradients and more 64-pixel parts than this, larger tiles are
 // walked in chunks (measured at the kernel).
@@ -369,7 +371,8 @@ struct StatePtrs {
     // Segmented backward of 64-pixel tiles: a tile's pair range is walked in
     // segments of kSegLen pairs, one wavefront each, restarted from
     // per-pixel states the forward stores at the segment boundaries.
-    uint4* seg_list;      // [seg_cap] (tile, first position, walk end, boundary record) in launch order (after the forward)
+    // [seg_cap] (tile, first position, walk end, boundary record) in launch order (after the forward)
+    uint4* seg_list;
     uint32_t* seg_base;   // [V*tiles] first entry of each tile's segments in the backward's list
     int32_t* tile_last;   // [V*tiles][parts] last blended position in each 64-pixel part of a tile (suffix pass)
     void* ckpt;           // [ckpt_cap][6][64] T, colour (3), depth, target probability before each boundary

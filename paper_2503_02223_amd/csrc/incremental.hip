@@ -78,8 +78,10 @@ __device__ __forceinline__ bool spawns(uint8_t m, double d) { return m != 0 && d
 // (counts, pass 1) and by counting the pixels of its view in front of its run
 // again: that is one mask byte per pixel, read 16 at a time, and the depth of
 // the few pixels with a mask, and no scratch memory is needed.  More runs make
-// a run shorter and the counting longer: at 8 views of 640x480 the write takes
-// 45, 37, 48, 48, 60 and 71 us with 20, 32, 48, 64, 128 and 256 runs.
+// a run shorter and the counting longer.  The write at 640x480 with 16, 32, 64,
+// 128 and 256 runs per view: 8 views, a keyframe batch, 50, 37, 48, 59 and 70
+// us; 2 views 47, 34, 25, 22 and 26; one view, whose 32 workgroups leave most
+// of the CUs idle, 44, 32, 24, 21 and 20.
 constexpr int kDensChunks = 32;
 constexpr int kDensMinChunk = 1024;
 
@@ -240,8 +242,8 @@ hipError_t launch_incremental_masks(const Frame<T>& f, const dqo_images& img, co
     hipLaunchKernelGGL(masks_kernel<T>,
                        dim3((unsigned)((HW + kMaskThreads * kMaskRounds - 1) / (kMaskThreads * kMaskRounds)),
                             (unsigned)f.views.n_views),
-                       dim3(kMaskThreads), 0, st, HW, f.K, (const T*)img.color, (const T*)img.depth, (const T*)img.p_target,
-                       (const T*)tgt.color, (const T*)tgt.depth, tgt.id, inc_cfg<T>(cfg), masks, counts);
+                       dim3(kMaskThreads), 0, st, HW, f.K, (const T*)img.color, (const T*)img.depth,
+                       (const T*)img.p_target, (const T*)tgt.color, (const T*)tgt.depth, tgt.id, inc_cfg<T>(cfg), masks, counts);
     return hipGetLastError();
 }
 

@@ -206,7 +206,8 @@ __global__ __launch_bounds__(256) void conv3x3_kernel(int H, int W, int n_tiles,
                         if constexpr (EPI == kEpiRelu) {
                             o[e] = f2bf_pair(fmaxf(lo + bv[2 * e], 0.0f), fmaxf(hi + bv[2 * e + 1], 0.0f));
                         } else {  // zero where the gate (a ReLU output) is not positive
-                            const uint32_t gw = e == 0 ? gt[m][q].x : e == 1 ? gt[m][q].y : e == 2 ? gt[m][q].z : gt[m][q].w;
+                            const uint32_t gw =
+                                e == 0 ? gt[m][q].x : e == 1 ? gt[m][q].y : e == 2 ? gt[m][q].z : gt[m][q].w;
                             o[e] = f2bf_pair(bf2f((uint16_t)gw) > 0.0f ? lo : 0.0f,
                                              bf2f((uint16_t)(gw >> 16)) > 0.0f ? hi : 0.0f);
                         }
@@ -685,7 +686,8 @@ __global__ __launch_bounds__(kCropThreads) void fallback_kernel(int HW, const fl
 }
 
 __global__ __launch_bounds__(kCropThreads) void psnr_kernel(int HW, const float* __restrict__ color,
-                                                            const float* __restrict__ rgbdm, double* __restrict__ psnr) {
+                                                            const float* __restrict__ rgbdm,
+                                                            double* __restrict__ psnr) {
     __shared__ double ss[kCropThreads / kWave];
     __shared__ int sc[kCropThreads / kWave];
     const int64_t v = blockIdx.x, N = HW;

@@ -271,8 +271,8 @@ __global__ __launch_bounds__(64) void fit_quadric_kernel(int n_obj, int n_views,
 // they only ever widen, so a stale value can cost an atomic but not lose one,
 // and almost every pixel lies inside the bounds that its neighbours have left.
 // Bound by the read of the id map (4 B per pixel): one workgroup per view with
-// four LDS atomics per pixel took 725 us at 640x480, these three launches
-// 12 us.
+// four LDS atomics per pixel took 725 us at 640x480, these three kernels 5 + 8
+// + 5 us.
 constexpr int kBoxThreads = 256;
 constexpr int kBoxRows = 8;
 

@@ -132,8 +132,9 @@ __device__ __forceinline__ void wave_totals(double (&x)[16], int nb, int lane) {
 // 1 - IoU of one box; with GRAD, its gradient with respect to mu, R and
 // w is added to acc[0..2], acc[3..11] (row-major R), acc[12..14].
 template <bool GRAD>
-__device__ __forceinline__ double box_term(const ThetaView& tv, const double* __restrict__ P, const double* __restrict__ o,
-                           const double* __restrict__ wh, double (&acc)[16], double& iou_out) {
+__device__ __forceinline__ double box_term(const ThetaView& tv, const double* __restrict__ P,
+                                           const double* __restrict__ o, const double* __restrict__ wh,
+                                           double (&acc)[16], double& iou_out) {
     // M = P3 R, g = P3 mu + p4
     double M[3][3], g[3];
 #pragma unroll

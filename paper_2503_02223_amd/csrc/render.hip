@@ -220,11 +220,12 @@ struct Parts {
 // One workgroup per tile with its waves in step (a barrier per batch, every
 // wave walking every record that touches the tile) took 202 us on 30k
 // Gaussians at 333x251 in 16x16 tiles with instance channels, 593 us on eight
-// keyframes of 1.2M in 16x8 tiles; with a workgroup per part 110 and 414 us.
+// keyframes of 1.2M in 16x8 tiles; with a workgroup per part 104 and 402 us.
 template <typename T, int TW, int TH, bool PROBS, bool NB = true>
 __global__ __launch_bounds__(kWave) void render_forward_kernel(
     Views<T> V, Consts<T> cs, int K, const T* __restrict__ splats, uint32_t* __restrict__ pvals,
-    const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ schedule, T* __restrict__ color, T* __restrict__ depth, T* __restrict__ tfinal,
+    const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ schedule, T* __restrict__ color,
+    T* __restrict__ depth, T* __restrict__ tfinal,
     int32_t* __restrict__ last, T* __restrict__ probs, int32_t* __restrict__ idmap,
     const int32_t* __restrict__ target, T* __restrict__ ptarget, int32_t* __restrict__ nblend, uint32_t cap,
     uint32_t M, T* __restrict__ ckpt, uint32_t ckpt_cap,
@@ -929,8 +930,8 @@ __global__ __launch_bounds__(kWave, 4) void render_backward_wave_kernel(
 // step, every wave testing every record that touches the tile, the sums through
 // LDS with a barrier for every six, took 445 us on 30k Gaussians at 333x251 in
 // 16x16 tiles with instance channels and 1375 us on eight keyframes of 1.2M in
-// 16x8 tiles; now 52 us, behind
-// 85 us of the recurrence, and 1267 us.  The same sums in the same order.)
+// 16x8 tiles; now 52 us, behind 87 us of the recurrence, and 1244 us.  The same
+// sums in the same order.)
 template <int NS, typename T>
 __device__ __forceinline__ void flush_rows(T (&v)[64], uint32_t chunk, T* __restrict__ rows) {
     int lane = (int)__lane_id();
@@ -1014,7 +1015,8 @@ __global__ __launch_bounds__(kWave) void suffix_state_kernel(
     using P = Parts<TW, TH>;
     __shared__ __align__(16) T s_sp[kWave * kWalkWords];
     extern __shared__ unsigned char s_dyn[];
-    T* s_dP = reinterpret_cast<T*>(s_dyn);  // [K][64] the pixels' channel gradients with PROBS (a gather per record waits longer)
+    // [K][64] the pixels' channel gradients with PROBS (a gather per record waits longer)
+    T* s_dP = reinterpret_cast<T*>(s_dyn);
     const int lane = threadIdx.x;
     const uint32_t n_tiles = (uint32_t)(V.n_views * V.tiles_per_view);
     uint32_t rank = blockIdx.x;
@@ -1606,7 +1608,8 @@ static hipError_t bwd_parts(const Frame<T>& f, const dqo_images& img, const dqo_
                            f.K, (const T*)s.splats, s.pair_vals[0], s.ranges, s.schedule, (const T*)img.t_final,
                            img.last, img.target, (const T*)g.d_color, (const T*)g.d_depth, (const T*)g.d_t_final,
                            (const T*)g.d_probs, (const T*)g.d_p_target, (uint32_t)s.capacity, (uint32_t)s.items,
-                           s.seg_base, s.suf_list, (uint32_t)s.suf_list_cap, (T*)s.suffix, (uint32_t)s.suf_cap, s.tile_last);
+                           s.seg_base, s.suf_list, (uint32_t)s.suf_list_cap, (T*)s.suffix, (uint32_t)s.suf_cap,
+                           s.tile_last);
     }
     if constexpr (PROBS && N > 1) {
         if (!suf && (int64_t)blocks * N > kStripPartsMax) {
@@ -1628,7 +1631,8 @@ static hipError_t bwd_parts(const Frame<T>& f, const dqo_images& img, const dqo_
                        s.pair_vals[0], s.ranges, s.schedule, (const T*)img.t_final, img.last, img.target,
                        (const T*)g.d_color, (const T*)g.d_depth, (const T*)g.d_t_final, (const T*)g.d_probs,
                        (const T*)g.d_p_target, (T*)s.partials, s.written, (uint32_t)s.capacity, (uint32_t)s.items,
-                       s.suf_list, (uint32_t)s.suf_list_cap, (const T*)s.suffix, (uint32_t)s.suf_cap, s.tile_last, s.ctrl);
+                       s.suf_list, (uint32_t)s.suf_list_cap, (const T*)s.suffix, (uint32_t)s.suf_cap, s.tile_last,
+                       s.ctrl);
     return hipGetLastError();
 }
 
@@ -1656,7 +1660,8 @@ static hipError_t bwd_tile(const Frame<T>& f, const dqo_images& img, const dqo_i
                            (const T*)g.d_color, (const T*)g.d_depth, (const T*)g.d_t_final, (const T*)g.d_probs,
                            (const T*)g.d_p_target, (T*)s.partials, s.written, (uint32_t)s.capacity,
                            (uint32_t)s.items, seg ? s.seg_list : nullptr, (uint32_t)s.seg_cap, (const T*)s.ckpt,
-                           (uint32_t)s.ckpt_cap, (const T*)img.color, (const T*)img.depth, (const T*)img.p_target, s.ctrl);
+                           (uint32_t)s.ckpt_cap, (const T*)img.color, (const T*)img.depth, (const T*)img.p_target,
+                           s.ctrl);
         return hipGetLastError();
     } else {
         return g.d_probs ? bwd_parts<T, TW, TH, true>(f, img, g, st) : bwd_parts<T, TW, TH, false>(f, img, g, st);

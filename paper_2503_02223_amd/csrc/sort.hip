@@ -873,8 +873,8 @@ hipError_t launch_pair_sort(const StatePtrs& s, int tiles_total, hipStream_t st)
                            (uint32_t)tiles_total, s.ranges,
                            (uint32_t*)s.written);
         hipLaunchKernelGGL(tile_schedule_kernel, dim3(1), dim3(kSchedThreads), 0, st, s.ranges, tiles_total,
-                           s.schedule, cap, segmented_backward(s, tiles_total) || suffix_backward(s) ? 1 : 0, s.seg_base,
-                           s.ctrl);
+                           s.schedule, cap, segmented_backward(s, tiles_total) || suffix_backward(s) ? 1 : 0,
+                           s.seg_base, s.ctrl);
         if (s.tile_sort)
             hipLaunchKernelGGL(tile_sort_kernel, dim3((unsigned)tiles_total), dim3(kTileSortThreads), 0, st, s.ranges,
                                s.schedule, s.depth_keys[0], (uint32_t)s.items, cap, (uint32_t)s.tile_sort_lds,

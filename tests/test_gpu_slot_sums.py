@@ -24,7 +24,9 @@ def test_slots_end_with_the_wave(order, stray):
           (("d_color", "color"), ("d_depth", "depth"), ("d_t_final", "t_final"))}
     want = r.backward(p, img, up)
     f = r.frame
-    seq = f.buf("depth_order", torch.int32, n).long() if order == B.DEPTH_ORDER_GLOBAL else torch.arange(n, device="cuda")
+    seq = torch.arange(n, device="cuda")
+    if order == B.DEPTH_ORDER_GLOBAL:
+        seq = f.buf("depth_order", torch.int32, n).long()
     counts, offsets = f.buf("counts", torch.int32, n), f.buf("offsets", torch.int32, n)
     waves = [w for w in range(64, n, 64) if counts[seq[w]] > 0 and want[:, seq[w - 1]].abs().max() > 0]
     assert len(waves) >= 4
