@@ -38,14 +38,15 @@ FLOP_PER_EXAMINED = 60.0
 BYTES_PER_PAIR, BYTES_PER_PIXEL, BYTES_PER_WRITTEN = 44.0, 32.0, 40.0
 # HBM bytes per launch of the render backward from rocprofv3 FETCH_SIZE + WRITE_SIZE
 # (scaled by a 256 MiB copy: x2.000 and x1.000), valid only for the kernel source
-# they were taken with (render.hip and dqo_device.hpp); reported as null otherwise.
-MEASURED_TRAFFIC = {"render_src_sha256_16": "dd985657367030ee", "bytes_per_launch": 145650000}
+# they were taken with (render.hip, dqo_device.hpp and segments.hpp); reported as null
+# otherwise.
+MEASURED_TRAFFIC = {"render_src_sha256_16": "69e86f710e93cd0c", "bytes_per_launch": 145650000}
 
 
 def measured_traffic():
     import hashlib
     h = hashlib.sha256()
-    for name in ("render.hip", "dqo_device.hpp"):  # the kernel and its constants
+    for name in ("render.hip", "dqo_device.hpp", "segments.hpp"):  # the kernel and its constants
         with open(os.path.join(ROOT, "paper_2503_02223_amd", "csrc", name), "rb") as fh:
             h.update(fh.read())
     h = h.hexdigest()[:16]

@@ -252,7 +252,9 @@ __global__ __launch_bounds__(256) void project_kernel(Views<T> V, Consts<T> cs, 
 // alone, so they are written when the segments differ from the frame's before
 // (a stamp in the state, written by the last workgroup): 88 bytes per item
 // then, 4 otherwise.  16 crops of 128x128, 983k unlisted items: 5 us, most of
-// it the launch, against 20 with all of it written every frame.
+// it the launch, against 20 with all of it written every frame; 8 keyframes and
+// 8 jobs of 1.2M Gaussians, 9.5M of them: 61 us, where the projection, which
+// wrote their counts and rectangles every frame, went from 379 to 311.
 template <typename T>
 __global__ __launch_bounds__(256) void unlisted_items_kernel(Views<T> V, int64_t n, uint32_t listed, int item_order,
                                                              T* __restrict__ splats, short4* __restrict__ rects,
